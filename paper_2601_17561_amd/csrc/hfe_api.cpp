@@ -646,6 +646,13 @@ static hfe_status chain_encrypt_db_impl(const hfe_keys* K, const int8_t* m_db, i
   a.R = D->R;
   a.k_db = K->k_db;
   a.p = K->cP;
+  // the errors are the same integers for every modulus: drawn once
+  DevBuf errs;
+  if (P.log_n_db <= (uint32_t)kMaxLogN) {
+    HFE_TRY(errs.alloc((size_t)D->K * d1, s));
+    HFE_LAUNCH(launch_errors(seed, kDbE, a.cdt, D->K, d1, errs.as<int8_t>(), s));
+    a.e = errs.as<int8_t>();
+  }
   for (int i = 0; i < nm; ++i) {
     uint64_t* Di = keep_plain ? D->Dt.as<uint64_t>() + (size_t)i * prime_elems : one.as<uint64_t>();
     HFE_LAUNCH(launch_db_encrypt(a, Di, chain_stream(K->cbase[i]), K->cmod[i], K->tab_db[0].tab,
@@ -716,6 +723,13 @@ static hfe_status encrypt_db_impl(const hfe_keys* K, const int8_t* m_db, int64_t
   a.R = D->R;
   a.k_db = K->k_db;
   a.p = P.p;
+  // the errors are the same integers for every modulus: drawn once
+  DevBuf errs;
+  if (P.log_n_db <= (uint32_t)kMaxLogN) {
+    HFE_TRY(errs.alloc((size_t)D->K * d1, s));
+    HFE_LAUNCH(launch_errors(seed, kDbE, a.cdt, D->K, d1, errs.as<int8_t>(), s));
+    a.e = errs.as<int8_t>();
+  }
   for (int z = 0; z < np; ++z) {
     uint64_t* Dz = keep_plain ? D->Dt.as<uint64_t>() + (size_t)z * prime_elems : one.as<uint64_t>();
     HFE_LAUNCH(launch_db_encrypt(a, Dz, K->prime_id[z], K->mods[z], K->tab_db[z].tab,
@@ -792,14 +806,13 @@ hfe_status hfe_encrypt(const hfe_keys* keys, const int8_t* m_q, int64_t d3, uint
   a.d2 = P.d2;
   a.K = Q->K;
   a.k = K->k;
-  // the errors are the same integers for every prime: drawn once when more than one prime needs them
-  // (the LDS-resident transforms; the two-pass ones draw their own)
+  // the errors are the same integers for every prime: drawn once (the two-pass transforms draw their own)
   DevBuf errs;
-  if (level > 1 && P.log_n_q <= (uint32_t)kMaxLogN) {
+  if (P.log_n_q <= (uint32_t)kMaxLogN) {
     st = errs.alloc((size_t)d3 * P.d2, s);
     if (st == HFE_OK) {
-      const hipError_t e = launch_q_errors(seed, a.cdt, d3, P.d2, errs.as<int8_t>(), s);
-      if (e != hipSuccess) st = hip_fail(e, "launch_q_errors");
+      const hipError_t e = launch_errors(seed, kQE, a.cdt, d3, P.d2, errs.as<int8_t>(), s);
+      if (e != hipSuccess) st = hip_fail(e, "launch_errors");
     }
     if (st != HFE_OK) {
       delete Q;
@@ -808,19 +821,21 @@ hfe_status hfe_encrypt(const hfe_keys* keys, const int8_t* m_q, int64_t d3, uint
     a.e = errs.as<int8_t>();
   }
   const int dl = delta_log(K, (int)level);
+  QEncModuli b;
+  std::memset(&b, 0, sizeof(b));
   for (uint32_t i = 0; i < level; ++i) {
     // the n^2 chain: modulus n_i^2, products with the secrets through the NTT prime (slot 0)
     const bool ch = K->family != 0;
-    const Mod& md = ch ? K->cmod[i] : K->mods[i];
-    const uint64_t delta_mod = pow_mod(2, (uint64_t)dl, md.q);
-    hipError_t e = launch_q_encrypt(a, Q->XT.as<uint64_t>() + (size_t)i * d3 * Q->K,
-                                    ch ? chain_stream(K->cbase[i]) : K->prime_id[i], md, delta_mod,
-                                    K->tab_q[ch ? 0 : i].tab,
-                                    K->s_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k * 2 * nq, s);
-    if (e != hipSuccess) {
-      delete Q;
-      return hip_fail(e, "launch_q_encrypt");
-    }
+    b.M[i] = ch ? K->cmod[i] : K->mods[i];
+    b.id[i] = ch ? chain_stream(K->cbase[i]) : K->prime_id[i];
+    b.delta[i] = pow_mod(2, (uint64_t)dl, b.M[i].q);
+    b.T[i] = K->tab_q[ch ? 0 : i].tab;
+    b.s_hat[i] = K->s_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k * 2 * nq;
+  }
+  const hipError_t e = launch_q_encrypt(a, b, (int)level, Q->XT.as<uint64_t>(), s);
+  if (e != hipSuccess) {
+    delete Q;
+    return hip_fail(e, "launch_q_encrypt");
   }
   st = check_ternary_end(chk, "m_q");  // a refused input: the ciphertext is freed in stream order
   if (st != HFE_OK) {
@@ -2102,11 +2117,14 @@ hfe_status hfe::decrypt_impl(const hfe_keys* K, const hfe_rct* R, double* v, int
   const int64_t ndb = 1ll << P.log_n_db;
   const int level = R->level;
   const bool ch = K->family != 0;  // n^2 chain: moduli cmod, secret products through the NTT prime
-  for (int i = 0; i < level; ++i)
-    HFE_LAUNCH(launch_dec_products(R->outp + (size_t)i * R->d3 * R->R_out, R->d3, R->R_out, R->row0, R->rows,
-                                   (int)P.log_n_db, K->tab_db[ch ? 0 : i].tab,
-                                   K->sdb_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k_db * 2 * ndb, K->k_db,
-                                   y + (size_t)i * R->d3 * R->rows, s, ch ? &K->cmod[i] : nullptr));
+  DecModuli b;
+  std::memset(&b, 0, sizeof(b));
+  for (int i = 0; i < level; ++i) {
+    b.M[i] = ch ? K->cmod[i] : K->mods[i];
+    b.T[i] = K->tab_db[ch ? 0 : i].tab;
+    b.s_hat[i] = K->sdb_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k_db * 2 * ndb;
+  }
+  HFE_LAUNCH(launch_dec_products(R->outp, R->d3, R->R_out, R->row0, R->rows, (int)P.log_n_db, b, level, K->k_db, y, s));
   DecodeArgs da;
   std::memset(&da, 0, sizeof(da));
   da.level = level;

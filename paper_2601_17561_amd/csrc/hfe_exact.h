@@ -49,6 +49,12 @@ HFE_HD double reduce_c_d(double x, double q, double qinv) {
 #pragma clang fp contract(off)
   return __builtin_fma(-__builtin_rint(x * qinv), q, x);
 }
+// A signed 64-bit integer x to a representative of x mod q of magnitude at most (1/2 + 2^-11) q, for any q < 2^36
+// and c32 = 2^32 mod q: x = h 2^32 + l with |h| <= 2^31 and 0 <= l < 2^32, the product h c32 (below 2^67) centered
+// as by mulmod_c_d, the sum below 2^36 + 2^32 an exact integer, reduced by reduce_c_d.
+HFE_HD double signed64_mod(int64_t x, double c32, double q, double qinv) {
+  return reduce_c_d(mulmod_c_d((double)(int32_t)(x >> 32), c32, q, qinv) + (double)(uint32_t)x, q, qinv);
+}
 // A centered value (|x| < q) to its residue in [0, q).
 HFE_HD double residue_of_c(double x, double q) { return x < 0.0 ? x + q : x; }
 // Cooley-Tukey butterfly on signed values: (X, Y) -> (X + W Y, X - W Y) with W Y centered.  Each

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "hfe_internal.h"
+#include "hfe_ntt_plan.h"
 #include "hfe_slots.h"
 
 namespace hfe {
@@ -188,6 +189,7 @@ hfe_status fold_keygen_impl(int logn, int k, int rho, uint64_t seed, hfe_foldkey
     const uint64_t q = primes[z];
     C.zd[z] = (double)q;
     C.zinv[z] = 1.0 / (double)q;
+    C.c32[z] = (double)((1ull << 32) % q);
     C.mod[z] = make_mod(q);
     C.pid[z] = z < 5 ? (uint32_t)z : 16u;
     ntt_tables_host(q, logn, tab);  // psi | psi_sh | ipsi | ipsi_sh
@@ -280,10 +282,11 @@ hfe_status fold_keygen_impl(int logn, int k, int rho, uint64_t seed, hfe_foldkey
     DevBuf sg_hat;
     HFE_TRY(small_hat(F, sg, sg_hat, s));
     HFE_TRY(make_ks_key(F, seed, 3 + (int)a, kRotLevel, sg_hat, F->rot.as<double>() + a * per_key, s));
-    // output point i is a(psi^(e_i g)) with e_i = 2 brv(i) + 1: the input point k with e_k = e_i g mod 2N
+    // (indices in the order of the transforms) output point i is a(psi^(e_i g)) with e_i = 2 brv(i) + 1: the input point k with e_k = e_i g mod 2N
     for (int i = 0; i < n; ++i) {
       const uint64_t e = (2ull * brv((uint32_t)i, logn) + 1) * g % (2ull * n);
-      perm[a * n + (size_t)i] = (int32_t)brv((uint32_t)((e - 1) / 2), logn);
+      const int from = (int)brv((uint32_t)((e - 1) / 2), logn);
+      perm[a * n + (size_t)ntt_index(logn, false, i)] = ntt_index(logn, false, from);
     }
   }
   HFE_TRY(put(F->perm, perm.data(), perm.size() * sizeof(int32_t), s));
@@ -337,7 +340,7 @@ hfe_status rescale(const Ev& e, const uint64_t* x, int l, uint64_t* out, const u
   ia.pmi = (l + 1) * e.N;
   FD_LAUNCH(launch_fold_inv(e.C, ia, e.n * 2, e.s));
   FoldLift la;
-  la.cen = cen.as<int64_t>();
+  la.cen = cen.as<double>();
   la.pm = pm;
   la.pmi = (l + 1) * e.N;
   la.x = x;
@@ -384,7 +387,7 @@ hfe_status ks_sums(const Ev& e, int l, const uint64_t* src, const uint64_t* y, i
   }
   FD_LAUNCH(launch_fold_inv(e.C, ia, e.n, e.s));
   FD_LAUNCH(launch_fold_ks_mac(e.C, l, ia, dig.as<uint64_t>(), keys, kstride, kidx, acc.as<uint64_t>(),
-                               accp.as<int64_t>(), e.n, e.s));
+                               accp.as<double>(), e.n, e.s));
   return HFE_OK;
 }
 
@@ -393,7 +396,7 @@ hfe_status key_switch(const Ev& e, int l, const uint64_t* src, const uint64_t* y
                       int64_t kstride, const int32_t* kidx, FoldLift tail) {
   DevBuf acc, accp;
   HFE_TRY(ks_sums(e, l, src, y, si, keys, kstride, kidx, acc, accp));
-  tail.cen = accp.as<int64_t>();
+  tail.cen = accp.as<double>();
   tail.x = acc.as<uint64_t>();
   tail.xi = 2 * (l + 1) * e.N;
   tail.xp = (l + 1) * e.N;
@@ -423,32 +426,31 @@ hfe_status mul(const Ev& e, const uint64_t* x, const uint64_t* y, int l, uint64_
     tail.oi = 2 * per;
     tail.op = per;
     if (add2) {
-      tail.add2 = add2;
-      tail.a2i = 2 * per;
-      tail.a2p = per;
+      tail.add = add2;
+      tail.ai = 2 * per;
+      tail.ap = per;
     }
     return key_switch(e, l, x + per, y + per, 2 * per, key, 0, nullptr, tail);
   }
   DevBuf acc, accp, cen;
   HFE_TRY(ks_sums(e, l, x + per, y + per, 2 * per, key, 0, nullptr, acc, accp));
   HFE_TRY(cen.alloc((size_t)e.n * 2 * e.N * 8, e.s));
-  FD_LAUNCH(launch_fold_relin_center(e.C, l, acc.as<uint64_t>(), accp.as<int64_t>(), x, y, e.n, cen.as<int64_t>(),
+  FD_LAUNCH(launch_fold_relin_center(e.C, l, acc.as<uint64_t>(), accp.as<double>(), x, y, e.n, cen.as<int64_t>(),
                                      e.s));
   const int64_t po = l * e.N;  // the output's slots q_0 .. q_{l-1}
-  tail.cen = cen.as<int64_t>();
+  tail.cen64 = cen.as<int64_t>();
   tail.x = acc.as<uint64_t>();
   tail.xi = 2 * per;
   tail.xp = per;
   tail.oi = 2 * po;
   tail.op = po;
   if (add2) {
-    tail.add2 = add2;
-    tail.a2i = 2 * po;
-    tail.a2p = po;
+    tail.add = add2;
+    tail.ai = 2 * po;
+    tail.ap = po;
   }
   tail.zm = slots_upto(l - 1, false);
   tail.nsl = l;
-  tail.has_tscale = 1;
   const uint64_t p = e.C.mod[5].q, ql = e.C.mod[l].q;
   for (int j = 0; j < l; ++j) {
     const uint64_t qj = e.C.mod[j].q;
@@ -472,7 +474,6 @@ hfe_status const_term(const Ev& e, const uint64_t* x, const uint64_t* u, int l, 
   la.x = x;
   la.xi = 2 * (l + 1) * e.N;
   la.xp = (l + 1) * e.N;
-  la.has_xmul = 1;
   la.xmul = const_res(e.C, k, to + 1);
   la.cres = const_res(e.C, c, to + 1);
   la.out = out.as<uint64_t>();
@@ -501,7 +502,7 @@ hfe_status rotate(const hfe_foldkeys* F, hipStream_t s, const uint64_t* x, const
   FoldLift tail;
   tail.add = P.as<uint64_t>();  // sigma(b), to part 0 only
   tail.ai = per;
-  tail.ap = 0;
+  tail.add_b = 1;
   tail.out = out;
   tail.oi = per;
   tail.op = nsl * N;
@@ -516,6 +517,48 @@ hfe_status fold_impl(const hfe_foldkeys* F, const hfe_fct* in, const int32_t* co
   const int logn = C.logn;
   Ev e{F, C, s, n, N};
   const int64_t* k = reinterpret_cast<const int64_t*>(F->ksum);
+  // The index tables of the rotations inside each group, the group sums and the rotation of group r by r k, in one
+  // copy before any work is queued: a copy between the passes would leave the device idle while the host waits.
+  const int kf = F->k;
+  const int64_t blocks = n / rho, gpb = (rho + kf - 1) / kf, groups = blocks * gpb;
+  auto amount_index = [&](int a) -> int32_t {
+    for (size_t i = 0; i < F->amounts.size(); ++i)
+      if (F->amounts[i] == a) return (int32_t)i;
+    return -1;
+  };
+  std::vector<int32_t> src1, amt1, beg(1, 0), mem, src2, amt2;
+  for (int64_t b = 0; b < blocks; ++b)
+    for (int64_t r = 0; r < gpb; ++r) {
+      const int64_t first = b * rho + r * kf;
+      mem.push_back((int32_t)(first * 2));
+      for (int64_t rp = 1; rp < std::min<int64_t>(kf, rho - r * kf); ++rp) {
+        mem.push_back((int32_t)(src1.size() * 2 + 1));
+        src1.push_back((int32_t)(first + rp));
+        amt1.push_back(amount_index((int)rp));
+      }
+      beg.push_back((int32_t)mem.size());
+      if (r) {
+        src2.push_back((int32_t)(b * gpb + r));
+        amt2.push_back(amount_index((int)(r * kf)));
+      }
+    }
+  for (int32_t a : amt1)
+    if (a < 0) return fail(HFE_EINVAL, "rotation amount without a key");
+  for (int32_t a : amt2)
+    if (a < 0) return fail(HFE_EINVAL, "rotation amount without a key");
+  DevBuf tables;
+  std::vector<int32_t> all;
+  size_t at[6];
+  const std::vector<int32_t>* parts[6] = {&src1, &amt1, &beg, &mem, &src2, &amt2};
+  for (int i = 0; i < 6; ++i) {
+    at[i] = all.size();
+    all.insert(all.end(), parts[i]->begin(), parts[i]->end());
+  }
+  HFE_TRY(put(tables, all.data(), all.size() * 4, s));
+  auto table = [&](int i) { return tables.as<int32_t>() + at[i]; };
+  const int32_t *d_src1 = table(0), *d_amt1 = table(1), *d_beg = table(2), *d_mem = table(3), *d_src2 = table(4),
+                *d_amt2 = table(5);
+
   if (ev) FD_LAUNCH(hipEventRecord(ev[0], s));
 
   // mu = Ecd(1 / counts) at scale 2^40, NTT at q_0 .. q_4
@@ -574,60 +617,23 @@ hfe_status fold_impl(const hfe_foldkeys* F, const hfe_fct* in, const int32_t* co
   if (ev) FD_LAUNCH(hipEventRecord(ev[3], s));
 
   // rotations inside each group, the group sums, and the rotation of group r by r k
-  const int kf = F->k;
-  const int64_t blocks = n / rho, gpb = (rho + kf - 1) / kf, groups = blocks * gpb;
-  auto amount_index = [&](int a) -> int32_t {
-    for (size_t i = 0; i < F->amounts.size(); ++i)
-      if (F->amounts[i] == a) return (int32_t)i;
-    return -1;
-  };
-  std::vector<int32_t> src1, amt1, beg(1, 0), mem, src2, amt2;
-  for (int64_t b = 0; b < blocks; ++b)
-    for (int64_t r = 0; r < gpb; ++r) {
-      const int64_t first = b * rho + r * kf;
-      mem.push_back((int32_t)(first * 2));
-      for (int64_t rp = 1; rp < std::min<int64_t>(kf, rho - r * kf); ++rp) {
-        mem.push_back((int32_t)(src1.size() * 2 + 1));
-        src1.push_back((int32_t)(first + rp));
-        amt1.push_back(amount_index((int)rp));
-      }
-      beg.push_back((int32_t)mem.size());
-      if (r) {
-        src2.push_back((int32_t)(b * gpb + r));
-        amt2.push_back(amount_index((int)(r * kf)));
-      }
-    }
-  for (int32_t a : amt1)
-    if (a < 0) return fail(HFE_EINVAL, "rotation amount without a key");
-  for (int32_t a : amt2)
-    if (a < 0) return fail(HFE_EINVAL, "rotation amount without a key");
-  DevBuf d_src1, d_amt1, d_beg, d_mem, d_src2, d_amt2, R1, R2;
-  auto up = [&](DevBuf& b, const std::vector<int32_t>& v) -> hfe_status {
-    if (v.empty()) return HFE_OK;
-    return put(b, v.data(), v.size() * 4, s);
-  };
-  HFE_TRY(up(d_src1, src1));
-  HFE_TRY(up(d_amt1, amt1));
-  HFE_TRY(up(d_beg, beg));
-  HFE_TRY(up(d_mem, mem));
-  HFE_TRY(up(d_src2, src2));
-  HFE_TRY(up(d_amt2, amt2));
+  DevBuf R1, R2;
   const int nr = kRotLevel + 1;
   const int64_t per = 2 * nr * N;
   if (!src1.empty()) {
     HFE_TRY(R1.alloc(src1.size() * per * 8, s));
-    HFE_TRY(rotate(F, s, f.as<uint64_t>(), d_src1.as<int32_t>(), d_amt1.as<int32_t>(), (int64_t)src1.size(),
+    HFE_TRY(rotate(F, s, f.as<uint64_t>(), d_src1, d_amt1, (int64_t)src1.size(),
                    R1.as<uint64_t>()));
   }
   DevBuf sums;
   HFE_TRY(sums.alloc((size_t)groups * per * 8, s));
-  FD_LAUNCH(launch_fold_group_sum(C, f.as<uint64_t>(), R1.as<uint64_t>(), d_beg.as<int32_t>(), d_mem.as<int32_t>(),
+  FD_LAUNCH(launch_fold_group_sum(C, f.as<uint64_t>(), R1.as<uint64_t>(), d_beg, d_mem,
                                   sums.as<uint64_t>(), groups, nr, s));
   if (!src2.empty()) {
     HFE_TRY(R2.alloc(src2.size() * per * 8, s));
-    HFE_TRY(rotate(F, s, sums.as<uint64_t>(), d_src2.as<int32_t>(), d_amt2.as<int32_t>(), (int64_t)src2.size(),
+    HFE_TRY(rotate(F, s, sums.as<uint64_t>(), d_src2, d_amt2, (int64_t)src2.size(),
                    R2.as<uint64_t>()));
-    FD_LAUNCH(launch_fold_scatter(C, R2.as<uint64_t>(), d_src2.as<int32_t>(), sums.as<uint64_t>(),
+    FD_LAUNCH(launch_fold_scatter(C, R2.as<uint64_t>(), d_src2, sums.as<uint64_t>(),
                                   (int64_t)src2.size(), nr, s));
   }
   // RS by q_1: the folded sums at level 0, scale F
@@ -772,7 +778,7 @@ hfe_status hfe_fold_decrypt(const hfe_foldkeys* fk, const hfe_fct* ct, double* v
   ia.nsl = 1;
   ia.mode = 1;
   FD_LAUNCH(launch_fold_inv(C, ia, X->count, s));
-  FD_LAUNCH(launch_fold_decode(m.as<int64_t>(), X->count, C.logn, F->slot_w.as<double>(), F->slot_z.as<double>(),
+  FD_LAUNCH(launch_fold_decode(m.as<double>(), X->count, C.logn, F->slot_w.as<double>(), F->slot_z.as<double>(),
                                F->slot_k.as<int32_t>(), 1.0 / X->scale, values, s));
   FD_LAUNCH(hipStreamSynchronize(s));
   return HFE_OK;

@@ -196,8 +196,9 @@ int cdt_table_quad_impl(uint64_t* dst);  // hfe_cdt.cpp (quad precision), 0 on s
 // All launchers enqueue on `s` and return hipGetLastError() of the launch.
 // Negacyclic forward NTT in place of `count` polynomials of length n = 2^tab.logn starting at
 // a + i * stride; with_shoup also writes the Shoup companions at a + i * stride + n.
+// The result is in the order of the register transforms (hfe_ntt_reg.h): by_ntt's, or by_ntt_acc's with acc_order.
 hipError_t launch_ntt_fwd(uint64_t* a, int64_t count, int64_t stride, NttTab tab, bool with_shoup,
-                          hipStream_t s);
+                          hipStream_t s, bool acc_order = false);
 
 // T = M_DB S_Q mod q_0, centered to int32 (row-major in Trow, d1 x N_Q scratch) and
 // transposed into Tt[v][i] (N_Q x d1).
@@ -216,6 +217,8 @@ struct DbEncArgs {
   int64_t d1, d2, K, R;
   int k_db;
   uint64_t p;
+  const int8_t* e = nullptr;  // the errors e(i, c), K x d1, the same for every prime (the two-pass transforms of
+                              // larger rings draw their own)
 };
 // Per prime: columns of D (Dt rows): [a_c (N_DB) | B[:, c] (d1)].
 hipError_t launch_db_encrypt(const DbEncArgs& a, uint64_t* Dt_prime, uint32_t prime_id,
@@ -228,14 +231,29 @@ struct QEncArgs {
   const uint64_t* cdt;
   int64_t d3, d2, K;
   int k;
-  const int8_t* e = nullptr;  // the query errors e(t, c), d3 x d2, when drawn once for every prime
+  const int8_t* e = nullptr;  // the query errors e(t, c), d3 x d2, the same for every prime (the two-pass
+                              // transforms of larger rings draw their own)
 };
-// The query errors of an encryption (stream QE, element (t, c); the same for every prime) into
-// e[c][t], d3 x d2 (|e| <= 19 fits int8), two positions from each Philox block.
-hipError_t launch_q_errors(uint64_t seed, const uint64_t* cdt, int64_t d3, int64_t d2, int8_t* e, hipStream_t s);
-hipError_t launch_q_encrypt(const QEncArgs& a, uint64_t* XT_prime, uint32_t prime_id,
-                            const Mod& m, uint64_t delta_mod, NttTab tab_q,
-                            const uint64_t* s_hat_prime, hipStream_t s);
+// The moduli of a query encryption and of a decryption, the level's in order: stream id, modulus (the table's
+// prime, or n^2 of the chain, whose products go through the table's prime), scale, tables, transformed secrets.
+struct QEncModuli {
+  uint32_t id[HFE_MAX_QPRIMES];
+  Mod M[HFE_MAX_QPRIMES];
+  uint64_t delta[HFE_MAX_QPRIMES];
+  NttTab T[HFE_MAX_QPRIMES];
+  const uint64_t* s_hat[HFE_MAX_QPRIMES];
+};
+struct DecModuli {
+  Mod M[HFE_MAX_QPRIMES];
+  NttTab T[HFE_MAX_QPRIMES];
+  const uint64_t* s_hat[HFE_MAX_QPRIMES];
+};
+// The Gaussian errors of a stream purpose (sub 0), elements (u, c) with u < per and c < cols, as e[c][u] (|e| <= 19
+// fits int8), two positions from each Philox block.
+hipError_t launch_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
+                         hipStream_t s);
+// XT[level][d3][K]; a.e is needed up to ring degree 2^14.
+hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, uint64_t* XT, hipStream_t s);
 
 // The same operations for ring degrees above 2^14 (k_ntt_big.hip): two-pass transforms through
 // device workspaces taken from the allocator; the LDS-resident launchers forward to these.
@@ -506,12 +524,10 @@ hipError_t launch_crt_rescale_rns(const uint8_t* res, int64_t n, const RnsCrtArg
 hipError_t launch_crt_rescale_p2(const uint16_t* res, int64_t n, const P2CrtArgs& ra, const RescaleArgs& rs,
                                  uint64_t* out, hipStream_t s);
 
-// Decryption: y[i][c][r] = B_out + (s'_j * A_out)[(row0 + r) mod N_DB] mod q_i.
-// arith: the modulus of the residues when it is not the table's prime (the n^2 chain; products then
-// go through the table's prime, see k_ntt.hip); nullptr: the table's prime.
-hipError_t launch_dec_products(const uint64_t* out_prime, int64_t d3, int64_t R_out, int64_t row0,
-                               int64_t rows, int n_db_log, NttTab tab, const uint64_t* sdb_hat_prime,
-                               int k_db, uint64_t* y_prime, hipStream_t s, const Mod* arith = nullptr);
+// Decryption: y[i][c][r] = B_out + (s'_j * A_out)[(row0 + r) mod N_DB] mod the modulus i < level of b, out and y
+// the arrays of all moduli ([level][d3][R_out], [level][d3][rows]).
+hipError_t launch_dec_products(const uint64_t* out, int64_t d3, int64_t R_out, int64_t row0, int64_t rows,
+                               int n_db_log, const DecModuli& b, int level, int k_db, uint64_t* y, hipStream_t s);
 
 struct DecodeArgs {
   int level;
@@ -732,7 +748,7 @@ struct KeyGadget {
 };
 
 // An inverse transform pass of the fold (k_fold_inv): source src[item si + s ss], optionally times y at the
-// same place or times pre[s]; mode 0 residues, 1 centered, 2 times f[s] (digits); dst[item di + s ds].
+// same place; mode 0 residues, 1 centered (doubles), 2 times f[s] (digits); dst[item di + s ds].
 struct FoldInv {
   const uint64_t* src = nullptr;
   int64_t si = 0, ss = 0;
@@ -747,24 +763,22 @@ struct FoldInv {
 };
 // A lift pass of the fold (k_fold_lift), see k_fold.hip.
 struct FoldLift {
-  const int64_t* cen = nullptr;          // [item][part][N] centered values of the divided-out modulus
+  const double* cen = nullptr;           // [item][part][N] centered values of the divided-out modulus (below 2^36)
+  const int64_t* cen64 = nullptr;        // or 64-bit ones (below 2^60: the divisor p q_l)
   const uint64_t* ures = nullptr;        // or residues u mod q_cl, [item][part][N]: cen = centered(ku u mod q_cl)
   int cl = 0;
   double ku = 0.0;
   const uint64_t* x = nullptr;           // kept residues, item stride xi, part stride xp, slot stride N
   int64_t xi = 0, xp = 0;
-  int has_xmul = 0;
-  SlotFactor xmul{};                     // x times xmul[s] first (a constant's rescale)
-  const uint64_t* add = nullptr;         // addend (ap = 0: part 0 only)
+  SlotFactor xmul{};                     // with ures: x times xmul[s] first (a constant's rescale)
+  const uint64_t* add = nullptr;         // addend, item stride ai, part stride ap
   int64_t ai = 0, ap = 0;
-  const uint64_t* add2 = nullptr;        // second addend, both parts
-  int64_t a2i = 0, a2p = 0;
+  int add_b = 0;                         // the addend goes to part 0 only
   const uint64_t* tx = nullptr;          // tensor addend of tx, ty (item stride ti, part stride tp)
   const uint64_t* ty = nullptr;
   int64_t ti = 0, tp = 0;
-  int has_tscale = 0;
-  SlotFactor tscale{};                   // tensor addend times tscale[s] (a rescale by p q_l: q_l^-1)
-  SlotFactor cres{};                     // constant added to part 0
+  SlotFactor tscale{};                   // with cen64: tensor addend times tscale[s] (a rescale by p q_l: q_l^-1)
+  SlotFactor cres{};                     // with ures: constant added to part 0
   uint64_t* out = nullptr;
   int64_t oi = 0, op = 0;
   SlotMap zm{};
@@ -777,6 +791,7 @@ struct FoldLift {
 struct FoldConsts {
   int logn;
   double zd[kFoldSlots], zinv[kFoldSlots];
+  double c32[kFoldSlots];        // 2^32 mod z
   Mod mod[kFoldSlots];
   uint32_t pid[kFoldSlots];      // random-stream ids (i, or 16 for p)
   NttTab tab[kFoldSlots];
@@ -826,10 +841,10 @@ hipError_t launch_fold_fwd(const FoldConsts& C, const int64_t* src, int64_t si, 
                            int64_t ds, const SlotMap& zm, int nsl, int64_t items, hipStream_t s);
 hipError_t launch_fold_inv(const FoldConsts& C, const FoldInv& a, int64_t items, hipStream_t s);
 hipError_t launch_fold_ks_mac(const FoldConsts& C, int level, const FoldInv& dg, const uint64_t* dig, const double* keys,
-                              int64_t kstride, const int32_t* kidx, uint64_t* acc, int64_t* accp, int64_t items,
+                              int64_t kstride, const int32_t* kidx, uint64_t* acc, double* accp, int64_t items,
                               hipStream_t s);
 hipError_t launch_fold_lift(const FoldConsts& C, const FoldLift& a, int64_t items, hipStream_t s);
-hipError_t launch_fold_relin_center(const FoldConsts& C, int level, const uint64_t* acc, const int64_t* accp,
+hipError_t launch_fold_relin_center(const FoldConsts& C, int level, const uint64_t* acc, const double* accp,
                                    const uint64_t* tx, const uint64_t* ty, int64_t items, int64_t* cen, hipStream_t s);
 hipError_t launch_fold_perm(const FoldConsts& C, const uint64_t* x, const int32_t* src, const int32_t* amt,
                             const int32_t* perm, uint64_t* out, int64_t items, int nsl, hipStream_t s);
@@ -848,7 +863,7 @@ hipError_t launch_fold_encrypt(const FoldConsts& C, uint64_t seed, const uint64_
                                hipStream_t s);
 hipError_t launch_fold_dec_products(const FoldConsts& C, const uint64_t* ct, const uint64_t* s_hat, uint64_t* out,
                                     int64_t items, hipStream_t s);
-hipError_t launch_fold_decode(const int64_t* m, int64_t items, int logn, const double* W, const double* Z,
+hipError_t launch_fold_decode(const double* m, int64_t items, int logn, const double* W, const double* Z,
                               const int32_t* kj, double inv_scale, double* v, hipStream_t s);
 // Coefficient-form residues [count][2][level + 1][N] of a fold ciphertext array (hfe_export).
 hfe_status fold_export(const hfe_fct* X, DevBuf& out, hipStream_t s);

@@ -13,10 +13,10 @@
 // divisible by rho of a product d K is d_0 K_0 + Y sum_{r >= 1} d_r K_{rho - r}, so the switched
 // mask and key parts are sums over the digits i and the parts r of products in R_{N_Q}.  The keys are
 // stored as the transforms of K~_0 = K_0 and K~_r = Y K_{rho - r}; each product is then one
-// LDS-resident NTT of d_r per (digit, part, slot) and a pointwise multiply-accumulate held in
+// register-resident NTT (hfe_ntt_reg.h) of d_r per (digit, part, slot) and a pointwise multiply-accumulate held in
 // registers, and one inverse transform per result.  Every value is the exact residue that the full
 // key switch followed by the extraction gives.
-#include "hfe_ntt_lds.h"
+#include "hfe_ntt_reg.h"
 
 namespace hfe {
 
@@ -156,7 +156,9 @@ __global__ void k_fs_ck_finish(FsConsts C, const uint64_t* coef_hat, const uint6
     } else {
       const int slot = z <= C.level ? z : p_index;
       const uint64_t* sh = s_hat + ((size_t)slot * C.k + (part - 1)) * 2 * nq;
-      ck[x] = submod_d(to_d(coef_hat[x]), mulmod_d(to_d(sh[v]), a, q, qinv), q);
+      // the CCMM's secrets are kept in the other order of the transform domain
+      const int w2 = ntt_index(C.logn_q, false, ntt_point(C.logn_q, true, v));
+      ck[x] = submod_d(to_d(coef_hat[x]), mulmod_d(to_d(sh[w2]), a, q, qinv), q);
     }
   }
 }
@@ -175,30 +177,38 @@ hipError_t launch_fs_ck_finish(const FsConsts& C, const uint64_t* coef_hat, cons
 // T layout: [i <= l][col][a | b][N_T].
 
 // Workgroup (col, i rho + r): draws part r of a, writes its coefficients to T, and its transform.
-__global__ void __launch_bounds__(kNttThreads)
+template <class X>
+__global__ void __launch_bounds__(X::MAXT) __attribute__((amdgpu_waves_per_eu(ntt_waves(X::E, 1), ntt_waves(X::E, 1))))
 k_fs_tx_a(FsConsts C, uint64_t seed, int64_t ncols, double* Ahat, uint64_t* T) {
   extern __shared__ double lds[];
   const int nq = 1 << C.logn_q;
   const int64_t nt = (int64_t)nq * C.rho;
   const int64_t col = blockIdx.x;
-  const int i = blockIdx.y / C.rho, r = blockIdx.y - i * C.rho;
+  const int i = blockIdx.y / C.rho, p = blockIdx.y - i * C.rho;
   const Mod& M = C.mod[i];
   uint64_t* a = T + ((size_t)i * ncols + col) * 2 * nt;
-  for (int u = threadIdx.x; u < nq; u += blockDim.x) {
-    const uint64_t t = (uint64_t)C.rho * u + r;
-    const uint64_t x = uniform_at(seed, stream_tag(kTxA, (uint64_t)i), t, (uint64_t)col, M);
-    a[t] = x;
-    lds[u] = to_d(x);
+  double x[X::E];
+#pragma unroll
+  for (int r = 0; r < X::E; ++r) {
+    x[r] = 0.0;
+    if (!X::has(r, nq)) continue;
+    const uint64_t t = (uint64_t)C.rho * (X::base(r) + threadIdx.x) + p;
+    const uint64_t u = uniform_at(seed, stream_tag(kTxA, (uint64_t)i), t, (uint64_t)col, M);
+    a[t] = u;
+    x[r] = u2d(u);
   }
-  __syncthreads();
-  ntt_fwd_lds(lds, C.tab[i]);
-  double* o = Ahat + (((size_t)col * (C.level + 1) + i) * C.rho + r) * nq;
-  for (int v = threadIdx.x; v < nq; v += blockDim.x) o[v] = lds[v];
+  const NttTab& tab = C.tab[i];
+  X::fwd(x, lds, tab);
+  double* o = Ahat + (((size_t)col * (C.level + 1) + i) * C.rho + p) * nq;
+#pragma unroll
+  for (int r = 0; r < X::E; ++r)
+    if (X::has(r, nq))
+      (o + X::base(r))[threadIdx.x] = residue_of_c(reduce_c_d(x[r], tab.qd, tab.qinv), tab.qd);
 }
 
 // Workgroup (col, i rho + c'): part c' of s_T a, then b at the coefficients rho u + c'.
-template <int R>
-__global__ void __launch_bounds__(kNttThreads)
+template <class X>
+__global__ void __launch_bounds__(X::MAXT) __attribute__((amdgpu_waves_per_eu(ntt_waves(X::E, 1), ntt_waves(X::E, 1))))
 k_fs_tx_b(FsConsts C, uint64_t seed, const int8_t* m_q, int64_t ncols, const uint64_t* st_hat,
           const uint64_t* y_hat, const uint64_t* cdt, const double* Ahat, uint64_t* T) {
   extern __shared__ double lds[];
@@ -209,39 +219,37 @@ k_fs_tx_b(FsConsts C, uint64_t seed, const int8_t* m_q, int64_t ncols, const uin
   const double q = C.zd[i], qinv = C.zinv[i];
   const double* A = Ahat + ((size_t)col * (C.level + 1) + i) * C.rho * nq;
   const uint64_t* S = st_hat + (size_t)i * C.rho * nq;
-  double acc[R];
+  double acc[X::E];
 #pragma unroll
-  for (int k = 0; k < R; ++k) {
-    const int v = threadIdx.x + k * blockDim.x;
+  for (int k = 0; k < X::E; ++k) {
+    acc[k] = 0.0;
+    if (!X::has(k, nq)) continue;
+    const int v = X::base(k) + (int)threadIdx.x;
     double lo = 0.0, hi = 0.0;
     for (int r = 0; r < C.rho; ++r) {
       const bool wrap = r > cp;
       const int src = wrap ? cp + C.rho - r : cp - r;
-      const double pr = mulmod_d(to_d(S[(size_t)r * nq + v]), A[(size_t)src * nq + v], q, qinv);
+      const double pr = mulmod_d(u2d(S[(size_t)r * nq + v]), A[(size_t)src * nq + v], q, qinv);
       if (wrap)
         hi = addmod_d(hi, pr, q);
       else
         lo = addmod_d(lo, pr, q);
     }
-    acc[k] = addmod_d(lo, mulmod_d(hi, to_d(y_hat[(size_t)i * nq + v]), q, qinv), q);
+    acc[k] = addmod_d(lo, mulmod_d(hi, u2d(y_hat[(size_t)i * nq + v]), q, qinv), q);
   }
-#pragma unroll
-  for (int k = 0; k < R; ++k) lds[threadIdx.x + k * blockDim.x] = acc[k];
-  __syncthreads();
-  ntt_inv_lds_c(lds, C.tab[i]);
+  X::inv(acc, lds, C.tab[i]);  // centered
   const int64_t c = col / C.k, j = col - c * C.k;
-  const Mod& M = C.mod[i];
-  const uint64_t sc = (uint64_t)C.scale[i];
+  const double sc = C.scale[i];
   uint64_t* b = T + (((size_t)i * ncols + col) * 2 + 1) * nt;
-  for (int u = threadIdx.x; u < nq; u += blockDim.x) {
+#pragma unroll
+  for (int k = 0; k < X::E; ++k) {
+    if (!X::has(k, nq)) continue;
+    const int u = X::base(k) + (int)threadIdx.x;
     const uint64_t t = (uint64_t)C.rho * u + cp;
     const int64_t pos = j * nq + u;
     const int mv = (cp == 0 && pos < C.d2) ? (int)m_q[c * C.d2 + pos] : 0;
     const int32_t e = gaussian_at(seed, stream_tag(kTxE, 0), t, (uint64_t)col, cdt);
-    uint64_t val = sub_mod(from_signed(e, M.q, M.mu), to_u(lds[u]), M.q);
-    if (mv == 1) val = add_mod(val, sc, M.q);
-    if (mv == -1) val = sub_mod(val, sc, M.q);
-    b[t] = val;
+    b[t] = d2residue((double)mv * sc - acc[k] + (double)e, q, qinv);
   }
 }
 
@@ -249,16 +257,15 @@ hipError_t launch_fs_tx(const FsConsts& C, uint64_t seed, const int8_t* m_q, int
                         const uint64_t* y_hat, const uint64_t* cdt, double* Ahat, uint64_t* T, hipStream_t s) {
   const int64_t ncols = d3 * C.k;
   if (ncols <= 0) return hipSuccess;
-  const size_t lds = sizeof(double) << C.logn_q;
   const dim3 grid((unsigned)ncols, (unsigned)((C.level + 1) * C.rho));
-  return by_regs(regs_per_thread(C.logn_q), [&](auto rc) -> hipError_t {
-    constexpr int R = decltype(rc)::value;
-    hipError_t e = allow_lds(k_fs_tx_a, lds);
-    if (e == hipSuccess) e = allow_lds(k_fs_tx_b<R>, lds);
+  return by_ntt_acc(C.logn_q, [&](auto xc, int block) -> hipError_t {
+    using X = decltype(xc);
+    const size_t lds = sizeof(double) * X::LDS;
+    hipError_t e = allow_lds(k_fs_tx_a<X>, lds);
+    if (e == hipSuccess) e = allow_lds(k_fs_tx_b<X>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fs_tx_a, grid, dim3(ntt_block(C.logn_q)), lds, s, C, seed, ncols, Ahat, T);
-    hipLaunchKernelGGL(k_fs_tx_b<R>, grid, dim3(ntt_block(C.logn_q)), lds, s, C, seed, m_q, ncols, st_hat, y_hat,
-                       cdt, Ahat, T);
+    hipLaunchKernelGGL(k_fs_tx_a<X>, grid, dim3(block), lds, s, C, seed, ncols, Ahat, T);
+    hipLaunchKernelGGL(k_fs_tx_b<X>, grid, dim3(block), lds, s, C, seed, m_q, ncols, st_hat, y_hat, cdt, Ahat, T);
     return hipGetLastError();
   });
 }
@@ -293,7 +300,8 @@ __global__ void k_fs_digits(FsConsts C, const uint64_t* T, int64_t ncols, double
   }
 }
 
-// The forward transforms are fused with their load and their use (ntt_fwd_fused, hfe_ntt_lds.h).
+// The forward transforms take their inputs straight from global memory into registers and leave their outputs
+// there, where the keys multiply; the inverse transforms start from the accumulators.
 
 // acc + x w with the centered product (|x| <= 16q): acc stays an exact integer, below (1/2 + 2^-11) q
 // times the number of terms (at most 4096 here) in magnitude.
@@ -301,27 +309,25 @@ __device__ __forceinline__ double mac_c(double acc, double x, double w, double q
   return acc + mulmod_c_d(x, w, q, qinv);
 }
 
-// Inverse transform of the values x (positions 8g + k as above) through LDS, written to out in
-// natural order; x signed accumulators (below 2^47 in magnitude; the signed inverse reduces them).
-template <int GPT>
-__device__ __forceinline__ void ntt_inv_store(double* lds, const NttTab& T, const double (&x)[GPT][8], double* out) {
+// Inverse transform of the accumulators x (below 2^47 in magnitude), written to out as residues.
+template <class X>
+__device__ __forceinline__ void ntt_inv_store(double* lds, const NttTab& T, double (&x)[X::E], double* out) {
   const int n = 1 << T.logn;
-  __syncthreads();  // earlier readers of LDS are done
+  X::inv(x, lds, T);
 #pragma unroll
-  for (int j = 0; j < GPT; ++j) {
-    const int g = threadIdx.x + j * blockDim.x;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) lds[8 * g + k] = x[j][k];
-  }
-  __syncthreads();
-  ntt_inv_lds_c(lds, T);
-  for (int v = threadIdx.x; v < n; v += blockDim.x) out[v] = lds[v];
+  for (int r = 0; r < X::E; ++r)
+    if (X::has(r, n)) (out + X::base(r))[threadIdx.x] = residue_of_c(x[r], T.qd);
 }
 
 // Workgroup (col, z): the ring switch of ciphertext col in slot z, before RS_p:
 // Aring = sum_{i, r} d_{i,r} K~mask_{z,i,r},  Bring = sum_{i, r} d_{i,r} K~key_{z,i,r}  (in R_{N_Q}).
-template <int GPT, int S0>
-__global__ void __launch_bounds__(kNttThreads)
+// waves per SIMD of the ring switch: whole workgroups of 512 threads and more fill two or four
+template <class X>
+constexpr int ring_waves() {
+  return X::MAXT >= 1024 ? 4 : X::MAXT >= 512 ? 2 : ntt_waves(X::E, 3);
+}
+template <class X>
+__global__ void __launch_bounds__(X::MAXT) __attribute__((amdgpu_waves_per_eu(ring_waves<X>(), ring_waves<X>())))
 k_fs_ring(FsConsts C, int64_t ncols, const double* Dg, const double* rk, double* Aring, double* Bring) {
   extern __shared__ double lds[];
   const int64_t G = ncols * C.nz;
@@ -332,41 +338,44 @@ k_fs_ring(FsConsts C, int64_t ncols, const double* Dg, const double* rk, double*
   const int nq = 1 << C.logn_q;
   const NttTab& T = C.tab[z];
   const double q = C.zd[z], qinv = C.zinv[z];
-  double accA[GPT][8], accB[GPT][8], x[GPT][8];
+  double acc[2][X::E], x[X::E];
+  const double* src = Dg + (size_t)col * (C.level + 1) * C.rho * nq;
 #pragma unroll
-  for (int j = 0; j < GPT; ++j)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) accA[j][k] = accB[j][k] = 0.0;
-  for (int i = 0; i <= C.level; ++i) {
-    for (int r = 0; r < C.rho; ++r) {
-      const double* src = Dg + (((size_t)col * (C.level + 1) + i) * C.rho + r) * nq;
-      ntt_fwd_fused<GPT, S0>(lds, T, [&](int pos) { return src[pos]; }, x);  // digits below q_i < 2z
-      const double* ka = rk + (((size_t)z * (C.level + 1) + i) * 2 * C.rho + r) * nq;
-      const double* kb = ka + (size_t)C.rho * nq;
-#pragma unroll
-      for (int j = 0; j < GPT; ++j) {
-        const int v0 = 8 * (threadIdx.x + j * blockDim.x);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          accA[j][k] = mac_c(accA[j][k], x[j][k], ka[v0 + k], q, qinv);
-          accB[j][k] = mac_c(accB[j][k], x[j][k], kb[v0 + k], q, qinv);
-        }
-      }
-    }
+  for (int r = 0; r < X::E; ++r) {
+    acc[0][r] = acc[1][r] = 0.0;
+    x[r] = X::has(r, nq) ? (src + X::base(r))[threadIdx.x] : 0.0;
   }
-  ntt_inv_store<GPT>(lds, T, accA, Aring + ((size_t)z * ncols + col) * nq);
-  ntt_inv_store<GPT>(lds, T, accB, Bring + ((size_t)z * ncols + col) * nq);
+  const int terms = (C.level + 1) * C.rho;
+  for (int ir = 0; ir < terms; ++ir) {
+    const int i = ir / C.rho, p = ir - i * C.rho;
+    KeyMac<X, 2> mac;
+    mac.n = nq;
+    mac.key[0] = rk + (((size_t)z * (C.level + 1) + i) * 2 * C.rho + p) * nq;
+    mac.key[1] = mac.key[0] + (size_t)C.rho * nq;
+    mac.keys_begin();
+    X::fwd(x, lds, T);  // digits below q_i < 2z
+    src += ir + 1 < terms ? nq : 0;
+    mac.run(x, acc, src, q, qinv);
+  }
+  ntt_inv_store<X>(lds, T, acc[0], Aring + ((size_t)z * ncols + col) * nq);
+  ntt_inv_store<X>(lds, T, acc[1], Bring + ((size_t)z * ncols + col) * nq);
 }
 
 // Workgroup (c, z, g): the conversion of column c's k chunks in slot z, before RS_p, for the outputs
-// j' in [2g, 2g + 2) (and the shared mask when g = 0):
+// j' in [NB g, NB (g + 1)) (and the shared mask when g = 0), NB = 2, or 1 at 2^14 where the registers of a
+// workgroup of 1,024 threads do not hold three sums beside the transform:
 // Aconv = sum_{i, j} d_i(a'_j) k_ij,  Bconv_j' = sum_{i, j} d_i(a'_j) beta_ij'.
 // The chunks' masks a'_j = RS_p(Aring) and their digits are formed as the transforms load them.
-template <int GPT, int S0>
-__global__ void __launch_bounds__(kNttThreads)
+template <class X>
+constexpr int conv_outputs() {
+  return X::MAXT * X::E > (1 << 13) ? 1 : 2;
+}
+template <class X, int NB>
+__global__ void __launch_bounds__(X::MAXT)
+    __attribute__((amdgpu_waves_per_eu(ntt_waves(X::E, 2 + NB), ntt_waves(X::E, 2 + NB))))
 k_fs_conv(FsConsts C, int64_t d3, const double* Aring, const double* ck, double* Aconv, double* Bconv) {
   extern __shared__ double lds[];
-  const int groups = (C.k + 1) / 2;
+  const int groups = (C.k + NB - 1) / NB;
   const int64_t G = d3 * C.nz * groups;
   const int64_t f = xcd_item(blockIdx.x, G);
   if (f >= G) return;
@@ -378,41 +387,42 @@ k_fs_conv(FsConsts C, int64_t d3, const double* Aring, const double* ck, double*
   const int l = C.level;
   const NttTab& T = C.tab[z];
   const double q = C.zd[z], qinv = C.zinv[z], pd = C.zd[l + 1];
-  const int j0 = 2 * g;
-  const int nb = C.k - j0 < 2 ? C.k - j0 : 2;
-  double accA[GPT][8], accB0[GPT][8], accB1[GPT][8], x[GPT][8];
+  const int j0 = NB * g;
+  const int nb = C.k - j0 < NB ? C.k - j0 : NB;
+  double accA[X::E], accB0[X::E], accB1[X::E];
 #pragma unroll
-  for (int jj = 0; jj < GPT; ++jj)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) accA[jj][k] = accB0[jj][k] = accB1[jj][k] = 0.0;
+  for (int r = 0; r < X::E; ++r) accA[r] = accB0[r] = accB1[r] = 0.0;
   for (int j = 0; j < C.k; ++j) {
     const int64_t col = c * C.k + j;
     const double* Ap = Aring + ((size_t)(l + 1) * ncols + col) * nq;
     for (int i = 0; i <= l; ++i) {
       const double* Ai = Aring + ((size_t)i * ncols + col) * nq;
       const double qi = C.zd[i], qiinv = C.zinv[i], pinv = C.pinv[i], gh = C.ghat[i];
-      ntt_fwd_fused<GPT, S0>(
-          lds, T,
-          [&](int v) { return mulmod_d(rs_d(Ai[v], Ap[v], pd, qi, qiinv, pinv), gh, qi, qiinv); }, x);
+      double x[X::E];
+#pragma unroll
+      for (int r = 0; r < X::E; ++r) {
+        x[r] = 0.0;
+        if (!X::has(r, nq)) continue;
+        x[r] = mulmod_d(rs_d((Ai + X::base(r))[threadIdx.x], (Ap + X::base(r))[threadIdx.x], pd, qi, qiinv, pinv), gh,
+                        qi, qiinv);
+      }
+      X::fwd(x, lds, T);
       const double* kk = ck + (((size_t)z * (l + 1) + i) * C.k + j) * (1 + C.k) * nq;
       const double* kb0 = kk + (size_t)(1 + j0) * nq;
       const double* kb1 = kk + (size_t)(nb > 1 ? 2 + j0 : 1 + j0) * nq;
 #pragma unroll
-      for (int jj = 0; jj < GPT; ++jj) {
-        const int v0 = 8 * (threadIdx.x + jj * blockDim.x);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const double xv = x[jj][k];
-          if (g == 0) accA[jj][k] = mac_c(accA[jj][k], xv, kk[v0 + k], q, qinv);
-          accB0[jj][k] = mac_c(accB0[jj][k], xv, kb0[v0 + k], q, qinv);
-          if (nb > 1) accB1[jj][k] = mac_c(accB1[jj][k], xv, kb1[v0 + k], q, qinv);
-        }
+      for (int r = 0; r < X::E; ++r) {
+        if (!X::has(r, nq)) continue;
+        if (g == 0) accA[r] = mac_c(accA[r], x[r], (kk + X::base(r))[threadIdx.x], q, qinv);
+        accB0[r] = mac_c(accB0[r], x[r], (kb0 + X::base(r))[threadIdx.x], q, qinv);
+        if (NB > 1 && nb > 1) accB1[r] = mac_c(accB1[r], x[r], (kb1 + X::base(r))[threadIdx.x], q, qinv);
+        if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  if (g == 0) ntt_inv_store<GPT>(lds, T, accA, Aconv + ((size_t)z * d3 + c) * nq);
-  ntt_inv_store<GPT>(lds, T, accB0, Bconv + (((size_t)z * d3 + c) * C.k + j0) * nq);
-  if (nb > 1) ntt_inv_store<GPT>(lds, T, accB1, Bconv + (((size_t)z * d3 + c) * C.k + j0 + 1) * nq);
+  if (g == 0) ntt_inv_store<X>(lds, T, accA, Aconv + ((size_t)z * d3 + c) * nq);
+  ntt_inv_store<X>(lds, T, accB0, Bconv + (((size_t)z * d3 + c) * C.k + j0) * nq);
+  if (NB > 1 && nb > 1) ntt_inv_store<X>(lds, T, accB1, Bconv + (((size_t)z * d3 + c) * C.k + j0 + 1) * nq);
 }
 
 // Element (c, u): RS_p of the converted parts, the ring-switched b' = b(rho u) + RS_p(Bring), and
@@ -457,36 +467,30 @@ __global__ void k_fs_finish(FsConsts C, const uint64_t* T, int64_t d3, const dou
   }
 }
 
-// The fused kernels: blockDim = N_Q / (8 GPT) threads (GPT = 2 at N_Q = 2^14, 1024 threads).
-template <int GPT, int S0>
-static hipError_t launch_fused_as(const FsConsts& C, int64_t ncols, int64_t d3, const FsWork& w, const double* rk,
-                                  const double* ck, bool conv, hipStream_t s) {
-  const size_t lds = sizeof(double) << C.logn_q;
-  const int threads = (1 << C.logn_q) / (8 * GPT);
-  if (!conv) {
-    hipError_t e = allow_lds(k_fs_ring<GPT, S0>, lds);
+static hipError_t launch_ring(const FsConsts& C, int64_t ncols, const FsWork& w, const double* rk, hipStream_t s) {
+  return by_ntt_acc(C.logn_q, [&](auto xc, int block) -> hipError_t {
+    using X = decltype(xc);
+    const size_t lds = sizeof(double) * X::LDS;
+    hipError_t e = allow_lds(k_fs_ring<X>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_fs_ring<GPT, S0>), dim3(xcd_grid(ncols * C.nz)), dim3(threads), lds, s, C, ncols, w.Dg,
-                       rk, w.Aring, w.Bring);
-  } else {
-    hipError_t e = allow_lds(k_fs_conv<GPT, S0>, lds);
-    if (e != hipSuccess) return e;
-    const int groups = (C.k + 1) / 2;
-    hipLaunchKernelGGL((k_fs_conv<GPT, S0>), dim3(xcd_grid(d3 * C.nz * groups)), dim3(threads), lds, s, C, d3,
-                       w.Aring, ck, w.Aconv, w.Bconv);
-  }
-  return hipGetLastError();
+    hipLaunchKernelGGL(k_fs_ring<X>, dim3(xcd_grid(ncols * C.nz)), dim3(block), lds, s, C, ncols, w.Dg, rk, w.Aring,
+                       w.Bring);
+    return hipGetLastError();
+  });
 }
 
-static hipError_t launch_fused(const FsConsts& C, int64_t ncols, int64_t d3, const FsWork& w, const double* rk,
-                               const double* ck, bool conv, hipStream_t s) {
-  const int s0 = (C.logn_q - 1) % 3 + 1;
-  if (C.logn_q <= 13) {
-    if (s0 == 1) return launch_fused_as<1, 1>(C, ncols, d3, w, rk, ck, conv, s);
-    if (s0 == 2) return launch_fused_as<1, 2>(C, ncols, d3, w, rk, ck, conv, s);
-    return launch_fused_as<1, 3>(C, ncols, d3, w, rk, ck, conv, s);
-  }
-  return launch_fused_as<2, 2>(C, ncols, d3, w, rk, ck, conv, s);  // 2^14 = 2^(2 + 3 + 3 + 3 + 3)
+static hipError_t launch_conv(const FsConsts& C, int64_t d3, const FsWork& w, const double* ck, hipStream_t s) {
+  return by_ntt_acc(C.logn_q, [&](auto xc, int block) -> hipError_t {
+    using X = decltype(xc);
+    const size_t lds = sizeof(double) * X::LDS;
+    constexpr int NB = conv_outputs<X>();
+    hipError_t e = allow_lds(k_fs_conv<X, NB>, lds);
+    if (e != hipSuccess) return e;
+    const int groups = (C.k + NB - 1) / NB;
+    hipLaunchKernelGGL((k_fs_conv<X, NB>), dim3(xcd_grid(d3 * C.nz * groups)), dim3(block), lds, s, C, d3, w.Aring, ck,
+                       w.Aconv, w.Bconv);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_fs_switch(const FsConsts& C, const uint64_t* T, int64_t d3, const double* rk, const double* ck,
@@ -501,10 +505,10 @@ hipError_t launch_fs_switch(const FsConsts& C, const uint64_t* T, int64_t d3, co
     if (e != hipSuccess) return e;
   }
   if (ev) (void)hipEventRecord(ev[1], s);
-  hipError_t e = launch_fused(C, ncols, d3, w, rk, ck, false, s);
+  hipError_t e = launch_ring(C, ncols, w, rk, s);
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], s);
-  e = launch_fused(C, ncols, d3, w, rk, ck, true, s);
+  e = launch_conv(C, d3, w, ck, s);
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[3], s);
   {

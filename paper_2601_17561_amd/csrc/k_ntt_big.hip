@@ -1,7 +1,7 @@
-// Negacyclic NTT through HBM for ring degrees above the LDS-resident limit (2^15 and 2^16, the
+// Negacyclic NTT through HBM for ring degrees above the limit of the register transforms (2^15 and 2^16, the
 // transmission ring of Appendix C.1), and the products built on it: the secret-key transforms,
 // T = M_DB S_Q, database and query encryption and the decryption products of Section 2.3, with
-// the same random streams, the same arithmetic and the same results as the LDS-resident kernels.
+// the same random streams, the same arithmetic and the same results as the kernels of smaller rings.
 //
 // The merged Cooley-Tukey transform of degree n = 2^L (twiddle psi^brv(m + i) for block i of the
 // stage with m blocks, half-size t = n / 2m) splits after its first L1 = L / 2 stages:
@@ -12,7 +12,7 @@
 //    the stage with m' local blocks has global m = 2^L1 m' and block index b m' + i', so its
 //    twiddle index is m' (2^L1 + b) + i'.
 // Pass 1 (columns) and pass 2 (blocks) each keep 16 sub-transforms of 256 elements in LDS and
-// run the same three-stage register rounds as the LDS-resident transform, with the twiddle index
+// run the same three-stage register rounds as the LDS-resident transform of small rings, with the twiddle index
 // m (mult) + i: mult = 1 in pass 1 and 2^L1 + b in pass 2.  The inverse (Gentleman-Sande) runs
 // the passes in the opposite order with the same indexing and the 1/n factor at the end of
 // pass 1.  NTT-domain data stays in device workspaces; only coefficient-domain results leave.
@@ -232,7 +232,7 @@ __global__ void k_big_store_hat(const double* W, int n, uint64_t q, uint64_t* a,
   if (shoup) a[(int64_t)blockIdx.y * stride + n + v] = shoup_quot(x, q);
 }
 
-// The n^2 modulus chain takes its products through the table's prime q (as the LDS-resident
+// The n^2 modulus chain takes its products through the table's prime q (as the smaller rings
 // kernels): a residue mod m enters as its centered integer mod q, a product coefficient (an integer
 // of magnitude below q / 2) leaves centered and reduced mod m.  With m = q both are identities.
 __device__ __forceinline__ double big_to_ntt(uint64_t x, const Mod& M, uint64_t q) {
@@ -340,7 +340,7 @@ __global__ void k_big_emit_dec(const double* W2, const uint64_t* out, int64_t R_
 static dim3 elem_grid(int64_t n, int64_t cols) { return dim3((unsigned)((n + 255) / 256), (unsigned)cols); }
 
 // ------------------------------------------------------------------ launchers (same contracts as the
-// LDS-resident ones in k_ntt.hip, which call these for ring degrees above 2^14)
+// register-resident ones in k_ntt.hip and k_query.hip, which call these for ring degrees above 2^14)
 
 hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab T, bool with_shoup, hipStream_t s) {
   const int n = 1 << T.logn;

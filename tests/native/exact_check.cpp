@@ -12,7 +12,22 @@ using namespace hfe;
 static constexpr RnsModConsts kRns = make_rns_mod_consts();
 static constexpr P2BaseConsts kP2 = make_p2_base_consts();
 
+#include "../../paper_2601_17561_amd/csrc/hfe_ntt_plan.h"
+
 extern "C" {
+
+// signed64_mod of x[i] mod q.
+void xc_signed64_mod(const int64_t* x, int64_t n, uint64_t q, double* out) {
+  for (int64_t i = 0; i < n; ++i)
+    out[i] = hfe::signed64_mod(x[i], (double)((1ull << 32) % q), (double)q, 1.0 / (double)q);
+}
+// The transform-domain order: point[i] of index i, and index back[i] of point i.
+void xc_ntt_order(int logn, int acc, int32_t* point, int32_t* back) {
+  for (int i = 0; i < (1 << logn); ++i) {
+    point[i] = hfe::ntt_point(logn, acc != 0, i);
+    back[i] = hfe::ntt_index(logn, acc != 0, i);
+  }
+}
 
 // The fold's slot encoder (hfe_slots.h) on w (N/2 integers) at scale 2^e: out = N integer coefficients.
 void xc_slot_encode(const int64_t* w, int logn, int e, int64_t* out) {

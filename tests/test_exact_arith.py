@@ -56,6 +56,10 @@ for _name, _args in {
     getattr(_L, _name).argtypes = _args
     getattr(_L, _name).restype = None
 _L.xc_ntt_signed.restype = ctypes.c_int64
+_L.xc_signed64_mod.argtypes = [_p, ctypes.c_int64, ctypes.c_uint64, _p]
+_L.xc_signed64_mod.restype = None
+_L.xc_ntt_order.argtypes = [ctypes.c_int, ctypes.c_int, _p, _p]
+_L.xc_ntt_order.restype = None
 _L.xc_intt_signed.restype = ctypes.c_int64
 _L.xc_intt_signed.argtypes = [_p, _p, ctypes.c_int, ctypes.c_uint64, ctypes.c_uint64, _p]
 _L.xc_mod_u32_sweep.restype = ctypes.c_int64
@@ -371,3 +375,30 @@ def test_slot_encoder_matches_the_oracle_bit_for_bit(log_n, e):
     out = np.empty(1 << log_n, dtype=np.int64)
     _L.xc_slot_encode(_ptr(w), log_n, e, _ptr(out))
     assert np.array_equal(out, OF.encode(w, log_n, e))
+
+
+@pytest.mark.parametrize("q", [(1 << 36) - 5, (1 << 35) + 1, (1 << 23) - 15, (1 << 22) + 1])
+def test_signed64_mod_is_a_small_representative(q):
+    """Signed 64-bit integers (the fold's coefficients before a transform) to representatives of at most
+    (1/2 + 2^-11) q, at the ends of the range, around multiples of 2^32 and of q, and at random."""
+    rng = np.random.default_rng(q % 1000)
+    edge = [s * v + d for v in (0, 1 << 31, 1 << 32, 1 << 59, 1 << 62, q, q << 20) for s in (1, -1)
+            for d in (-2, -1, 0, 1, 2)]
+    edge += [-(1 << 63), (1 << 63) - 1, q // 2, q // 2 + 1, -(q // 2), -(q // 2) - 1]
+    x = np.concatenate([np.array(edge, dtype=np.int64),
+                        rng.integers(-(1 << 63), (1 << 63) - 1, 200_000, dtype=np.int64),
+                        rng.integers(-(1 << 40), 1 << 40, 200_000, dtype=np.int64)])
+    out = np.empty(len(x), dtype=np.float64)
+    _L.xc_signed64_mod(_ptr(x), len(x), q, _ptr(out))
+    assert np.all(out == np.rint(out)) and np.abs(out).max() <= (0.5 + 2.0 ** -11) * q
+    got = out.astype(np.int64)
+    assert all((int(a) - int(b)) % q == 0 for a, b in zip(x, got))
+
+
+@pytest.mark.parametrize("log_n", range(1, 15))
+@pytest.mark.parametrize("acc", [0, 1])
+def test_transform_domain_order_is_a_permutation(log_n, acc):
+    n = 1 << log_n
+    point, back = np.empty(n, dtype=np.int32), np.empty(n, dtype=np.int32)
+    _L.xc_ntt_order(log_n, acc, _ptr(point), _ptr(back))
+    assert np.array_equal(np.sort(point), np.arange(n)) and np.array_equal(back[point], np.arange(n))

@@ -1,0 +1,91 @@
+"""Every ring degree that a transform kernel is built for, end to end.
+
+The oracle tests pin the residues at some degrees; each other degree has its own register and exchange
+layout, so each is run here: a wrong layout on either side of a product turns decryption into noise.  Inner
+products must equal the exact plaintext products with |v - IP| <= 0.25 (the library's decryption bound), and
+folds must lie within Appendix C.2's allowance of 0.02 plus the input's encryption error.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("needs a GPU", allow_module_level=True)
+H = pytest.importorskip("paper_2601_17561_amd")
+
+import hfe_synth as S  # noqa: E402
+
+
+def _say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def _ternary(rng, n, d):
+    return rng.integers(-1, 2, (n, d)).astype(np.int8)
+
+
+def _check(keys, r, mq, mdb, what):
+    v, ip = H.hfe_decrypt(keys, r)
+    torch.cuda.synchronize()
+    want = mq.astype(np.int64) @ mdb.astype(np.int64).T
+    assert np.array_equal(ip.cpu().numpy(), want), what
+    assert float(np.abs(v.cpu().numpy() - want).max()) <= 0.25, what
+
+
+# two database chunks and three query chunks, the last ones ragged; both sides of the transforms' own sizes
+@pytest.mark.parametrize("log_n", [5, 8, 9, 10, 11, 12, 13, 14])
+@pytest.mark.parametrize("family", ["primes", "chain"])
+def test_ccmm_decrypts_exactly_at_every_ring_degree(log_n, family):
+    n = 1 << log_n
+    d1 = n + 37 if log_n <= 12 else 40
+    d2 = min(2 * n + 11, 9001)
+    rng = np.random.default_rng(100 + log_n)
+    mdb, mq = _ternary(rng, d1, d2), _ternary(rng, 3, d2)
+    if family == "primes":
+        keys, level, form = H.hfe_keygen(H.hfe_default_params(log_n, log_n, 2, d2, d1), 5), 2, H.HFE_FORM_RNS_I8
+    else:
+        keys = H.hfe_chain_keygen(H.hfe_chain_default_params(log_n, log_n, 5, 3, d2, d1), 5)
+        level, form = 5, H.HFE_FORM_P2_I8
+    _say(f"[gpu-degrees] {family} 2^{log_n} d1 {d1} d2 {d2}")
+    db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, form)
+    q = H.hfe_encrypt(keys, torch.from_numpy(mq).cuda(), level, 7)
+    _check(keys, H.hfe_ccmm(db, q, 0, d1, form), mq, mdb, "all rows")
+    lo, rows = d1 // 3, d1 // 2
+    _check(keys, H.hfe_ccmm(db, q, lo, rows, form), mq, mdb[lo:lo + rows], "a row range")
+    # enough columns that each workgroup takes every chunk of its column
+    many = _ternary(rng, 200, d2)
+    q = H.hfe_encrypt(keys, torch.from_numpy(many).cuda(), level, 8)
+    _check(keys, H.hfe_ccmm(db, q, 0, d1, form), many, mdb, "many columns")
+
+
+@pytest.mark.parametrize("log_n_q", [6, 9, 10, 11, 12, 13, 14])
+def test_format_switch_decrypts_exactly_at_every_query_ring(log_n_q):
+    n = 1 << log_n_q
+    d1, d2 = 50, n + 9
+    rng = np.random.default_rng(200 + log_n_q)
+    mdb, mq = _ternary(rng, d1, d2), _ternary(rng, 3, d2)
+    keys = H.hfe_keygen(H.hfe_default_params(7, log_n_q, 3, d2, d1), 5)
+    _say(f"[gpu-degrees] format switch to 2^{log_n_q}")
+    db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, H.HFE_FORM_RNS_I8)
+    fk = H.hfe_fs_keygen(keys, 2, log_n_q + 1, 7)
+    T = H.hfe_fs_encrypt(fk, torch.from_numpy(mq).cuda(), 8)
+    q = H.hfe_format_switch(fk, T, 3)
+    _check(keys, H.hfe_ccmm(db, q, 0, d1, H.HFE_FORM_RNS_I8), mq, mdb, "switched query")
+
+
+@pytest.mark.parametrize("log_n", [6, 8, 9, 11, 12, 13])
+def test_fold_matches_the_plain_values_at_every_ring_degree(log_n):
+    from oracle import fold as OF
+    w = S.FoldWorkload(f"fold_n{1 << log_n}", log_n, 4, 6, 1, 1100, (1 << log_n) // 2, S.BASE_SEED + 300 + log_n)
+    ip, counts = S.fold_inputs(w)
+    _say(f"[gpu-degrees] fold 2^{log_n}")
+    fk = H.hfe_fold_keygen(w.log_n, w.k, w.rho, 5)
+    ct = H.hfe_fold_encrypt(fk, torch.from_numpy(ip).cuda(), 6)
+    got = H.hfe_fold_decrypt(fk, H.hfe_fold(fk, ct, torch.from_numpy(counts).cuda(), w.rho)).cpu().numpy()
+    want = OF.fold_plain(ip.astype(np.int64), counts.astype(np.int64), w.rho, w.k)
+    assert float(np.max(np.abs(got - want))) < 0.02 + 4 * 19 * w.k / 2.0 ** 20
