@@ -2170,13 +2170,12 @@ hfe_status hfe_match(const int32_t* ip, const uint8_t* q_masks, int64_t n_eyes, 
   if (n_shifts < 1 || n_shifts > 64) return fail(HFE_EINVAL, "n_shifts must be 1..64");
   if (t_den == 0 || 2ull * t_num >= t_den) return fail(HFE_EINVAL, "threshold must satisfy 0 <= t < 1/2");
   hipStream_t s = (hipStream_t)stream;
-  const int64_t W = (d2 + 63) / 64, d3 = n_eyes * n_shifts, nb = (rows + 255) / 256;
-  DevBuf qw, dbw, part;
-  HFE_TRY(qw.alloc(sizeof(uint64_t) * (size_t)W * d3, s));
+  const int64_t W = (d2 + 63) / 64, d3 = n_eyes * n_shifts;
+  DevBuf qw, dbw;
+  HFE_TRY(qw.alloc(sizeof(uint64_t) * (size_t)(W * match_cols(d3)), s));
   HFE_TRY(dbw.alloc(sizeof(uint64_t) * (size_t)W * rows, s));
-  HFE_TRY(part.alloc((size_t)d3 * nb, s));
   HFE_LAUNCH(launch_match(ip, q_masks, n_eyes, shifts, n_shifts, db_masks, rows, d2, t_num, t_den,
-                          qw.as<uint64_t>(), dbw.as<uint64_t>(), decision, part.as<uint8_t>(), eye_match, s));
+                          qw.as<uint64_t>(), dbw.as<uint64_t>(), decision, eye_match, s));
   return HFE_OK;
 }
 

@@ -549,10 +549,10 @@ hipError_t launch_encode(const uint8_t* codes, const uint8_t* masks, int64_t n, 
                          const int32_t* shifts_dev, int32_t n_shifts, int8_t* out, hipStream_t s);
 
 hipError_t launch_match(const int32_t* ip, const uint8_t* q_masks, int64_t n_eyes,
-                        const int32_t* shifts_dev, int32_t n_shifts, const uint8_t* db_masks,
-                        int64_t rows, int32_t d2, uint32_t t_num, uint32_t t_den,
-                        uint64_t* qwords, uint64_t* dbwords, uint8_t* decision, uint8_t* col_any,
-                        uint8_t* eye_match, hipStream_t s);
+                        const int32_t* shifts, int32_t n_shifts, const uint8_t* db_masks,
+                        int64_t rows, int32_t d2, uint32_t t_num, uint32_t t_den, uint64_t* qwords,
+                        uint64_t* dbwords, uint8_t* decision, uint8_t* eye_match, hipStream_t s);
+int64_t match_cols(int64_t d3);  // columns of qwords [W][match_cols(d3)]; dbwords [W][rows], W = ceil(d2 / 64)
 
 constexpr int kMaxBatch = 256;                   // items per batched launch
 struct BatchElemHeader {

@@ -268,134 +268,135 @@ hipError_t launch_decode(const uint64_t* y, int64_t n, const DecodeArgs& da, dou
 // ------------------------------------------------------------------ match decision
 // Masks packed into 64-bit words, words-major ([word][row]) so that a row block reads
 // contiguous words.  Query masks are rolled by their shifts while packing.
-// Thread (word w, row): out[w][row] = bits t = 64 w .. 64 w + 63 of the row rolled by its shift
-// (bit b = mask[(t - r) mod d2] & 1, zero beyond d2).  Lanes take consecutive rows of one word,
-// so the word-major writes are coalesced; an unshifted row whose 64 bytes lie inside the mask row
-// is read as four 16-byte loads (one aligned 64-byte line when d2 is a multiple of 64).
-__global__ void k_pack_masks(const uint8_t* masks, int64_t n, int32_t d2, Shifts sh, int32_t n_shifts,
-                             int32_t W, uint64_t* out) {
-  const int64_t rows = n * n_shifts;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * W) return;
-  const int32_t w = (int32_t)(idx / rows);
-  const int64_t row = idx - (int64_t)w * rows;  // e * S + s
-  const int64_t e = row / n_shifts;
-  const int32_t r = sh.r[row % n_shifts];
-  const uint8_t* m = masks + e * d2;
-  const int64_t t0 = (int64_t)w * 64;
+// The bits of four mask bytes, byte k's lowest bit at bit k (the product's partial sums never meet).
+__device__ __forceinline__ uint32_t pack4(uint32_t v) { return ((v & 0x01010101u) * 0x01020408u) >> 24 & 15u; }
+
+// Bits t0 .. t0 + 63 of a mask row rolled by r, 0 <= r < d2 (bit b = mask[(t - r) mod d2] & 1, zero beyond d2), in pieces of 16:
+// one 16-byte load (of any alignment) where a piece neither wraps nor ends inside, else byte by byte.
+__device__ __forceinline__ uint64_t pack_word(const uint8_t* m, int32_t d2, int32_t t0, int32_t r) {
   uint64_t word = 0;
-  if (r == 0 && t0 + 64 <= d2 && (((uintptr_t)(m + t0)) & 15) == 0) {
-    const uint4* p = reinterpret_cast<const uint4*>(m + t0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint4 v = p[i];
-      const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+  for (int p = 0; p < 4; ++p) {
+    const int32_t t = t0 + 16 * p;
+    if (t >= d2) break;
+    int32_t src = t - r;
+    if (src < 0) src += d2;
+    if (t + 16 <= d2 && src + 16 <= d2) {
+      uint32_t v[4];
+      __builtin_memcpy(v, m + src, 16);
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) word |= (uint64_t)((d[k] >> (8 * b)) & 1u) << (16 * i + 4 * k + b);
-    }
-  } else {
-    for (int b = 0; b < 64; ++b) {
-      const int64_t t = t0 + b;
-      if (t < d2) {
-        int64_t src = (t - r) % d2;
-        if (src < 0) src += d2;
-        word |= (uint64_t)(m[src] & 1) << b;
+      for (int k = 0; k < 4; ++k) word |= (uint64_t)pack4(v[k]) << (16 * p + 4 * k);
+    } else {
+      const int n = d2 - t < 16 ? d2 - t : 16;
+      for (int b = 0; b < n; ++b) {
+        word |= (uint64_t)(m[src] & 1) << (16 * p + b);
+        src = src + 1 == d2 ? 0 : src + 1;
       }
     }
   }
-  out[(int64_t)w * rows + row] = word;
+  return word;
 }
 
-constexpr int kMatchCols = 16;
-
-// Block (column group g, row block): thread = one database row, kMatchCols query columns.
+// Thread (word, row), lanes on consecutive rows of one word (coalesced writes): the first q_items threads pack the
+// query masks (columns d3 .. d3p - 1 are zero), the others the database's.  Thread 0 .. n_eyes - 1 also clear
+// the eyes' answers, which k_match sets.
 __global__ void __launch_bounds__(256)
-k_match(const int32_t* ip, const uint64_t* qwords, const uint64_t* dbwords, int64_t d3, int64_t rows,
-        int32_t W, uint32_t t_num, uint32_t t_den, uint8_t* decision, uint8_t* part) {
-  extern __shared__ uint64_t qw[];  // [kMatchCols][W]
-  __shared__ int any_flag[kMatchCols];
-  const int64_t c0 = (int64_t)blockIdx.y * kMatchCols;
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int i = threadIdx.x; i < kMatchCols * W; i += blockDim.x) {
-    const int cc = i / W, w = i % W;
-    qw[i] = (c0 + cc < d3) ? qwords[(int64_t)w * d3 + c0 + cc] : 0ull;
+k_pack_masks(const uint8_t* q_masks, int64_t d3, int64_t d3p, Shifts sh, int32_t n_shifts, const uint8_t* db_masks,
+             int64_t rows, int32_t d2, int32_t W, uint64_t* qwords, uint64_t* dbwords, int64_t n_eyes, uint8_t* eye) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n_eyes) eye[i] = 0;
+  const int64_t q_items = d3p * W;
+  if (i < q_items) {
+    const int32_t w = (int32_t)(i / d3p);
+    const int64_t c = i - (int64_t)w * d3p;  // e * S + s
+    qwords[i] = c < d3 ? pack_word(q_masks + c / n_shifts * d2, d2, w * 64, sh.r[c % n_shifts]) : 0;
+    return;
   }
-  if (threadIdx.x < kMatchCols) any_flag[threadIdx.x] = 0;
-  __syncthreads();
-  int ov[kMatchCols];
-#pragma unroll
-  for (int cc = 0; cc < kMatchCols; ++cc) ov[cc] = 0;
-  if (r < rows) {
-    for (int w = 0; w < W; ++w) {
-      const uint64_t dw = dbwords[(int64_t)w * rows + r];
-#pragma unroll
-      for (int cc = 0; cc < kMatchCols; ++cc) ov[cc] += __popcll(qw[cc * W + w] & dw);
-    }
-  }
-  const int64_t lhs_scale = t_den, rhs_scale = (int64_t)t_den - 2 * (int64_t)t_num;
-#pragma unroll
-  for (int cc = 0; cc < kMatchCols; ++cc) {
-    const int64_t c = c0 + cc;
-    if (r < rows && c < d3) {
-      const int64_t x = ip[c * rows + r];
-      const bool dec = ov[cc] > 0 && x * lhs_scale > rhs_scale * ov[cc];
-      if (decision) decision[c * rows + r] = dec ? 1 : 0;
-      if (dec) any_flag[cc] = 1;  // benign race: every writer stores 1
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < kMatchCols && c0 + threadIdx.x < d3)
-    part[(c0 + threadIdx.x) * gridDim.x + blockIdx.x] = (uint8_t)any_flag[threadIdx.x];
+  const int64_t j = i - q_items;
+  if (j >= rows * W) return;
+  const int32_t w = (int32_t)(j / rows);
+  const int64_t row = j - (int64_t)w * rows;
+  dbwords[j] = pack_word(db_masks + row * d2, d2, w * 64, 0);
 }
 
-// eye_match[e] = OR of part[c][b] over its columns c and row blocks b.
-__global__ void k_eye_any(const uint8_t* part, int64_t n_eyes, int32_t n_shifts, int32_t nb,
-                          uint8_t* eye_match) {
-  const int64_t e = blockIdx.x;
-  __shared__ int flag;
-  if (threadIdx.x == 0) flag = 0;
-  __syncthreads();
-  const int64_t total = (int64_t)n_shifts * nb;
-  int mine = 0;
-  for (int64_t i = threadIdx.x; i < total; i += blockDim.x) mine |= part[e * total + i];
-  if (mine) flag = 1;
-  __syncthreads();
-  if (threadIdx.x == 0) eye_match[e] = (uint8_t)flag;
+// Block (row block, column group): thread = one database row, COLS query columns, whose words are the same for every
+// thread (scalar loads, four vector instructions per word and column: two ANDs, two counting adds).  U words of the
+// row are loaded before the first is used: a thread waits for memory W / U times.
+template <int COLS, int U>
+__global__ void __launch_bounds__(256)
+k_match(const int32_t* ip, const uint64_t* qwords, const uint64_t* dbwords, int64_t d3, int64_t d3p, int64_t rows,
+        int32_t W, uint32_t t_num, uint32_t t_den, int32_t n_shifts, uint8_t* decision, uint8_t* eye) {
+  const int64_t c0 = (int64_t)blockIdx.y * COLS;
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool live = r < rows;
+  const uint64_t* dp = dbwords + (live ? r : 0);
+  const auto* qp = (const __attribute__((address_space(4))) uint64_t*)(qwords + c0);
+  uint32_t ov[COLS];
+#pragma unroll
+  for (int cc = 0; cc < COLS; ++cc) ov[cc] = 0;
+  for (int w0 = 0; w0 < W; w0 += U) {
+    uint64_t dw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) dw[u] = w0 + u < W ? dp[(int64_t)(w0 + u) * rows] : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (w0 + u >= W) break;
+      const auto* qw = qp + (int64_t)(w0 + u) * d3p;
+#pragma unroll
+      for (int cc = 0; cc < COLS; ++cc) {
+        const uint64_t q = qw[cc];
+        ov[cc] += __popc((uint32_t)q & (uint32_t)dw[u]);
+        ov[cc] += __popc((uint32_t)(q >> 32) & (uint32_t)(dw[u] >> 32));
+      }
+    }
+  }
+  if (!live) return;
+  const int64_t lhs_scale = t_den, rhs_scale = (int64_t)t_den - 2 * (int64_t)t_num;
+  int64_t eye_i = c0 / n_shifts;
+  int left = n_shifts - (int)(c0 - eye_i * n_shifts);  // columns of this eye still to come
+#pragma unroll
+  for (int cc = 0; cc < COLS; ++cc) {
+    const int64_t c = c0 + cc;
+    if (c >= d3) break;
+    if (left-- == 0) {
+      ++eye_i;
+      left = n_shifts - 1;
+    }
+    const int64_t x = ip[c * rows + r];
+    const bool dec = ov[cc] > 0 && x * lhs_scale > rhs_scale * (int64_t)ov[cc];
+    if (decision) decision[c * rows + r] = dec ? 1 : 0;
+    if (dec) eye[eye_i] = 1;  // benign race: every writer stores 1
+  }
 }
+
+int64_t match_cols(int64_t d3) { return (d3 + 15) / 16 * 16; }
 
 hipError_t launch_match(const int32_t* ip, const uint8_t* q_masks, int64_t n_eyes,
                         const int32_t* shifts, int32_t n_shifts, const uint8_t* db_masks,
                         int64_t rows, int32_t d2, uint32_t t_num, uint32_t t_den, uint64_t* qwords,
-                        uint64_t* dbwords, uint8_t* decision, uint8_t* part, uint8_t* eye_match,
-                        hipStream_t s) {
+                        uint64_t* dbwords, uint8_t* decision, uint8_t* eye_match, hipStream_t s) {
   if (n_shifts < 1 || n_shifts > kMaxShifts) return hipErrorInvalidValue;
   const int32_t W = (d2 + 63) / 64;
-  const int64_t d3 = n_eyes * n_shifts;
-  Shifts sh{}, zero{};
-  for (int i = 0; i < n_shifts; ++i) sh.r[i] = shifts[i];
-  hipLaunchKernelGGL(k_pack_masks, dim3((unsigned)((d3 * W + 255) / 256)), dim3(256), 0, s,
-                     q_masks, n_eyes, d2, sh, n_shifts, W, qwords);
+  const int64_t d3 = n_eyes * n_shifts, d3p = match_cols(d3);
+  Shifts sh{};
+  for (int i = 0; i < n_shifts; ++i) {
+    const int64_t r = shifts[i] % (int64_t)d2;
+    sh.r[i] = (int32_t)(r < 0 ? r + d2 : r);
+  }
+  const int64_t items = (d3p + rows) * W;  // at least n_eyes
+  hipLaunchKernelGGL(k_pack_masks, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, q_masks, d3, d3p, sh,
+                     n_shifts, db_masks, rows, d2, W, qwords, dbwords, n_eyes, eye_match);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pack_masks, dim3((unsigned)((rows * W + 255) / 256)), dim3(256), 0, s,
-                     db_masks, rows, d2, zero, 1, W, dbwords);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const unsigned nb = (unsigned)((rows + 255) / 256);
-  const size_t lds = sizeof(uint64_t) * kMatchCols * W;
-  if (lds > 65536) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_match),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_match, dim3(nb, (unsigned)((d3 + kMatchCols - 1) / kMatchCols)), dim3(256), lds, s,
-                     ip, qwords, dbwords, d3, rows, W, t_num, t_den, decision, part);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_eye_any, dim3((unsigned)n_eyes), dim3(256), 0, s, part, n_eyes, n_shifts,
-                     (int32_t)nb, eye_match);
+  // 16 columns per thread where that fills the chip (a word of the row is read once per 16 columns), else 4 columns
+  // and blocks of one wavefront
+  const int64_t nb = (rows + 255) / 256;
+  if (nb * (d3p / 16) >= 512)
+    hipLaunchKernelGGL((k_match<16, 4>), dim3((unsigned)nb, (unsigned)(d3p / 16)), dim3(256), 0, s, ip, qwords, dbwords,
+                       d3, d3p, rows, W, t_num, t_den, n_shifts, decision, eye_match);
+  else
+    hipLaunchKernelGGL((k_match<4, 8>), dim3((unsigned)((rows + 63) / 64), (unsigned)((d3 + 3) / 4)), dim3(64), 0, s,
+                       ip, qwords, dbwords, d3, d3p, rows, W, t_num, t_den, n_shifts, decision, eye_match);
   return hipGetLastError();
 }
 

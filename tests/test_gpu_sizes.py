@@ -1,4 +1,4 @@
-"""Every ring degree that a transform kernel is built for, end to end.
+"""Every ring degree that a transform kernel is built for, end to end, and odd sizes of the decision.
 
 The oracle tests pin the residues at some degrees; each other degree has its own register and exchange
 layout, so each is run here: a wrong layout on either side of a product turns decryption into noise.  Inner
@@ -51,7 +51,7 @@ def test_ccmm_decrypts_exactly_at_every_ring_degree(log_n, family):
     else:
         keys = H.hfe_chain_keygen(H.hfe_chain_default_params(log_n, log_n, 5, 3, d2, d1), 5)
         level, form = 5, H.HFE_FORM_P2_I8
-    _say(f"[gpu-degrees] {family} 2^{log_n} d1 {d1} d2 {d2}")
+    _say(f"[gpu-sizes] {family} 2^{log_n} d1 {d1} d2 {d2}")
     db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, form)
     q = H.hfe_encrypt(keys, torch.from_numpy(mq).cuda(), level, 7)
     _check(keys, H.hfe_ccmm(db, q, 0, d1, form), mq, mdb, "all rows")
@@ -70,7 +70,7 @@ def test_format_switch_decrypts_exactly_at_every_query_ring(log_n_q):
     rng = np.random.default_rng(200 + log_n_q)
     mdb, mq = _ternary(rng, d1, d2), _ternary(rng, 3, d2)
     keys = H.hfe_keygen(H.hfe_default_params(7, log_n_q, 3, d2, d1), 5)
-    _say(f"[gpu-degrees] format switch to 2^{log_n_q}")
+    _say(f"[gpu-sizes] format switch to 2^{log_n_q}")
     db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, H.HFE_FORM_RNS_I8)
     fk = H.hfe_fs_keygen(keys, 2, log_n_q + 1, 7)
     T = H.hfe_fs_encrypt(fk, torch.from_numpy(mq).cuda(), 8)
@@ -83,9 +83,37 @@ def test_fold_matches_the_plain_values_at_every_ring_degree(log_n):
     from oracle import fold as OF
     w = S.FoldWorkload(f"fold_n{1 << log_n}", log_n, 4, 6, 1, 1100, (1 << log_n) // 2, S.BASE_SEED + 300 + log_n)
     ip, counts = S.fold_inputs(w)
-    _say(f"[gpu-degrees] fold 2^{log_n}")
+    _say(f"[gpu-sizes] fold 2^{log_n}")
     fk = H.hfe_fold_keygen(w.log_n, w.k, w.rho, 5)
     ct = H.hfe_fold_encrypt(fk, torch.from_numpy(ip).cuda(), 6)
     got = H.hfe_fold_decrypt(fk, H.hfe_fold(fk, ct, torch.from_numpy(counts).cuda(), w.rho)).cpu().numpy()
     want = OF.fold_plain(ip.astype(np.int64), counts.astype(np.int64), w.rho, w.k)
     assert float(np.max(np.abs(got - want))) < 0.02 + 4 * 19 * w.k / 2.0 ** 20
+
+
+def _match_by_hand(ip, qm, shifts, dm):
+    rolled = np.stack([np.roll(qm, int(s), 1) for s in shifts], 1).reshape(-1, qm.shape[1]).astype(np.int64)
+    ov = rolled @ dm.astype(np.int64).T
+    dec = (ov > 0) & (ip.astype(np.int64) * 8 > 2 * ov)
+    return dec.astype(np.uint8), dec.reshape(len(qm), -1).any(1).astype(np.uint8)
+
+
+# code lengths around the 16-byte pieces and 64-bit words, unaligned rows, shifts beyond the code length; few and many
+# columns (both column groups of the kernel)
+@pytest.mark.parametrize("d2,rows,eyes,shifts", [(1, 3, 2, (0,)), (15, 5, 1, (0, 1)), (63, 65, 3, (-8, 7, 0)),
+                                                 (64, 64, 2, (0, 5)), (65, 63, 2, (-1, 1)), (257, 300, 5, (0, -300, 1000)),
+                                                 (1000, 4100, 34, tuple(range(-8, 8))), (1023, 257, 7, (3, -5, 9))])
+def test_match_decisions_at_odd_lengths(d2, rows, eyes, shifts):
+    rng = np.random.default_rng(d2 + rows)
+    qm, dm = (rng.random((eyes, d2)) < 0.9).astype(np.uint8), (rng.random((rows, d2)) < 0.9).astype(np.uint8)
+    qm[0], dm[0] = 0, 0  # no overlap
+    qm[-1] |= (rng.integers(0, 128, d2) * 2).astype(np.uint8)  # only the lowest bit of a mask byte counts
+    ip = rng.integers(-d2, d2 + 1, (eyes * len(shifts), rows)).astype(np.int32)
+    ip[:, 1:] //= 3
+    if eyes > 2:
+        ip[len(shifts):2 * len(shifts)] = -1  # an eye without a match
+    _say(f"[gpu-sizes] match d2 {d2} rows {rows} columns {eyes * len(shifts)}")
+    dec, eye = H.hfe_match(torch.from_numpy(ip).cuda(), torch.from_numpy(qm).cuda(), list(shifts),
+                           torch.from_numpy(dm).cuda())
+    want, want_eye = _match_by_hand(ip, qm & 1, shifts, dm)
+    assert np.array_equal(dec.cpu().numpy(), want) and np.array_equal(eye.cpu().numpy(), want_eye)
