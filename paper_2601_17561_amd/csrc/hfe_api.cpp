@@ -937,6 +937,38 @@ struct Workspace {
 };
 }  // extern "C++"
 
+extern "C++" {
+static int device_cus() {
+  static int cus = 0;
+  if (!cus) {
+    int dev = 0;
+    hipDeviceProp_t prop;
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
+      cus = prop.multiProcessorCount;
+    else
+      cus = 256;
+  }
+  return cus;
+}
+
+// The buffer of a split contraction's parts: `splits` times the bytes of one result (*part).  One part, and no buffer,
+// when the workspace is a fixed region, whose capacity decides what it accepts, or when the memory is not there.
+template <class T>
+static void split_parts(Workspace& W, int64_t tiles, int wgs_per_cu, int64_t KB, size_t elems, hipStream_t s,
+                        int* splits, T** part) {
+  *splits = W.base ? 1 : gemm_splits(tiles, (int64_t)device_cus() * wgs_per_cu, KB);
+  if (*splits > 1 && W.get(sizeof(T) * elems * (size_t)*splits, s, part) != HFE_OK) *splits = 1;
+}
+static AddPartsArgs add_parts_args(int planes, int splits, int64_t n) {
+  AddPartsArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.planes = planes;
+  a.splits = splits;
+  a.n = n;
+  return a;
+}
+}  // extern "C++"
+
 // Every buffer of the call is obtained before its first launch, so a workspace that cannot supply
 // one fails the call with nothing enqueued.
 // C_ext == nullptr: the result (rescaled residues) into R->out.  C_ext != nullptr: only the exact
@@ -987,6 +1019,9 @@ static hfe_status chain_ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t ro
   HFE_TRY(W.get((size_t)slots * 2 * planeX, s, &Xd));
   uint16_t* res = nullptr;
   HFE_TRY(W.get(sizeof(uint16_t) * (size_t)slots * d3 * R_out, s, &res));
+  int splits = 1;
+  uint16_t* part = nullptr;
+  split_parts(W, p2_tiles(d3, R_out, tq) * slots, 1, D->KB, (size_t)slots * d3 * R_out, s, &splits, &part);
   if (out_ext) {
     R->outp = out_ext;
   } else if (!C_ext) {
@@ -1011,7 +1046,8 @@ static hfe_status chain_ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t ro
     pg.rn[j] = la.base[j].rcp_n;
     pg.rm[j] = la.base[j].rcp_m;
   }
-  pg.res = res;
+  pg.res = splits > 1 ? part : res;
+  pg.splits = splits;
   pg.KB = D->KB;
   pg.R_pad = D->R_pad;
   pg.n_db = ndb;
@@ -1021,6 +1057,12 @@ static hfe_status chain_ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t ro
   pg.d3_pad = d3_pad;
   HFE_LAUNCH(mark(1));
   HFE_LAUNCH(launch_gemm_p2(pg, tq, s));
+  if (splits > 1) {
+    AddPartsArgs aa = add_parts_args(slots, splits, d3 * R_out);
+    aa.mods = slots;
+    for (int j = 0; j < slots; ++j) aa.m[j] = (uint64_t)pg.m[j];
+    HFE_LAUNCH(launch_add_parts(aa, 2, part, res, s));
+  }
   if (C_ext) return hip_ok_or_fail(launch_chain_widen(res, d3 * R_out, level, np, C_ext, s));
   HFE_LAUNCH(mark(2));
   ChainRescaleArgs ra;
@@ -1123,6 +1165,10 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     HFE_TRY(W.get((size_t)nz * n * planeX, s, &Xd));
     uint8_t* res = nullptr;
     HFE_TRY(W.get((size_t)nz * n * d3 * R_out, s, &res));
+    int splits = 1;
+    uint8_t* part = nullptr;
+    split_parts(W, rns_tiles(d3, R_out, tq) * n * nz, rns_wgs_per_cu(tq), D->KB, (size_t)nz * n * d3 * R_out, s,
+                &splits, &part);
     HFE_LAUNCH(launch_lift_rns(Qc->XT.as<uint64_t>(), d3, D->K, D->KB, d3_pad, la, n, Xd, s));
     RnsGemmArgs rg;
     std::memset(&rg, 0, sizeof(rg));
@@ -1136,7 +1182,8 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
       rg.m[j] = kRnsMods[j];
       rg.magic[j] = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)kRnsMods[j] - 1) / (uint64_t)kRnsMods[j]);
     }
-    rg.res = res;
+    rg.res = splits > 1 ? part : res;
+    rg.splits = splits;
     rg.KB = D->KB;
     rg.R_pad = D->R_pad;
     rg.n_db = ndb;
@@ -1146,6 +1193,12 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     rg.d3_pad = d3_pad;
     HFE_LAUNCH(mark(1));
     HFE_LAUNCH(launch_gemm_rns(rg, tq, s));
+    if (splits > 1) {
+      AddPartsArgs aa = add_parts_args(nz * n, splits, d3 * R_out);
+      aa.mods = n;
+      for (int j = 0; j < n; ++j) aa.m[j] = (uint64_t)rg.m[j];
+      HFE_LAUNCH(launch_add_parts(aa, 1, part, res, s));
+    }
     HFE_LAUNCH(mark(2));
     if (product)
       HFE_LAUNCH(launch_crt_rns(res, nz, d3 * R_out, make_rns_crt_args(K, level, n), Cp, s));
@@ -1161,6 +1214,9 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     HFE_TRY(W.get((size_t)nz * 2 * n * planeX, s, &Xd));
     uint16_t* res = nullptr;
     HFE_TRY(W.get(sizeof(uint16_t) * (size_t)nz * n * d3 * R_out, s, &res));
+    int splits = 1;
+    uint16_t* part = nullptr;
+    split_parts(W, p2_tiles(d3, R_out, tq) * n * nz, 1, D->KB, (size_t)nz * n * d3 * R_out, s, &splits, &part);
     HFE_LAUNCH(launch_lift_p2(Qc->XT.as<uint64_t>(), d3, D->K, D->KB, d3_pad, la, n, Xd, s));
     P2GemmArgs pg;
     std::memset(&pg, 0, sizeof(pg));
@@ -1176,7 +1232,8 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
       pg.rn[j] = 1.0 / (double)pg.n[j];
       pg.rm[j] = 1.0 / (double)pg.m[j];
     }
-    pg.res = res;
+    pg.res = splits > 1 ? part : res;
+    pg.splits = splits;
     pg.KB = D->KB;
     pg.R_pad = D->R_pad;
     pg.n_db = ndb;
@@ -1186,6 +1243,12 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     pg.d3_pad = d3_pad;
     HFE_LAUNCH(mark(1));
     HFE_LAUNCH(launch_gemm_p2(pg, tq, s));
+    if (splits > 1) {
+      AddPartsArgs aa = add_parts_args(nz * n, splits, d3 * R_out);
+      aa.mods = n;
+      for (int j = 0; j < n; ++j) aa.m[j] = (uint64_t)pg.m[j];
+      HFE_LAUNCH(launch_add_parts(aa, 2, part, res, s));
+    }
     HFE_LAUNCH(mark(2));
     if (product)
       HFE_LAUNCH(launch_crt_p2(res, nz, d3 * R_out, make_p2_crt_args(K, level, n), Cp, s));
@@ -1196,13 +1259,23 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     const size_t planeD = (size_t)D->KB * D->R_pad * kKB;
     int8_t* Xd = nullptr;
     HFE_TRY(W.get((size_t)nz * kDigits * planeX, s, &Xd));
+    const int variant = pick_i8_variant(level, d3);
+    const int64_t br = i8_variant_tile_rows(variant), bq = i8_variant_tile_cols(variant);
+    split_parts(W, ((R_out + br - 1) / br) * ((d3 + bq - 1) / bq) * nz, i8_variant_wgs_per_cu(variant), D->KB,
+                (size_t)nz * d3 * R_out, s, &g.splits, &g.part);
     HFE_LAUNCH(launch_lift(Qc->XT.as<uint64_t>(), d3, D->K, D->KB, g.d3_pad, la, nullptr, Xd, s));
     for (int z = 0; z < nz; ++z) {
       g.Dd[z] = D->digits.as<int8_t>() + (size_t)slot(z) * kDigits * planeD;
       g.Xd[z] = Xd + (size_t)z * kDigits * planeX;
     }
     HFE_LAUNCH(mark(1));
-    HFE_LAUNCH(launch_gemm_i8(g, pick_i8_variant(level, d3), s));
+    HFE_LAUNCH(launch_gemm_i8(g, variant, s));
+    if (g.splits > 1) {
+      AddPartsArgs aa = add_parts_args(nz, g.splits, d3 * R_out);
+      aa.mods = nz;
+      for (int z = 0; z < nz; ++z) aa.m[z] = g.mod[z].q;
+      HFE_LAUNCH(launch_add_parts(aa, 8, g.part, Cp, s));
+    }
   }
   if (!fused && !product) {
     HFE_LAUNCH(mark(2));
@@ -1623,19 +1696,6 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
     ch->n = small ? np : 0;
   }
   return z;
-}
-
-int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-    else
-      cus = 256;
-  }
-  return cus;
 }
 
 int gemm_grid_for(int form, int variant) {

@@ -303,12 +303,14 @@ struct RnsGemmArgs {
   const int8_t* Xr[kMaxPrimes];                // [n_mod][KB][d3_pad][64]
   int32_t m[kRnsMaxMods];
   uint32_t magic[kRnsMaxMods];                 // ceil(2^32 / m): x mod m by multiply-high, x < 2^24
-  uint8_t* res;                                // [nz][n_mod][d3][R_out], residues < m_j <= 256
+  uint8_t* res;                                // [splits][nz][n_mod][d3][R_out], residues < m_j <= 256
+  int splits;                                  // 0 or 1: whole
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
 hipError_t launch_gemm_rns(const RnsGemmArgs& g, int tq, hipStream_t s);
 // the tile width with less padded work for problems of d3 columns, R_out rows and nz prime slots
+int64_t rns_tiles(int64_t d3, int64_t R_out, int tq);  // workgroups of one (prime, modulus)
 int rns_tile_q(const int64_t* d3, const int64_t* R_out, const int* nz, int n);
 struct RnsCrtArgs {
   int n;                                       // moduli in use
@@ -340,12 +342,14 @@ struct P2GemmArgs {
   const int8_t* Xq[kMaxPrimes];                // [2 n_bases][KB][d3_pad][64]
   int32_t n[kP2ArgBases], m[kP2ArgBases];      // base j: n_j and n_j^2
   double rn[kP2ArgBases], rm[kP2ArgBases];     // RN(1 / n_j), RN(1 / n_j^2)
-  uint16_t* res;                               // [nz][n_bases][d3][R_out], residues < n^2
+  uint16_t* res;                               // [splits][nz][n_bases][d3][R_out], residues < n^2
+  int splits;                                  // 0 or 1: whole
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;  // d3_pad a multiple of the query tile width
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
 hipError_t launch_gemm_p2(const P2GemmArgs& g, int tq, hipStream_t s);
 // the tile width with less padded work for problems of d3 columns, R_out rows and nz prime slots
+int64_t p2_tiles(int64_t d3, int64_t R_out, int tq);  // workgroups of one (slot, base)
 int p2_tile_q(const int64_t* d3, const int64_t* R_out, const int* nz, int n);
 struct P2CrtArgs {
   int n;                                       // bases in use
@@ -457,7 +461,20 @@ struct GemmArgs {
   uint64_t* C[kMaxPrimes];
   Mod mod[kMaxPrimes];
   int64_t K, KB, R_db, R_pad, n_db, row0, rows, R_out, d3, d3_pad;
+  int splits;                                  // parts of the K-blocks (0 or 1: whole), see gemm_splits
+  uint64_t* part;                              // [splits][nz][d3][R_out] when splits > 1
 };
+// Parts to cut the K-blocks of a contraction into when its `tiles` workgroups do not fill the chip's `slots`
+// resident ones, or leave a last wave nearly empty: each part's workgroups give residues of their own, and one
+// pass adds them (launch_add_parts).
+int gemm_splits(int64_t tiles, int64_t slots, int64_t KB);
+// out[p][e] = sum over s < splits of part[s][p][e] mod m[p], p < planes, e < n; residues of `bytes` (1, 2 or 8) each
+struct AddPartsArgs {
+  int planes, splits, mods;                    // plane p is mod m[p % mods]
+  int64_t n;
+  uint64_t m[kMaxPrimes + 16];
+};
+hipError_t launch_add_parts(const AddPartsArgs& a, int bytes, const void* part, void* out, hipStream_t s);
 hipError_t launch_gemm_plain(const GemmArgs& g, hipStream_t s);
 // rate probes (k_probe.hip): which 1 = int8 MFMA on streaming random operands, 2 = on zero
 // operands, 3 = v_mad_u64_u32; grid workgroups of 256 threads, sink >= grid * 256 * 8 bytes

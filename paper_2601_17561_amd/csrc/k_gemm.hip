@@ -125,6 +125,7 @@ struct I8Tile {
   Mod m;
   int64_t KB, R_pad, d3_pad, n_db, row0, R_out, d3;
   int64_t r0, c0;     // tile origin: output row, query column
+  int64_t nk;         // K-blocks of the tile, from the first of Xd and Dd
 };
 
 // Tile index within one prime of a problem -> (row tile, column tile), XCD-aware: tile index l
@@ -219,8 +220,8 @@ __device__ __forceinline__ void tile_basic(const I8Tile& T, int8_t* lds) {
         if (okB[i]) *reinterpret_cast<v4i*>(sB(buf, t) + offB[i]) = pb[t][i];
     }
   };
-  for (int64_t kb0 = 0; kb0 < T.KB; kb0 += kChunkKB) {
-    const int64_t kb1 = kb0 + kChunkKB < T.KB ? kb0 + kChunkKB : T.KB;
+  for (int64_t kb0 = 0; kb0 < T.nk; kb0 += kChunkKB) {
+    const int64_t kb1 = kb0 + kChunkKB < T.nk ? kb0 + kChunkKB : T.nk;
     v16i acc[9];
 #pragma unroll
     for (int u = 0; u < 9; ++u) acc[u] = (v16i){0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -295,8 +296,8 @@ __device__ __forceinline__ void tile_pipe(const I8Tile& T, int8_t* lds) {
       *reinterpret_cast<v4i*>(sB(buf, i - kDigits) + st_off) = p[i];
   };
 
-  for (int64_t kb0 = 0; kb0 < T.KB; kb0 += kChunkKB) {
-    const int64_t kb_end = kb0 + kChunkKB < T.KB ? kb0 + kChunkKB : T.KB;
+  for (int64_t kb0 = 0; kb0 < T.nk; kb0 += kChunkKB) {
+    const int64_t kb_end = kb0 + kChunkKB < T.nk ? kb0 + kChunkKB : T.nk;
     const int64_t n = kb_end - kb0;
     v16i acc[9];
 #pragma unroll
@@ -400,8 +401,8 @@ __device__ __forceinline__ void tile_dma(const I8Tile& T, int8_t* lds) {
   const int offA = (wq * 32 + (lane & 31)) * kDmaRow, offB = kDigits * kPA + (wr * 32 + (lane & 31)) * kDmaRow;
   const int c0 = lane >> 5;  // logical chunk of the first K-half; the second half adds 2
 
-  for (int64_t kb0 = 0; kb0 < T.KB; kb0 += kChunkKB) {
-    const int64_t kb_end = kb0 + kChunkKB < T.KB ? kb0 + kChunkKB : T.KB;
+  for (int64_t kb0 = 0; kb0 < T.nk; kb0 += kChunkKB) {
+    const int64_t kb_end = kb0 + kChunkKB < T.nk ? kb0 + kChunkKB : T.nk;
     const int64_t n = kb_end - kb0;
     auto clamp = [&](int64_t i) { return kb0 + (i < n ? i : n - 1); };
     v16i acc[9];
@@ -515,8 +516,8 @@ __device__ __forceinline__ void tile_dma_split(const I8Tile& T, int8_t* lds) {
   const int offA = (wq * 32 + (lane & 31)) * kDmaRow, offB = 2 * kQS + (wr * 32 + (lane & 31)) * kDmaRow;
   const int c0 = lane >> 5;
 
-  for (int64_t kb0 = 0; kb0 < T.KB; kb0 += kChunkKB) {
-    const int64_t kb_end = kb0 + kChunkKB < T.KB ? kb0 + kChunkKB : T.KB;
+  for (int64_t kb0 = 0; kb0 < T.nk; kb0 += kChunkKB) {
+    const int64_t kb_end = kb0 + kChunkKB < T.nk ? kb0 + kChunkKB : T.nk;
     const int64_t n = kb_end - kb0;
     auto clamp = [&](int64_t i) { return kb0 + (i < n ? i : n - 1); };
     v16i acc[9];
@@ -584,8 +585,11 @@ k_gemm_i8(GemmArgs g) {
   const int64_t n_ct = (g.d3 + BQ - 1) / BQ, n_rt = (g.R_out + BR - 1) / BR;
   int64_t rt, ct;
   if (!tile_coords(blockIdx.x, n_rt, n_ct, rt, ct)) return;
-  I8Tile T{g.Xd[z], g.Dd[z], g.C[z], g.mod[z], g.KB, g.R_pad, g.d3_pad, g.n_db, g.row0, g.R_out, g.d3,
-           rt * BR, ct * BQ};
+  const int sp = blockIdx.y, ns = gridDim.y;  // part sp of the K-blocks
+  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;
+  I8Tile T{g.Xd[z] + (size_t)k0 * g.d3_pad * kKB, g.Dd[z] + (size_t)k0 * g.R_pad * kKB,
+           ns > 1 ? g.part + ((size_t)sp * g.nz + z) * g.d3 * g.R_out : g.C[z], g.mod[z], g.KB, g.R_pad, g.d3_pad,
+           g.n_db, g.row0, g.R_out, g.d3, rt * BR, ct * BQ, k1 - k0};
   run_tile<WR, WQ, NBUF, WPE, MODE>(T, lds);
 }
 
@@ -630,7 +634,7 @@ k_gemm_i8_batched(BatchGemmArgs a) {
     const size_t planeX = (size_t)a.KB * d.d3_pad * kKB * kDigits;
     const size_t planeD = (size_t)a.KB * a.R_pad * kKB * kDigits;
     I8Tile T{d.Xd + z * planeX, a.Dd + d.slot[z] * planeD, d.C + (size_t)z * d.d3 * d.R_out, d.mod[z], a.KB,
-             a.R_pad, d.d3_pad, d.n_db, d.row0, d.R_out, d.d3, rt * BR, ct * BQ};
+             a.R_pad, d.d3_pad, d.n_db, d.row0, d.R_out, d.d3, rt * BR, ct * BQ, a.KB};
     run_tile<WR, WQ, NBUF, WPE, MODE>(T, lds);
   }
 }
@@ -675,8 +679,50 @@ hipError_t launch_gemm_i8(const GemmArgs& g, int variant, hipStream_t s) {
   if (g.d3_pad % v.bq != 0) return hipErrorInvalidValue;  // query padding must cover the tile
   const int64_t n_ct = (g.d3 + v.bq - 1) / v.bq, n_rt = (g.R_out + v.br - 1) / v.br;
   const int64_t n_rt8 = (n_rt + kXcds - 1) / kXcds * kXcds;
-  dim3 grid((unsigned)(n_rt8 * n_ct), 1, (unsigned)g.nz);
+  const int ns = g.splits > 1 ? g.splits : 1;
+  if (ns > g.KB || (ns > 1 && !g.part)) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)ns, (unsigned)g.nz);
   hipLaunchKernelGGL(v.grid, grid, dim3(v.threads), 0, s, g);
+  return hipGetLastError();
+}
+
+// Splitting pays where it shortens the longest chain of K-blocks a CU works through, ceil(tiles / slots) of them
+// whole: the fewest parts within 15% of the shortest (each part costs a prologue and an epilogue), of at least 16
+// K-blocks.  Measured, contraction + sum of the parts: 4 columns, 4,352 rows, K = 5,120 (68 workgroups of the digit
+// tile) 168 -> 71 + 5 us in 3 parts; 48 columns, 4,896 rows, K = 7,563 (77) 288 -> 129 + 5 us in 3; the n^2 tile at a
+// nearly empty last wave 1,032 -> 937 + 27 us; the RNS tile, which streams more bytes per product, 85 -> 75 + 5 us.
+int gemm_splits(int64_t tiles, int64_t slots, int64_t KB) {
+  if (tiles <= 0 || slots <= 0) return 1;
+  auto cost = [&](int64_t s) { return (double)((tiles * s + slots - 1) / slots) / (double)s; };
+  int best = 1;
+  for (int s = 2; s <= 16 && s * 16 <= KB; ++s)
+    if (cost(s) < 0.85 * cost(best)) best = s;
+  return best;
+}
+
+template <class T>
+__global__ void __launch_bounds__(256) k_add_parts(AddPartsArgs a, const T* part, T* out) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= a.n) return;
+  const int p = blockIdx.y;
+  const size_t off = (size_t)p * a.n + e, step = (size_t)a.planes * a.n;
+  uint64_t v = 0;
+  for (int s = 0; s < a.splits; ++s) v += part[off + s * step];  // at most 16 residues below 2^36
+  const uint64_t m = a.m[p % a.mods];
+  if constexpr (sizeof(T) == 8)
+    out[off] = (T)(v % m);
+  else
+    out[off] = (T)((uint32_t)v % (uint32_t)m);
+}
+
+hipError_t launch_add_parts(const AddPartsArgs& a, int bytes, const void* part, void* out, hipStream_t s) {
+  const dim3 grid((unsigned)((a.n + 255) / 256), (unsigned)a.planes);
+  if (bytes == 1)
+    hipLaunchKernelGGL(k_add_parts<uint8_t>, grid, dim3(256), 0, s, a, (const uint8_t*)part, (uint8_t*)out);
+  else if (bytes == 2)
+    hipLaunchKernelGGL(k_add_parts<uint16_t>, grid, dim3(256), 0, s, a, (const uint16_t*)part, (uint16_t*)out);
+  else
+    hipLaunchKernelGGL(k_add_parts<uint64_t>, grid, dim3(256), 0, s, a, (const uint64_t*)part, (uint64_t*)out);
   return hipGetLastError();
 }
 

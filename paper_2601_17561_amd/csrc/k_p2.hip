@@ -111,6 +111,7 @@ struct P2Tile {
   int32_t bn, bm;        // the base n and n^2 of this product
   double brn, brm;       // RN(1 / n), RN(1 / n^2)
   int64_t KB, R_pad, d3_pad, n_db, row0, R_out, d3, r0, c0;
+  int64_t nk;  // K-blocks of the tile, from the first of X and D (KB: the planes' stride)
 };
 
 template <int TQ>
@@ -158,7 +159,7 @@ __device__ __forceinline__ void p2_tile(const P2Tile& g, int8_t* lds) {
       acc0[a][b] = (v16i){0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
       acc1[a][b] = acc0[a][b];
     }
-  const int64_t KB = g.KB;
+  const int64_t KB = g.nk;
   auto clamp = [&](int64_t i) { return i < KB ? i : KB - 1; };
   // fragments of one half (32 bytes of K) of the K-block in stage st: [0] the M / N plane, [1] M' / N'
   struct Frags {
@@ -243,14 +244,15 @@ __global__ void __launch_bounds__(64 * P2Cfg<TQ>::NW) __attribute__((amdgpu_wave
 k_gemm_p2(P2GemmArgs g) {
   using C = P2Cfg<TQ>;
   __shared__ __attribute__((aligned(16))) int8_t lds[C::LDS];
-  const int j = blockIdx.y, z = blockIdx.z;
+  const int j = blockIdx.y % g.n_bases, sp = blockIdx.y / g.n_bases, ns = gridDim.y / g.n_bases, z = blockIdx.z;
+  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;  // part sp of the K-blocks
   const int64_t n_ct = (g.d3 + C::TQ - 1) / C::TQ, n_rt = (g.R_out + C::TR - 1) / C::TR;
   const int64_t l = blockIdx.x, xcd = l % kXcds, jj = l / kXcds;
   const int64_t rt = (jj / n_ct) * kXcds + xcd, ct = jj % n_ct;
   if (rt >= n_rt) return;
-  P2Tile t{g.Xq[z] + (size_t)(2 * j) * g.KB * g.d3_pad * kKB, g.Dq[z] + (size_t)(2 * j) * g.KB * g.R_pad * kKB,
-           g.res + ((size_t)z * g.n_bases + j) * g.d3 * g.R_out, j, g.n[j], g.m[j], g.rn[j], g.rm[j], g.KB, g.R_pad,
-           g.d3_pad, g.n_db, g.row0, g.R_out, g.d3, rt * C::TR, ct * C::TQ};
+  P2Tile t{g.Xq[z] + ((size_t)(2 * j) * g.KB + k0) * g.d3_pad * kKB, g.Dq[z] + ((size_t)(2 * j) * g.KB + k0) * g.R_pad * kKB,
+           g.res + (((size_t)sp * g.nz + z) * g.n_bases + j) * g.d3 * g.R_out, j, g.n[j], g.m[j], g.rn[j], g.rm[j], g.KB, g.R_pad,
+           g.d3_pad, g.n_db, g.row0, g.R_out, g.d3, rt * C::TR, ct * C::TQ, k1 - k0};
   p2_tile<TQ>(t, lds);
 }
 
@@ -295,7 +297,7 @@ k_gemm_p2_batched(P2BatchArgs a) {
               a.Dq + (size_t)(d.slot[z] * a.n_bases + j) * 2 * a.KB * a.R_pad * kKB,
               reinterpret_cast<uint16_t*>(d.res) + ((size_t)z * a.n_bases + j) * d.d3 * d.R_out, j, kP2C.n[j],
               kP2C.m[j], kP2C.rcp_n[j], kP2C.rcp_m[j], a.KB, a.R_pad, d.d3_pad, d.n_db, d.row0, d.R_out, d.d3,
-              rt * C::TR, ct * C::TQ};
+              rt * C::TR, ct * C::TQ, a.KB};
     p2_tile<TQ>(tl, lds);
   }
 }
@@ -329,6 +331,11 @@ hipError_t launch_gemm_p2_batched(const P2BatchArgs& a, int grid, int tq, hipStr
   return hipGetLastError();
 }
 
+int64_t p2_tiles(int64_t d3, int64_t R_out, int tq) {
+  const int64_t tr = p2_rows_of(tq);
+  return ((d3 + tq - 1) / tq) * ((R_out + tr - 1) / tr);
+}
+
 hipError_t launch_gemm_p2(const P2GemmArgs& g, int tq, hipStream_t s) {
   if (g.R_out <= 0 || g.d3 <= 0) return hipSuccess;
   if ((tq != 128 && tq != 256) || g.d3_pad % tq != 0 || g.n_bases < 1 || g.n_bases > kP2ArgBases)
@@ -336,7 +343,9 @@ hipError_t launch_gemm_p2(const P2GemmArgs& g, int tq, hipStream_t s) {
   const int64_t tr = p2_rows_of(tq);
   const int64_t n_ct = (g.d3 + tq - 1) / tq, n_rt = (g.R_out + tr - 1) / tr;
   const int64_t n_rt8 = (n_rt + kXcds - 1) / kXcds * kXcds;
-  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)g.n_bases, (unsigned)g.nz);
+  const int ns = g.splits > 1 ? g.splits : 1;
+  if (ns > g.KB) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)(g.n_bases * ns), (unsigned)g.nz);
   if (tq == 128)
     hipLaunchKernelGGL(k_gemm_p2<128>, grid, dim3(64 * P2Cfg<128>::NW), 0, s, g);
   else

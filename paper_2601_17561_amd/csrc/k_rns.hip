@@ -96,7 +96,7 @@ struct RnsTile {
   uint8_t* res;
   int32_t m;
   uint32_t magic;
-  int64_t KB, R_pad, d3_pad, n_db, row0, R_out, d3, r0, c0;
+  int64_t nk, R_pad, d3_pad, n_db, row0, R_out, d3, r0, c0;  // nk: K-blocks from the first of X and D
 };
 
 // this wave's loads of the oldest outstanding K-block have landed (the younger ones may still fly)
@@ -150,7 +150,7 @@ __device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds) {
   for (int a = 0; a < C::WQB; ++a)
 #pragma unroll
     for (int b = 0; b < C::WRB; ++b) acc[a][b] = (v16i){0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const int64_t KB = g.KB;
+  const int64_t KB = g.nk;
   auto clamp = [&](int64_t i) { return i < KB ? i : KB - 1; };
   // fragments of one half (32 bytes of K) of the K-block in stage st
   auto read_half = [&](int st, int h, v4i (&fa)[C::WQB], v4i (&fb)[C::WRB]) {
@@ -222,13 +222,14 @@ __global__ void __launch_bounds__(64 * RnsCfg<TQ>::NW) __attribute__((amdgpu_wav
 k_gemm_rns(RnsGemmArgs g) {
   using C = RnsCfg<TQ>;
   __shared__ __attribute__((aligned(16))) int8_t lds[C::LDS];
-  const int j = blockIdx.y, z = blockIdx.z;
+  const int j = blockIdx.y % g.n_mod, sp = blockIdx.y / g.n_mod, ns = gridDim.y / g.n_mod, z = blockIdx.z;
+  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;  // part sp of the K-blocks
   const int64_t n_ct = (g.d3 + TQ - 1) / TQ, n_rt = (g.R_out + C::TR - 1) / C::TR;
   const int64_t l = blockIdx.x, xcd = l % kXcds, jj = l / kXcds;
   const int64_t rt = (jj / n_ct) * kXcds + xcd, ct = jj % n_ct;
   if (rt >= n_rt) return;
-  RnsTile t{g.Xr[z] + (size_t)j * g.KB * g.d3_pad * kKB, g.Dr[z] + (size_t)j * g.KB * g.R_pad * kKB,
-            g.res + ((size_t)z * g.n_mod + j) * g.d3 * g.R_out, g.m[j], g.magic[j], g.KB, g.R_pad, g.d3_pad, g.n_db,
+  RnsTile t{g.Xr[z] + ((size_t)j * g.KB + k0) * g.d3_pad * kKB, g.Dr[z] + ((size_t)j * g.KB + k0) * g.R_pad * kKB,
+            g.res + (((size_t)sp * g.nz + z) * g.n_mod + j) * g.d3 * g.R_out, g.m[j], g.magic[j], k1 - k0, g.R_pad, g.d3_pad, g.n_db,
             g.row0, g.R_out, g.d3, rt * C::TR, ct * TQ};
   rns_tile<TQ>(t, lds);
 }
@@ -293,6 +294,10 @@ hipError_t launch_gemm_rns_batched(const RnsBatchArgs& a, int grid, int tq, hipS
   return hipGetLastError();
 }
 
+int64_t rns_tiles(int64_t d3, int64_t R_out, int tq) {
+  return ((d3 + tq - 1) / tq) * ((R_out + kRnsTileR - 1) / kRnsTileR);
+}
+
 // resident workgroups per CU: as many as the 160 KiB of LDS hold, at most two waves per SIMD
 template <int TQ>
 static int wgs_per_cu() {
@@ -320,7 +325,9 @@ hipError_t launch_gemm_rns(const RnsGemmArgs& g, int tq, hipStream_t s) {
   if ((tq != 128 && tq != 256) || g.d3_pad % tq != 0) return hipErrorInvalidValue;
   const int64_t n_ct = (g.d3 + tq - 1) / tq, n_rt = (g.R_out + kRnsTileR - 1) / kRnsTileR;
   const int64_t n_rt8 = (n_rt + kXcds - 1) / kXcds * kXcds;
-  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)g.n_mod, (unsigned)g.nz);
+  const int ns = g.splits > 1 ? g.splits : 1;
+  if (ns > g.KB) return hipErrorInvalidValue;
+  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)(g.n_mod * ns), (unsigned)g.nz);
   if (tq == 128)
     hipLaunchKernelGGL(k_gemm_rns<128>, grid, dim3(64 * RnsCfg<128>::NW), 0, s, g);
   else

@@ -117,3 +117,28 @@ def test_match_decisions_at_odd_lengths(d2, rows, eyes, shifts):
                            torch.from_numpy(dm).cuda())
     want, want_eye = _match_by_hand(ip, qm & 1, shifts, dm)
     assert np.array_equal(dec.cpu().numpy(), want) and np.array_equal(eye.cpu().numpy(), want_eye)
+
+
+# K-blocks of 64: 145 (the last one ragged), so parts of unequal length; one row tile and three, one column and several
+@pytest.mark.parametrize("rows,cols", [(37, 1), (37, 130), (300, 5)])
+@pytest.mark.parametrize("form", ["i8", "rns", "p2", "chain"])
+def test_contraction_split_along_the_code_length_gives_the_same_residues(form, rows, cols):
+    d2 = 9219
+    rng = np.random.default_rng(300 + rows + cols)
+    if form == "chain":
+        keys, level, f = H.hfe_chain_keygen(H.hfe_chain_default_params(6, 6, 5, 3, d2, rows), 5), 5, H.HFE_FORM_P2_I8
+    else:
+        keys, level = H.hfe_keygen(H.hfe_default_params(6, 6, 3, d2, rows), 5), 3
+        f = {"i8": H.HFE_FORM_I8_MFMA, "rns": H.HFE_FORM_RNS_I8, "p2": H.HFE_FORM_P2_I8}[form]
+    mdb, mq = _ternary(rng, rows, d2), _ternary(rng, cols, d2)
+    db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, f)
+    q = H.hfe_encrypt(keys, torch.from_numpy(mq).cuda(), level, 7)
+    H.hfe_noalloc_init()
+    _say(f"[gpu-sizes] split {form} rows {rows} cols {cols}")
+    r = H.hfe_ccmm(db, q, 0, rows, f)
+    got = H.hfe_export(r, 0)
+    out = torch.zeros(got.size, dtype=torch.int64, device="cuda")
+    H.hfe_ccmm_noalloc(db, q, 0, rows, f, out)  # one part: its region is fixed
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), got.astype(np.int64))
+    _check(keys, r, mq, mdb, "split")
