@@ -1578,7 +1578,7 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
     z.xd_bytes += (size_t)(P.level + 1) * planes * D->KB * d3_pad[b] * kKB;
   }
   int64_t tiles = 0, crt_e = 0, tiles_wide = 0;
-  int n_wide = 0;
+  int n_wide = 0, rot = 0;
   for (int k = 0; k < np; ++k) {
     const int b = ord[k];  // table position k
     const Problem& P = gr.p[b];
@@ -1600,6 +1600,7 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
       g.d3_pad = d3_pad[P.owner];
       g.tile_begin = tiles;
       g.nz = nz;
+      g.rot = rot;
       for (int zz = 0; zz < nz; ++zz) {
         g.slot[zz] = zz < level ? zz : K->L;
         g.mod[zz] = K->mods[g.slot[zz]];
@@ -1616,9 +1617,11 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
         c.pslot = K->L;
       }
     }
-    tiles += rns      ? rns_batched_tiles(d3, R_out[b], nz, planes, tq[b])
-             : fs.p2 ? p2_batched_tiles(d3, R_out[b], nz, D->n_p2, tq[b])
-                     : i8_batched_tiles(variant, d3, R_out[b], nz);
+    int64_t groups = 0;
+    tiles += rns      ? rns_batched_tiles(d3, R_out[b], nz, planes, tq[b], &groups)
+             : fs.p2 ? p2_batched_tiles(d3, R_out[b], nz, D->n_p2, tq[b], &groups)
+                     : i8_batched_tiles(variant, d3, R_out[b], nz, &groups);
+    rot = (int)((rot + groups) % kXcds);
     if (small && tq[b] == 256) {
       tiles_wide = tiles;
       n_wide = k + 1;

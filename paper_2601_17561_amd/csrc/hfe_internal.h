@@ -304,7 +304,7 @@ struct RnsGemmArgs {
   int32_t m[kRnsMaxMods];
   uint32_t magic[kRnsMaxMods];                 // ceil(2^32 / m): x mod m by multiply-high, x < 2^24
   uint8_t* res;                                // [splits][nz][n_mod][d3][R_out], residues < m_j <= 256
-  int splits;                                  // 0 or 1: whole
+  int splits;                                  // parts of the K-blocks, see gemm_splits
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
@@ -343,7 +343,7 @@ struct P2GemmArgs {
   int32_t n[kP2ArgBases], m[kP2ArgBases];      // base j: n_j and n_j^2
   double rn[kP2ArgBases], rm[kP2ArgBases];     // RN(1 / n_j), RN(1 / n_j^2)
   uint16_t* res;                               // [splits][nz][n_bases][d3][R_out], residues < n^2
-  int splits;                                  // 0 or 1: whole
+  int splits;                                  // parts of the K-blocks, see gemm_splits
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;  // d3_pad a multiple of the query tile width
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
@@ -412,7 +412,7 @@ struct BatchHeader;
 struct BatchElemHeader;
 struct BatchCrtDesc;
 // Batched RNS contraction: problem b's tiles are [tile_begin, tile_begin + rns_batched_tiles(...)),
-// ordered (z, modulus, XCD-ordered tile); workgroups claim tiles per XCD as the digit form's.  The
+// ordered (z, modulus, row tile, column tile); workgroups claim tiles per XCD as the digit form's.  The
 // launch with tq = 256 serves problems [0, hdr->n_wide), the one with tq = 128 the others.
 struct RnsBatchArgs {
   const BatchHeader* hdr;
@@ -425,10 +425,10 @@ struct RnsBatchArgs {
   uint32_t magic[kRnsMaxMods];
   int64_t KB, R_pad;
 };
-int64_t rns_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_mod, int tq);
+int64_t rns_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_mod, int tq, int64_t* groups);
 hipError_t launch_gemm_rns_batched(const RnsBatchArgs& a, int grid, int tq, hipStream_t s);
 // Batched n^2 contraction: problem b's tiles are [tile_begin, tile_begin + p2_batched_tiles(...)),
-// ordered (z, base, XCD-ordered tile); the launch with tq = 256 serves problems [0, hdr->n_wide)
+// ordered (z, base, row tile, column tile); the launch with tq = 256 serves problems [0, hdr->n_wide)
 // through hdr->next, the one with tq = 128 the others through hdr->next_narrow.  Residues (uint16)
 // go to desc.res.
 struct P2BatchArgs {
@@ -440,7 +440,7 @@ struct P2BatchArgs {
   int32_t n_bases, pad_;
   int64_t KB, R_pad;
 };
-int64_t p2_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_bases, int tq);
+int64_t p2_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_bases, int tq, int64_t* groups);
 hipError_t launch_gemm_p2_batched(const P2BatchArgs& a, int grid, int tq, hipStream_t s);
 // ra indexed by database slot; d[b].res points at uint16 residues
 hipError_t launch_crt_p2_batched(const BatchElemHeader* hdr, const BatchCrtDesc* d, const P2CrtArgs& ra, int grid,
@@ -461,13 +461,21 @@ struct GemmArgs {
   uint64_t* C[kMaxPrimes];
   Mod mod[kMaxPrimes];
   int64_t K, KB, R_db, R_pad, n_db, row0, rows, R_out, d3, d3_pad;
-  int splits;                                  // parts of the K-blocks (0 or 1: whole), see gemm_splits
+  int splits;                                  // parts of the K-blocks, see gemm_splits
   uint64_t* part;                              // [splits][nz][d3][R_out] when splits > 1
 };
 // Parts to cut the K-blocks of a contraction into when its `tiles` workgroups do not fill the chip's `slots`
 // resident ones, or leave a last wave nearly empty: each part's workgroups give residues of their own, and one
 // pass adds them (launch_add_parts).
 int gemm_splits(int64_t tiles, int64_t slots, int64_t KB);
+// Launch grid of `groups` groups of n_ct tiles (xcd_tile), in rows of a multiple of 8.
+inline dim3 xcd_grid(int64_t groups, int64_t n_ct) {
+  const int64_t rest = groups % kXcds * n_ct;
+  const int64_t wgs = (groups / kXcds * n_ct + (rest + kXcds - 1) / kXcds) * kXcds, gx = wgs < (1 << 20) ? wgs : (1 << 20);
+  return dim3((unsigned)gx, (unsigned)((wgs + gx - 1) / gx));
+}
+// Tile slots of one problem of a batch (batch_tile).
+inline int64_t batch_slots(int64_t groups, int64_t n_ct) { return (groups + kXcds - 1) / kXcds * kXcds * n_ct; }
 // out[p][e] = sum over s < splits of part[s][p][e] mod m[p], p < planes, e < n; residues of `bytes` (1, 2 or 8) each
 struct AddPartsArgs {
   int planes, splits, mods;                    // plane p is mod m[p % mods]
@@ -497,13 +505,13 @@ struct BatchDesc {
   uint8_t* res;                   // RNS form: [nz][n_mod][d3][R_out] residues by small modulus
   int64_t n_db, row0, R_out, d3;  // output row r < n_db: database row r; r >= n_db: n_db + row0 + (r - n_db)
   int64_t d3_pad;                 // columns of the query planes Xd points into (their row stride)
-  int64_t tile_begin;             // first tile of this problem in the launch (multiple of 8)
-  int32_t nz, pad_;
+  int64_t tile_begin;             // first tile slot of this problem in the launch (multiple of 8)
+  int32_t nz, rot;                // rot: the XCD of its first tile
   int32_t slot[kMaxPrimes];       // database prime slot of each z
   Mod mod[kMaxPrimes];
 };
 struct BatchHeader {
-  int64_t total_tiles;            // multiple of kXcds
+  int64_t total_tiles;            // tile slots, multiple of kXcds
   int32_t n, pad_;
   uint32_t next[kXcds];           // tiles claimed per XCD; zero in every uploaded table
   // RNS and n^2 forms: problems [0, n_wide) use 256-column query tiles (tiles [0, tiles_wide)),
@@ -519,7 +527,7 @@ struct BatchGemmArgs {
   const int8_t* Dd;               // database digits, all slots
   int64_t KB, R_pad;
 };
-int64_t i8_batched_tiles(int variant, int64_t d3, int64_t R_out, int nz);
+int64_t i8_batched_tiles(int variant, int64_t d3, int64_t R_out, int nz, int64_t* groups);
 
 
 hipError_t launch_gemm_i8_batched(const BatchGemmArgs& a, int variant, int grid, hipStream_t s);

@@ -128,16 +128,6 @@ struct I8Tile {
   int64_t nk;         // K-blocks of the tile, from the first of Xd and Dd
 };
 
-// Tile index within one prime of a problem -> (row tile, column tile), XCD-aware: tile index l
-// runs on XCD l % 8 when the launch grid is a multiple of 8 and the problem starts at a
-// multiple of 8.  Returns false for the padding tiles (row tile beyond the last one).
-__device__ __forceinline__ bool tile_coords(int64_t l, int64_t n_rt, int64_t n_ct, int64_t& rt, int64_t& ct) {
-  const int64_t xcd = l % kXcds, j = l / kXcds;
-  rt = (j / n_ct) * kXcds + xcd;
-  ct = j % n_ct;
-  return rt < n_rt;
-}
-
 __device__ __forceinline__ void store_tile(const I8Tile& T, const v16i* acc, int wq, int wr, int lane, bool accumulate) {
   // 32x32 MFMA result layout: lane l, element j holds row (M = query) 8 (j / 4) + 4 (l / 32)
   // + j % 4 and column (N = database row) l % 32.
@@ -557,7 +547,6 @@ __device__ __forceinline__ void tile_dma_split(const I8Tile& T, int8_t* lds) {
   }
 }
 
-// Grid launch: blockIdx.z = prime slot, blockIdx.x = XCD-ordered tile.
 template <int WR, int WQ, int NBUF, int WPE, int MODE>
 constexpr int lds_bytes() {
   if constexpr (MODE == 3) return kDigits * (2 * 32 * WQ + 3 * 32 * WR) * kDmaRow;  // 2 query + 3 database stages
@@ -581,11 +570,12 @@ __global__ void __launch_bounds__(64 * WR * WQ) __attribute__((amdgpu_waves_per_
 k_gemm_i8(GemmArgs g) {
   constexpr int BR = 32 * WR, BQ = 32 * WQ;
   __shared__ __attribute__((aligned(16))) int8_t lds[lds_bytes<WR, WQ, NBUF, WPE, MODE>()];
-  const int z = blockIdx.z;
   const int64_t n_ct = (g.d3 + BQ - 1) / BQ, n_rt = (g.R_out + BR - 1) / BR;
-  int64_t rt, ct;
-  if (!tile_coords(blockIdx.x, n_rt, n_ct, rt, ct)) return;
-  const int sp = blockIdx.y, ns = gridDim.y;  // part sp of the K-blocks
+  const int ns = g.splits;
+  TileAt at;
+  if (!xcd_tile(ns * g.nz, n_rt, n_ct, at)) return;
+  const int64_t ct = at.ct, rt = at.rt;
+  const int z = uniform(at.plane / ns), sp = at.plane - z * ns;  // part sp of the K-blocks, prime slot z
   const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;
   I8Tile T{g.Xd[z] + (size_t)k0 * g.d3_pad * kKB, g.Dd[z] + (size_t)k0 * g.R_pad * kKB,
            ns > 1 ? g.part + ((size_t)sp * g.nz + z) * g.d3 * g.R_out : g.C[z], g.mod[z], g.KB, g.R_pad, g.d3_pad,
@@ -593,9 +583,8 @@ k_gemm_i8(GemmArgs g) {
   run_tile<WR, WQ, NBUF, WPE, MODE>(T, lds);
 }
 
-// Persistent grouped launch over a table of problems (batched CCMM): workgroup w processes
-// tiles w, w + G, w + 2G, ... of the concatenated tile list (G = grid size, a multiple of 8,
-// and every problem starts at a multiple of 8, so tile t always runs on XCD t % 8).
+// Persistent grouped launch over a table of problems (batched CCMM): the workgroups of an XCD claim its tiles of the
+// concatenated list (problem, prime, row tile, column tile) in order; slot t is XCD t mod 8's.
 template <int WR, int WQ, int NBUF, int WPE, int MODE>
 __global__ void __launch_bounds__(64 * WR * WQ) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 k_gemm_i8_batched(BatchGemmArgs a) {
@@ -605,8 +594,7 @@ k_gemm_i8_batched(BatchGemmArgs a) {
   const int n = a.hdr->n;
   // Tiles are claimed in order from one counter per XCD (workgroup b runs on XCD b mod 8), so
   // the workgroups of an XCD always work on a contiguous window of tiles that share database
-  // and query blocks in L2, however unevenly tiles finish; tile t = 8 j + xcd.  The claim is
-  // passed to the workgroup through the first LDS word, which no tile uses between tiles.
+  // and query blocks in L2, however unevenly tiles finish.  The claim is passed to the workgroup through the first LDS word, which no tile uses between tiles.
   const int xcd = blockIdx.x % kXcds;
   const int64_t per_xcd = a.hdr->total_tiles / kXcds;
   for (;;) {
@@ -626,11 +614,10 @@ k_gemm_i8_batched(BatchGemmArgs a) {
     }
     const BatchDesc& d = a.desc[lo];
     const int64_t n_ct = (d.d3 + BQ - 1) / BQ, n_rt = (d.R_out + BR - 1) / BR;
-    const int64_t per_prime = (n_rt + kXcds - 1) / kXcds * kXcds * n_ct;
-    const int64_t local = t - d.tile_begin;
-    const int z = (int)(local / per_prime);
-    int64_t rt, ct;
-    if (!tile_coords(local % per_prime, n_rt, n_ct, rt, ct)) continue;
+    TileAt at;
+    if (!batch_tile(t - d.tile_begin, d.nz, n_rt, n_ct, d.rot, at)) continue;
+    const int64_t ct = at.ct, rt = at.rt;
+    const int z = at.plane;
     const size_t planeX = (size_t)a.KB * d.d3_pad * kKB * kDigits;
     const size_t planeD = (size_t)a.KB * a.R_pad * kKB * kDigits;
     I8Tile T{d.Xd + z * planeX, a.Dd + d.slot[z] * planeD, d.C + (size_t)z * d.d3 * d.R_out, d.mod[z], a.KB,
@@ -678,11 +665,8 @@ hipError_t launch_gemm_i8(const GemmArgs& g, int variant, hipStream_t s) {
   const I8Variant& v = kI8Variants[variant];
   if (g.d3_pad % v.bq != 0) return hipErrorInvalidValue;  // query padding must cover the tile
   const int64_t n_ct = (g.d3 + v.bq - 1) / v.bq, n_rt = (g.R_out + v.br - 1) / v.br;
-  const int64_t n_rt8 = (n_rt + kXcds - 1) / kXcds * kXcds;
-  const int ns = g.splits > 1 ? g.splits : 1;
-  if (ns > g.KB || (ns > 1 && !g.part)) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)ns, (unsigned)g.nz);
-  hipLaunchKernelGGL(v.grid, grid, dim3(v.threads), 0, s, g);
+  if (g.splits < 1 || g.splits > g.KB || (g.splits > 1 && !g.part)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(v.grid, xcd_grid(n_rt * g.splits * g.nz, n_ct), dim3(v.threads), 0, s, g);
   return hipGetLastError();
 }
 
@@ -726,10 +710,11 @@ hipError_t launch_add_parts(const AddPartsArgs& a, int bytes, const void* part, 
   return hipGetLastError();
 }
 
-int64_t i8_batched_tiles(int variant, int64_t d3, int64_t R_out, int nz) {
+int64_t i8_batched_tiles(int variant, int64_t d3, int64_t R_out, int nz, int64_t* groups) {
   const I8Variant& v = kI8Variants[variant];
   const int64_t n_ct = (d3 + v.bq - 1) / v.bq, n_rt = (R_out + v.br - 1) / v.br;
-  return (n_rt + kXcds - 1) / kXcds * kXcds * n_ct * nz;
+  *groups = n_rt * nz;
+  return batch_slots(*groups, n_ct);
 }
 
 hipError_t launch_gemm_i8_batched(const BatchGemmArgs& a, int variant, int grid, hipStream_t s) {

@@ -261,20 +261,21 @@ __global__ void __launch_bounds__(64 * P2Cfg<TQ>::NW) __attribute__((amdgpu_wave
 k_gemm_p2(P2GemmArgs g) {
   using C = P2Cfg<TQ>;
   __shared__ __attribute__((aligned(16))) int8_t lds[C::LDS];
-  const int j = blockIdx.y % g.n_bases, sp = blockIdx.y / g.n_bases, ns = gridDim.y / g.n_bases, z = blockIdx.z;
-  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;  // part sp of the K-blocks
   const int64_t n_ct = (g.d3 + C::TQ - 1) / C::TQ, n_rt = (g.R_out + C::TR - 1) / C::TR;
-  const int64_t l = blockIdx.x, xcd = l % kXcds, jj = l / kXcds;
-  const int64_t rt = (jj / n_ct) * kXcds + xcd, ct = jj % n_ct;
-  if (rt >= n_rt) return;
+  const int ns = g.splits;
+  TileAt at;
+  if (!xcd_tile(g.n_bases * ns * g.nz, n_rt, n_ct, at)) return;
+  const int64_t ct = at.ct, rt = at.rt;
+  const int zs = uniform(at.plane / g.n_bases), j = at.plane - zs * g.n_bases, z = uniform((uint32_t)zs / ns), sp = zs - z * ns;
+  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;  // part sp of the K-blocks
   P2Tile t{g.Xq[z] + ((size_t)(2 * j) * g.KB + k0) * g.d3_pad * kKB, g.Dq[z] + ((size_t)(2 * j) * g.KB + k0) * g.R_pad * kKB,
            g.res + (((size_t)sp * g.nz + z) * g.n_bases + j) * g.d3 * g.R_out, j, g.n[j], g.m[j], g.rn[j], g.rm[j], g.KB, g.R_pad,
            g.d3_pad, g.n_db, g.row0, g.R_out, g.d3, rt * C::TR, ct * C::TQ, k1 - k0};
   p2_tile<TQ>(t, lds);
 }
 
-// Persistent batched form: problem b's tiles are ordered (z, base, XCD-ordered tile), starting at its
-// tile_begin; workgroups claim tiles in order from one counter per XCD (tile t = 8 i + xcd), as the
+// Persistent batched form: problem b's tiles are ordered (z, base, row tile, column tile), starting at its
+// tile_begin; workgroups claim tiles in order from one counter per XCD, slot t from XCD t mod 8's, as the
 // digit form's batched kernel.  The 256-column launch serves problems [0, n_wide) (tiles
 // [0, tiles_wide), counters next), the 128-column launch the others (counters next_narrow).
 template <int TQ>
@@ -303,13 +304,10 @@ k_gemm_p2_batched(P2BatchArgs a) {
     }
     const BatchDesc& d = a.desc[lo];
     const int64_t n_ct = (d.d3 + C::TQ - 1) / C::TQ, n_rt = (d.R_out + C::TR - 1) / C::TR;
-    const int64_t per_base = (n_rt + kXcds - 1) / kXcds * kXcds * n_ct;
-    const int64_t local = t - d.tile_begin;
-    const int zj = (int)(local / per_base);
-    const int z = zj / a.n_bases, j = zj % a.n_bases;
-    const int64_t l = local % per_base, lj = l / kXcds;
-    const int64_t rt = (lj / n_ct) * kXcds + l % kXcds, ct = lj % n_ct;
-    if (rt >= n_rt) continue;
+    TileAt at;
+    if (!batch_tile(t - d.tile_begin, a.n_bases * d.nz, n_rt, n_ct, d.rot, at)) continue;
+    const int64_t ct = at.ct, rt = at.rt;
+    const int z = uniform(at.plane / a.n_bases), j = at.plane - z * a.n_bases;
     P2Tile tl{d.Xd + (size_t)(z * a.n_bases + j) * 2 * a.KB * d.d3_pad * kKB,
               a.Dq + (size_t)(d.slot[z] * a.n_bases + j) * 2 * a.KB * a.R_pad * kKB,
               reinterpret_cast<uint16_t*>(d.res) + ((size_t)z * a.n_bases + j) * d.d3 * d.R_out, j, kP2C.n[j],
@@ -321,10 +319,11 @@ k_gemm_p2_batched(P2BatchArgs a) {
 
 static int64_t p2_rows_of(int tq) { return 128 * 256 / tq; }
 
-int64_t p2_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_bases, int tq) {
+int64_t p2_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_bases, int tq, int64_t* groups) {
   const int64_t tr = p2_rows_of(tq);
   const int64_t n_ct = (d3 + tq - 1) / tq, n_rt = (R_out + tr - 1) / tr;
-  return (n_rt + kXcds - 1) / kXcds * kXcds * n_ct * nz * n_bases;
+  *groups = n_rt * nz * n_bases;
+  return batch_slots(*groups, n_ct);
 }
 
 // Query tile of the n^2 contraction for a set of problems: the width with less padded work (rows
@@ -359,10 +358,8 @@ hipError_t launch_gemm_p2(const P2GemmArgs& g, int tq, hipStream_t s) {
     return hipErrorInvalidValue;
   const int64_t tr = p2_rows_of(tq);
   const int64_t n_ct = (g.d3 + tq - 1) / tq, n_rt = (g.R_out + tr - 1) / tr;
-  const int64_t n_rt8 = (n_rt + kXcds - 1) / kXcds * kXcds;
-  const int ns = g.splits > 1 ? g.splits : 1;
-  if (ns > g.KB) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)(g.n_bases * ns), (unsigned)g.nz);
+  if (g.splits < 1 || g.splits > g.KB) return hipErrorInvalidValue;
+  const dim3 grid = xcd_grid(n_rt * g.n_bases * g.splits * g.nz, n_ct);
   if (tq == 128)
     hipLaunchKernelGGL(k_gemm_p2<128>, grid, dim3(64 * P2Cfg<128>::NW), 0, s, g);
   else

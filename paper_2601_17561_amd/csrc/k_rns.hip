@@ -239,20 +239,21 @@ __global__ void __launch_bounds__(64 * RnsCfg<TQ>::NW) __attribute__((amdgpu_wav
 k_gemm_rns(RnsGemmArgs g) {
   using C = RnsCfg<TQ>;
   __shared__ __attribute__((aligned(16))) int8_t lds[C::LDS];
-  const int j = blockIdx.y % g.n_mod, sp = blockIdx.y / g.n_mod, ns = gridDim.y / g.n_mod, z = blockIdx.z;
-  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;  // part sp of the K-blocks
   const int64_t n_ct = (g.d3 + TQ - 1) / TQ, n_rt = (g.R_out + C::TR - 1) / C::TR;
-  const int64_t l = blockIdx.x, xcd = l % kXcds, jj = l / kXcds;
-  const int64_t rt = (jj / n_ct) * kXcds + xcd, ct = jj % n_ct;
-  if (rt >= n_rt) return;
+  const int ns = g.splits;
+  TileAt at;
+  if (!xcd_tile(g.n_mod * ns * g.nz, n_rt, n_ct, at)) return;
+  const int64_t ct = at.ct, rt = at.rt;
+  const int zs = uniform(at.plane / g.n_mod), j = at.plane - zs * g.n_mod, z = uniform((uint32_t)zs / ns), sp = zs - z * ns;
+  const int64_t k0 = g.KB * sp / ns, k1 = g.KB * (sp + 1) / ns;  // part sp of the K-blocks
   RnsTile t{g.Xr[z] + ((size_t)j * g.KB + k0) * g.d3_pad * kKB, g.Dr[z] + ((size_t)j * g.KB + k0) * g.R_pad * kKB,
             g.res + (((size_t)sp * g.nz + z) * g.n_mod + j) * g.d3 * g.R_out, g.m[j], g.magic[j], k1 - k0, g.R_pad, g.d3_pad, g.n_db,
             g.row0, g.R_out, g.d3, rt * C::TR, ct * TQ};
   rns_tile<TQ>(t, lds);
 }
 
-// Persistent batched form: problem b's tiles are ordered (z, modulus, XCD-ordered tile), starting at
-// its tile_begin; workgroups claim tiles in order from one counter per XCD (tile t = 8 j + xcd), as
+// Persistent batched form: problem b's tiles are ordered (z, modulus, row tile, column tile), starting at
+// its tile_begin; workgroups claim tiles in order from one counter per XCD, slot t from XCD t mod 8's, as
 // the digit form's batched kernel.
 template <int TQ>
 __global__ void __launch_bounds__(64 * RnsCfg<TQ>::NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -281,13 +282,10 @@ k_gemm_rns_batched(RnsBatchArgs a) {
     }
     const BatchDesc& d = a.desc[lo];
     const int64_t n_ct = (d.d3 + TQ - 1) / TQ, n_rt = (d.R_out + C::TR - 1) / C::TR;
-    const int64_t per_mod = (n_rt + kXcds - 1) / kXcds * kXcds * n_ct;
-    const int64_t local = t - d.tile_begin;
-    const int zj = (int)(local / per_mod);
-    const int z = zj / a.n_mod, j = zj % a.n_mod;
-    const int64_t l = local % per_mod, lj = l / kXcds;
-    const int64_t rt = (lj / n_ct) * kXcds + l % kXcds, ct = lj % n_ct;
-    if (rt >= n_rt) continue;
+    TileAt at;
+    if (!batch_tile(t - d.tile_begin, a.n_mod * d.nz, n_rt, n_ct, d.rot, at)) continue;
+    const int64_t ct = at.ct, rt = at.rt;
+    const int z = uniform(at.plane / a.n_mod), j = at.plane - z * a.n_mod;
     RnsTile tl{d.Xd + ((size_t)z * a.n_mod + j) * a.KB * d.d3_pad * kKB,
                a.Dr + ((size_t)d.slot[z] * a.n_mod + j) * a.KB * a.R_pad * kKB,
                d.res + ((size_t)z * a.n_mod + j) * d.d3 * d.R_out, a.m[j], a.magic[j], a.KB, a.R_pad, d.d3_pad,
@@ -296,9 +294,10 @@ k_gemm_rns_batched(RnsBatchArgs a) {
   }
 }
 
-int64_t rns_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_mod, int tq) {
+int64_t rns_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_mod, int tq, int64_t* groups) {
   const int64_t n_ct = (d3 + tq - 1) / tq, n_rt = (R_out + kRnsTileR - 1) / kRnsTileR;
-  return (n_rt + kXcds - 1) / kXcds * kXcds * n_ct * nz * n_mod;
+  *groups = n_rt * nz * n_mod;
+  return batch_slots(*groups, n_ct);
 }
 
 hipError_t launch_gemm_rns_batched(const RnsBatchArgs& a, int grid, int tq, hipStream_t s) {
@@ -341,10 +340,8 @@ hipError_t launch_gemm_rns(const RnsGemmArgs& g, int tq, hipStream_t s) {
   if (g.R_out <= 0 || g.d3 <= 0) return hipSuccess;
   if ((tq != 128 && tq != 256) || g.d3_pad % tq != 0) return hipErrorInvalidValue;
   const int64_t n_ct = (g.d3 + tq - 1) / tq, n_rt = (g.R_out + kRnsTileR - 1) / kRnsTileR;
-  const int64_t n_rt8 = (n_rt + kXcds - 1) / kXcds * kXcds;
-  const int ns = g.splits > 1 ? g.splits : 1;
-  if (ns > g.KB) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(n_rt8 * n_ct), (unsigned)(g.n_mod * ns), (unsigned)g.nz);
+  if (g.splits < 1 || g.splits > g.KB) return hipErrorInvalidValue;
+  const dim3 grid = xcd_grid(n_rt * g.n_mod * g.splits * g.nz, n_ct);
   if (tq == 128)
     hipLaunchKernelGGL(k_gemm_rns<128>, grid, dim3(64 * RnsCfg<128>::NW), 0, s, g);
   else
