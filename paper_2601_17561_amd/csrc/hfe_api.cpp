@@ -6,6 +6,7 @@
 #include <map>
 #include <atomic>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <string>
@@ -1413,9 +1414,10 @@ FormShape hfe::form_shape(const hfe_db* D, int form) {
 namespace {
 // Byte layout of the descriptor tables of a batch of up to `items` items and `problems` problems
 // (256-byte aligned parts): contraction (per problem), lift (per item), rescale (per item), RNS
-// reconstruction (per problem).
+// reconstruction (per problem), RNS contraction (jobs and their segments).
 struct BlobLayout {
-  size_t gh, gd, lh, ld, rh, rd, ch, cd, bytes;
+  size_t gh, gd, lh, ld, rh, rd, ch, cd, jd, sd, bytes;
+  int max_jobs, max_segs;  // RNS form: at least what any batch needs request by request
   BlobLayout(int items, int problems) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     gh = 0;
@@ -1426,7 +1428,11 @@ struct BlobLayout {
     rd = al(rh + sizeof(BatchElemHeader));
     ch = al(rd + sizeof(BatchRescaleDesc) * items);
     cd = al(ch + sizeof(BatchElemHeader));
-    bytes = al(cd + sizeof(BatchCrtDesc) * problems);
+    max_jobs = kMaxPrimes * 4 * (items + 1);
+    max_segs = 10 * (items + problems);
+    jd = al(cd + sizeof(BatchCrtDesc) * problems);
+    sd = al(jd + sizeof(RnsJob) * max_jobs);
+    bytes = al(sd + sizeof(RnsSeg) * max_segs);
   }
 };
 // problems of a batch of n items: at most one more per level than items (see group_items)
@@ -1535,6 +1541,157 @@ Grouping group_items(const hfe_batch_item* items, int n) {
   return g;
 }
 
+// The RNS contraction's jobs: runs of database rows, each with the problems whose rows they hold.  The A rows are one
+// job of every problem that includes them, whatever its level.  The B rows are cut where the set of problems on a tile
+// of kRnsTileR rows changes, so that rows several problems share are read once and their columns padded once; or each
+// problem keeps a job of its own where that is less work, as with many short ranges that share only a tile's padding.
+// Work: padded rows times padded columns, the narrow tile's 128 counting as 180, since with so few columns it takes the
+// time of reading its rows (16 columns, 30,720 rows: 4.97 ms; 512: 14.2).  Segments come by falling level, so that those
+// of a prime slot are the first of each job.
+struct RowRun {
+  int64_t db_row = 0, rows = 0;
+  struct Part {
+    int p;                // problem
+    int64_t lo, hi, out;  // its rows of the run; its output row of the run's row 0
+  };
+  std::vector<Part> parts;
+};
+
+std::vector<RowRun> rns_runs(const Grouping& gr, int64_t ndb, int64_t d1, bool shared) {
+  std::vector<int> ord(gr.p.size());
+  for (size_t b = 0; b < ord.size(); ++b) ord[b] = (int)b;
+  std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return gr.p[x].level > gr.p[y].level; });
+  std::vector<RowRun> out(1);
+  out[0].rows = ndb;
+  for (int b : ord)
+    if (gr.p[b].a_rows) out[0].parts.push_back({b, 0, ndb, 0});
+  auto add = [&](int64_t lo, int64_t hi, const std::vector<int>& on) {
+    if (on.empty()) return;
+    RowRun r;
+    r.db_row = ndb + lo;
+    r.rows = hi - lo;
+    for (int b : on) {
+      const Problem& P = gr.p[b];
+      r.parts.push_back({b, std::max(P.row0, lo) - lo, std::min(P.row0 + P.rows, hi) - lo,
+                         (P.a_rows ? ndb : 0) + lo - P.row0});
+    }
+    out.push_back(std::move(r));
+  };
+  if (!shared) {
+    for (int b : ord)
+      if (gr.p[b].rows > 0) add(gr.p[b].row0, gr.p[b].row0 + gr.p[b].rows, {b});
+    return out;
+  }
+  std::vector<int64_t> cut;  // tiles at which the set of problems may change
+  for (const Problem& P : gr.p)
+    if (P.rows > 0) {
+      cut.push_back(P.row0 / kRnsTileR);
+      cut.push_back((P.row0 + P.rows + kRnsTileR - 1) / kRnsTileR);
+    }
+  std::sort(cut.begin(), cut.end());
+  cut.erase(std::unique(cut.begin(), cut.end()), cut.end());
+  for (size_t c = 0; c + 1 < cut.size(); ++c) {
+    const int64_t lo = cut[c] * kRnsTileR, hi = std::min(cut[c + 1] * kRnsTileR, d1);
+    std::vector<int> on;
+    for (int b : ord)
+      if (gr.p[b].rows > 0 && gr.p[b].row0 < hi && gr.p[b].row0 + gr.p[b].rows > lo) on.push_back(b);
+    add(lo, hi, on);
+  }
+  return out;
+}
+
+// A run in one prime slot: the parts on it (the first of the run's, whose level reaches the slot) and their columns.
+struct RunSlot {
+  int n_parts = 0;
+  int64_t cols = 0;
+  RunSlot(const Grouping& gr, const RowRun& r, int slot, bool p_slot) {
+    for (const auto& part : r.parts) {
+      if (!p_slot && gr.p[part.p].level <= slot) break;
+      ++n_parts;
+      cols += gr.p[part.p].d3;
+    }
+  }
+  // the columns of its tiles of width tq: whole 256-column tiles, and a rest of up to 128 in a narrow one
+  int64_t cols_in(int tq) const {
+    const int64_t rest = cols % kRnsTileQ, narrow = rest <= 128 ? rest : 0;
+    return tq == 128 ? narrow : cols - narrow;
+  }
+};
+
+// Jobs and segments of a batch into the tables at blob; the tile slots of the 256-column jobs, and of all.
+void fill_rns_jobs(const hfe_db* D, const Grouping& gr, int max_level, const std::function<RnsSeg(int)>& seg_of,
+                   uint8_t* blob, const BlobLayout& L, BatchHeader* gh) {
+  const int64_t ndb = 1ll << D->keys->P.log_n_db;
+  std::vector<RowRun> best;
+  double best_cost = 0;
+  for (int shared = 0; shared < 2; ++shared) {
+    std::vector<RowRun> runs = rns_runs(gr, ndb, D->d1, shared != 0);
+    double cost = 0;
+    int64_t jobs = 0, segs = 0;
+    for (const RowRun& r : runs) {
+      segs += (int64_t)r.parts.size();
+      for (int slot = 0; slot <= max_level; ++slot) {
+        const RunSlot rs(gr, r, slot, slot == max_level);
+        if (!rs.n_parts) continue;
+        const int64_t wide = (rs.cols_in(256) + kRnsTileQ - 1) / kRnsTileQ, narrow = rs.cols_in(128) > 0;
+        jobs += (wide > 0) + narrow;
+        cost += (double)((r.rows + kRnsTileR - 1) / kRnsTileR) * (256.0 * wide + 180.0 * narrow);
+      }
+    }
+    if (jobs > L.max_jobs || segs > L.max_segs) continue;  // request by request always fits
+    if (best.empty() || cost < best_cost) {
+      best = std::move(runs);
+      best_cost = cost;
+    }
+  }
+  RnsJob* jobs = reinterpret_cast<RnsJob*>(blob + L.jd);
+  RnsSeg* segs = reinterpret_cast<RnsSeg*>(blob + L.sd);
+  std::vector<int> seg0;
+  int n_seg = 0;
+  for (const RowRun& r : best) {
+    seg0.push_back(n_seg);
+    for (const auto& part : r.parts) {
+      RnsSeg g = seg_of(part.p);
+      g.res += part.out;
+      g.lo = (int32_t)part.lo;
+      g.hi = (int32_t)part.hi;
+      segs[n_seg++] = g;
+    }
+  }
+  int n = 0, rot = 0;
+  int64_t tiles = 0;
+  for (const int tq : {256, 128}) {
+    for (int slot = 0; slot <= max_level; ++slot)
+      for (size_t i = 0; i < best.size(); ++i) {
+        const RowRun& r = best[i];
+        const RunSlot rs(gr, r, slot, slot == max_level);
+        const int64_t cols = rs.cols_in(tq);
+        if (!cols) continue;
+        RnsJob& d = jobs[n++];
+        std::memset(&d, 0, sizeof(d));
+        d.tile_begin = tiles;
+        d.db_row = r.db_row;
+        d.rows = r.rows;
+        d.cols = cols;
+        d.col0 = tq == 128 ? rs.cols - cols : 0;
+        d.n_slot_p = slot == max_level;
+        d.slot = d.n_slot_p ? D->keys->L : slot;
+        d.seg = seg0[i];
+        d.n_seg = rs.n_parts;
+        d.rot = rot;
+        int64_t groups = 0;
+        tiles += rns_batched_tiles(cols, r.rows, D->n_rns, tq, &groups);
+        rot = (int)((rot + groups) % kXcds);
+      }
+    if (tq == 256) {
+      gh->tiles_wide = tiles;
+      gh->n_wide = n;
+    }
+  }
+  gh->total_tiles = tiles;
+  gh->n = n;
+}
+
 // Sizes of a batch for a form (HFE_FORM_I8_MFMA with the digit tile `variant`, HFE_FORM_RNS_I8 or
 // HFE_FORM_P2_I8),
 // and (when blob != nullptr) its descriptor tables pointing into the given workspace (xd_base,
@@ -1558,16 +1715,15 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
   for (int b = 0; b < np; ++b)
     if (gr.p[b].owner != b) feeds[gr.p[b].owner] = 1;
   for (int b = 0; b < np; ++b) R_out[b] = (gr.p[b].a_rows ? ndb : 0) + gr.p[b].rows;
-  // RNS and n^2 forms: each problem's query tile width by its own padded work; the 256-column problems come
+  // n^2 form: each problem's query tile width by its own padded work; the 256-column problems come
   // first in the tables (one launch each width).  Owners' planes are padded for the widest tiles.
   std::vector<int> tq(np, 0), ord(np);
   for (int b = 0; b < np; ++b) {
     ord[b] = b;
     const int nzb = gr.p[b].level + 1;
-    if (rns) tq[b] = rns_tile_q(&gr.p[b].d3, &R_out[b], &nzb, 1);
     if (fs.p2) tq[b] = p2_tile_q(&gr.p[b].d3, &R_out[b], &nzb, 1);
   }
-  if (small) std::stable_partition(ord.begin(), ord.end(), [&](int b) { return tq[b] == 256; });
+  if (fs.p2) std::stable_partition(ord.begin(), ord.end(), [&](int b) { return tq[b] == 256; });
   // query planes of the owners: whole tiles, and for an owner that feeds split problems room for
   // their last tile, which may reach qpad - 1 columns past the owner's columns
   for (int b = 0; b < np; ++b) {
@@ -1618,11 +1774,11 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
       }
     }
     int64_t groups = 0;
-    tiles += rns      ? rns_batched_tiles(d3, R_out[b], nz, planes, tq[b], &groups)
+    tiles += rns     ? 0  // its jobs' are counted below
              : fs.p2 ? p2_batched_tiles(d3, R_out[b], nz, D->n_p2, tq[b], &groups)
                      : i8_batched_tiles(variant, d3, R_out[b], nz, &groups);
     rot = (int)((rot + groups) % kXcds);
-    if (small && tq[b] == 256) {
+    if (fs.p2 && tq[b] == 256) {
       tiles_wide = tiles;
       n_wide = k + 1;
     }
@@ -1686,8 +1842,20 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
     BatchHeader* gh = reinterpret_cast<BatchHeader*>(blob + L.gh);
     gh->total_tiles = tiles;
     gh->n = np;
-    gh->tiles_wide = small ? tiles_wide : tiles;
-    gh->n_wide = small ? n_wide : np;
+    gh->tiles_wide = fs.p2 ? tiles_wide : tiles;
+    gh->n_wide = fs.p2 ? n_wide : np;
+    if (rns)
+      fill_rns_jobs(D, gr, z.max_level, [&](int b) {
+        RnsSeg g;
+        std::memset(&g, 0, sizeof(g));
+        g.X = xd_base + xd_off[gr.p[b].owner] + gr.p[b].xc0 * kKB;
+        g.res = res_base + res_off[b];
+        g.d3_pad = d3_pad[gr.p[b].owner];
+        g.R_out = R_out[b];
+        g.cols = (int32_t)gr.p[b].d3;
+        g.level = gr.p[b].level;
+        return g;
+      }, blob, L, gh);
     BatchElemHeader* lh = reinterpret_cast<BatchElemHeader*>(blob + L.lh);
     lh->total = lift_e;
     lh->n = n;
@@ -1723,7 +1891,8 @@ hfe_status batch_enqueue(const hfe_db* D, const uint8_t* dblob, const BlobLayout
     a.hdr = hdr;
     a.next = const_cast<uint32_t*>(hdr->next);
     a.next_narrow = const_cast<uint32_t*>(hdr->next_narrow);
-    a.desc = reinterpret_cast<const BatchDesc*>(dblob + L.gd);
+    a.job = reinterpret_cast<const RnsJob*>(dblob + L.jd);
+    a.seg = reinterpret_cast<const RnsSeg*>(dblob + L.sd);
     a.Dr = D->rns.as<int8_t>();
     a.n_mod = D->n_rns;
     for (int j = 0; j < D->n_rns; ++j) {
@@ -1732,7 +1901,7 @@ hfe_status batch_enqueue(const hfe_db* D, const uint8_t* dblob, const BlobLayout
     }
     a.KB = D->KB;
     a.R_pad = D->R_pad;
-    // the 256-column problems, then the 128-column ones (either launch may find no tiles)
+    // the 256-column jobs, then the 128-column ones (either launch may find no tiles)
     HFE_LAUNCH(launch_gemm_rns_batched(a, gemm_grid_for(form, 256), 256, s));
     HFE_LAUNCH(launch_gemm_rns_batched(a, gemm_grid_for(form, 128), 128, s));
     // by-slot constants: level L makes z index the database slot

@@ -411,21 +411,38 @@ struct BatchDesc;
 struct BatchHeader;
 struct BatchElemHeader;
 struct BatchCrtDesc;
-// Batched RNS contraction: problem b's tiles are [tile_begin, tile_begin + rns_batched_tiles(...)),
-// ordered (z, modulus, row tile, column tile); workgroups claim tiles per XCD as the digit form's.  The
-// launch with tq = 256 serves problems [0, hdr->n_wide), the one with tq = 128 the others.
+// Batched RNS contraction.  A job is a run of database rows in one prime slot, multiplied by the columns of every
+// problem that covers them there, side by side; its segments say whose columns those are.  So rows that several
+// requests share are read once, and the columns are padded to whole tiles once.
+struct RnsSeg {                                // columns of one problem
+  const int8_t* X;                             // [z][modulus][KB][d3_pad][64], at the first of them
+  uint8_t* res;                                // [z][modulus][cols][R_out], their entry of the job's row 0
+  int64_t d3_pad, R_out;
+  int32_t cols, level;                         // level: the problem's z of slot p
+  int32_t lo, hi;                              // rows of the job that are the problem's
+};
+struct RnsJob {
+  int64_t tile_begin;                          // first tile slot in the launch (multiple of 8)
+  int64_t db_row;                              // database row of row 0
+  int64_t rows, cols, col0;                    // its columns: [col0, col0 + cols) of the segments'
+  int32_t slot, n_slot_p;                      // database slot; whether it is p's (then z is the segment's level)
+  int32_t seg, n_seg, rot, pad_;               // segments [seg, seg + n_seg); the XCD of the first tile
+};
+// Jobs [0, hdr->n_wide) are the 256-column launch's, the rest the 128-column one's; tiles are ordered (modulus, row
+// tile, column tile), claimed per XCD as the digit form's.
 struct RnsBatchArgs {
   const BatchHeader* hdr;
   uint32_t* next;                              // hdr->next (256-column tiles)
   uint32_t* next_narrow;                       // hdr->next_narrow (128-column tiles)
-  const BatchDesc* desc;
+  const RnsJob* job;
+  const RnsSeg* seg;
   const int8_t* Dr;                            // database planes, all slots: [slot][n_mod][KB][R_pad][64]
   int32_t n_mod, pad_;
   int32_t m[kRnsMaxMods];
   uint32_t magic[kRnsMaxMods];
   int64_t KB, R_pad;
 };
-int64_t rns_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_mod, int tq, int64_t* groups);
+int64_t rns_batched_tiles(int64_t cols, int64_t rows, int n_mod, int tq, int64_t* groups);
 hipError_t launch_gemm_rns_batched(const RnsBatchArgs& a, int grid, int tq, hipStream_t s);
 // Batched n^2 contraction: problem b's tiles are [tile_begin, tile_begin + p2_batched_tiles(...)),
 // ordered (z, base, row tile, column tile); the launch with tq = 256 serves problems [0, hdr->n_wide)

@@ -114,8 +114,17 @@ __device__ __forceinline__ void rns_wait_block() {
     asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int TQ>
-__device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds) {
+// A query column of a job's tile: its planes, its results' entry of the job's row 0, and the rows that are its own.
+struct RnsCol {
+  const int8_t* X;
+  uint8_t* res;
+  int32_t lo, hi;
+  int64_t step;  // bytes between its K-blocks
+};
+
+// JOB: the tile is of a job's rows (g.D and g.r0, g.R_out) and its columns are `col`; otherwise of one problem.
+template <int TQ, bool JOB>
+__device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds, const RnsCol* col) {
   using C = RnsCfg<TQ>;
   const int64_t r0 = g.r0, c0 = g.c0;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -128,12 +137,18 @@ __device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds) {
   const int ld_row = 16 * wave + (lane >> 2);
   const int ld_chunk = ((lane & 3) ^ ((ld_row >> 2) & 3)) * 16;
   const int8_t* gA[C::LA];
+  size_t colstep[JOB ? C::LA : 1];  // columns of several problems: each its own stride
   const int8_t* gB[C::LB];
 #pragma unroll
-  for (int i = 0; i < C::LA; ++i) gA[i] = X + (size_t)(c0 + ld_row + 16 * C::NW * i) * kKB + ld_chunk;
+  for (int i = 0; i < C::LA; ++i) {
+    const int c = ld_row + 16 * C::NW * i;
+    gA[i] = (JOB ? col[c].X : X + (size_t)(c0 + c) * kKB) + ld_chunk;
+    if constexpr (JOB) colstep[i] = col[c].step;
+  }
 #pragma unroll
   for (int i = 0; i < C::LB; ++i)
-    gB[i] = D + (size_t)src_row(r0 + ld_row + 16 * C::NW * i, g.n_db, g.row0) * kKB + ld_chunk;
+    gB[i] = D + (size_t)(JOB ? r0 + ld_row + 16 * C::NW * i
+                             : src_row(r0 + ld_row + 16 * C::NW * i, g.n_db, g.row0)) * kKB + ld_chunk;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds + wave * 16 * kKB;
   auto issue = [&](int stage) {
     const uint32_t base = lds0 + stage * C::STAGE;
@@ -151,7 +166,7 @@ __device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds) {
     const size_t dA = left > 0 ? stepA : 0, dB = left > 0 ? stepB : 0;
     --left;
 #pragma unroll
-    for (int i = 0; i < C::LA; ++i) gA[i] += dA;
+    for (int i = 0; i < C::LA; ++i) gA[i] += JOB ? (left >= 0 ? colstep[i] : 0) : dA;
 #pragma unroll
     for (int i = 0; i < C::LB; ++i) gB[i] += dB;
   };
@@ -218,6 +233,22 @@ __device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds) {
   const uint32_t m = (uint32_t)g.m;
   const uint32_t magic = g.magic;
   const RnsAccConsts ac = rns_acc_consts(m, magic);  // |acc| < 2^31 -> acc mod m (hfe_exact.h)
+  if constexpr (JOB) {
+#pragma unroll
+    for (int a = 0; a < C::WQB; ++a)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const RnsCol& cc = col[wq * 32 * C::WQB + a * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+        uint8_t* out = cc.res;
+        const int32_t lo = cc.lo, hi = cc.hi;
+#pragma unroll
+        for (int b = 0; b < C::WRB; ++b) {
+          const int64_t r = r0 + wr * 32 * C::WRB + b * 32 + (lane & 31);
+          if (r >= lo && r < hi) out[r] = (uint8_t)rns_acc_mod(acc[a][b][e], m, magic, ac);
+        }
+      }
+    return;
+  }
   uint8_t* res = g.res;
 #pragma unroll
   for (int b = 0; b < C::WRB; ++b) {
@@ -249,18 +280,20 @@ k_gemm_rns(RnsGemmArgs g) {
   RnsTile t{g.Xr[z] + ((size_t)j * g.KB + k0) * g.d3_pad * kKB, g.Dr[z] + ((size_t)j * g.KB + k0) * g.R_pad * kKB,
             g.res + (((size_t)sp * g.nz + z) * g.n_mod + j) * g.d3 * g.R_out, g.m[j], g.magic[j], k1 - k0, g.R_pad, g.d3_pad, g.n_db,
             g.row0, g.R_out, g.d3, rt * C::TR, ct * TQ};
-  rns_tile<TQ>(t, lds);
+  rns_tile<TQ, false>(t, lds, nullptr);
 }
 
-// Persistent batched form: problem b's tiles are ordered (z, modulus, row tile, column tile), starting at
-// its tile_begin; workgroups claim tiles in order from one counter per XCD, slot t from XCD t mod 8's, as
-// the digit form's batched kernel.
+// Persistent batched form: workgroups claim the jobs' tiles in order from one counter per XCD, slot t from XCD t mod
+// 8's, as the digit form's batched kernel.  What bounds it is reading the database planes, which is why requests on the
+// same rows share a job: twelve requests of 16 .. 128 columns on shards of 30,720 rows, K = 20,992 read 133 GB request
+// by request (20.2 + 6.3 ms), 70 GB in shared jobs (3.4 + 14.4 ms).
 template <int TQ>
 __global__ void __launch_bounds__(64 * RnsCfg<TQ>::NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_gemm_rns_batched(RnsBatchArgs a) {
   using C = RnsCfg<TQ>;
   __shared__ __attribute__((aligned(16))) int8_t lds[C::LDS];
-  // this launch's problems and tiles (read on the device, so that a captured graph serves any batch)
+  __shared__ RnsCol col[TQ];
+  // this launch's jobs and tiles (read on the device, so that a captured graph serves any batch)
   constexpr bool narrow = TQ == 128;
   const int p_lo = narrow ? a.hdr->n_wide : 0, p_hi = narrow ? a.hdr->n : a.hdr->n_wide;
   const int64_t t_lo = narrow ? a.hdr->tiles_wide : 0, t_hi = narrow ? a.hdr->total_tiles : a.hdr->tiles_wide;
@@ -278,26 +311,41 @@ k_gemm_rns_batched(RnsBatchArgs a) {
     int lo = p_lo, hi = p_hi - 1;  // last problem of this launch whose first tile is <= t
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (a.desc[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
+      if (a.job[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
     }
-    const BatchDesc& d = a.desc[lo];
-    const int64_t n_ct = (d.d3 + TQ - 1) / TQ, n_rt = (d.R_out + C::TR - 1) / C::TR;
+    const RnsJob& d = a.job[lo];
+    const int64_t n_ct = (d.cols + TQ - 1) / TQ, n_rt = (d.rows + C::TR - 1) / C::TR;
     TileAt at;
-    if (!batch_tile(t - d.tile_begin, a.n_mod * d.nz, n_rt, n_ct, d.rot, at)) continue;
+    if (!batch_tile(t - d.tile_begin, a.n_mod, n_rt, n_ct, d.rot, at)) continue;
     const int64_t ct = at.ct, rt = at.rt;
-    const int z = uniform(at.plane / a.n_mod), j = at.plane - z * a.n_mod;
-    RnsTile tl{d.Xd + ((size_t)z * a.n_mod + j) * a.KB * d.d3_pad * kKB,
-               a.Dr + ((size_t)d.slot[z] * a.n_mod + j) * a.KB * a.R_pad * kKB,
-               d.res + ((size_t)z * a.n_mod + j) * d.d3 * d.R_out, a.m[j], a.magic[j], a.KB, a.R_pad, d.d3_pad,
-               d.n_db, d.row0, d.R_out, d.d3, rt * C::TR, ct * TQ};
-    rns_tile<TQ>(tl, lds);
+    const int j = at.plane;
+    if (threadIdx.x < TQ) {  // the column's segment; padding columns read the last column and keep nothing
+      const int64_t want = ct * TQ + threadIdx.x;
+      const int64_t c = d.col0 + (want < d.cols ? want : d.cols - 1);
+      int64_t first = 0, at0 = 0;
+      int sel = 0;
+      for (int i = 0; i < d.n_seg; ++i) {
+        if (c >= first) {
+          sel = i;
+          at0 = first;
+        }
+        first += a.seg[d.seg + i].cols;
+      }
+      const RnsSeg g = a.seg[d.seg + sel];
+      const int64_t k = c - at0, zj = (int64_t)(d.n_slot_p ? g.level : d.slot) * a.n_mod + j;
+      col[threadIdx.x] = RnsCol{g.X + (zj * a.KB * g.d3_pad + k) * kKB, g.res + (zj * g.cols + k) * g.R_out,
+                                want < d.cols ? g.lo : 0, want < d.cols ? g.hi : 0, g.d3_pad * kKB};
+    }
+    __syncthreads();
+    RnsTile tl{nullptr, a.Dr + (((size_t)d.slot * a.n_mod + j) * a.KB * a.R_pad + d.db_row) * kKB, nullptr, a.m[j],
+               a.magic[j], a.KB, a.R_pad, 0, 0, 0, d.rows, d.cols, rt * C::TR, ct * TQ};
+    rns_tile<TQ, true>(tl, lds, col);
   }
 }
 
-int64_t rns_batched_tiles(int64_t d3, int64_t R_out, int nz, int n_mod, int tq, int64_t* groups) {
-  const int64_t n_ct = (d3 + tq - 1) / tq, n_rt = (R_out + kRnsTileR - 1) / kRnsTileR;
-  *groups = n_rt * nz * n_mod;
-  return batch_slots(*groups, n_ct);
+int64_t rns_batched_tiles(int64_t cols, int64_t rows, int n_mod, int tq, int64_t* groups) {
+  *groups = (rows + kRnsTileR - 1) / kRnsTileR * n_mod;
+  return batch_slots(*groups, (cols + tq - 1) / tq);
 }
 
 hipError_t launch_gemm_rns_batched(const RnsBatchArgs& a, int grid, int tq, hipStream_t s) {

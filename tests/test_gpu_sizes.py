@@ -142,3 +142,29 @@ def test_contraction_split_along_the_code_length_gives_the_same_residues(form, r
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), got.astype(np.int64))
     _check(keys, r, mq, mdb, "split")
+
+
+# rows several requests share (one job of both widths, cut at tile boundaries and beyond the last row), short ranges
+# apart, one request alone; levels mixed so that each prime slot has its own set of requests
+@pytest.mark.parametrize("spans", [
+    [(0, 1500, 20, 3), (100, 900, 70, 1), (255, 2, 3, 2), (600, 900, 130, 2), (1499, 1, 1, 3), (0, 1500, 4, 3)],
+    [(256 * i + 17, 40, 2 + i, 1 + i % 3) for i in range(5)],
+    [(300, 1200, 33, 2)],
+    [(0, 1500, 48, 1 + i % 3) for i in range(8)],
+])
+def test_batched_rns_jobs_give_every_request_its_single_result(spans):
+    d1, d2 = 1500, 201
+    rng = np.random.default_rng(400 + len(spans))
+    keys = H.hfe_keygen(H.hfe_default_params(6, 6, 3, d2, d1), 5)
+    mdb = _ternary(rng, d1, d2)
+    db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, H.HFE_FORM_RNS_I8)
+    items, mqs = [], []
+    for i, (row0, rows, cols, level) in enumerate(spans):
+        mqs.append(_ternary(rng, cols, d2))
+        items.append((H.hfe_encrypt(keys, torch.from_numpy(mqs[-1]).cuda(), level, 50 + i), row0, rows))
+    _say(f"[gpu-sizes] batched rns {spans}")
+    outs = H.hfe_ccmm_batched(db, items, H.HFE_FORM_RNS_I8)
+    for i, (q, row0, rows) in enumerate(items):
+        one = H.hfe_ccmm(db, q, row0, rows, H.HFE_FORM_RNS_I8)
+        assert np.array_equal(H.hfe_export(outs[i], 0), H.hfe_export(one, 0)), f"request {i}"
+        _check(keys, outs[i], mqs[i], mdb[row0:row0 + rows], f"request {i}")
