@@ -344,92 +344,124 @@ __device__ __forceinline__ void tile_pipe(const I8Tile& T, int8_t* lds) {
 // makes the b128 fragment reads of 16 consecutive rows hit 64 distinct banks.  Wait counts are
 // managed here: with three stages every wave issues the same number of loads per block and waits
 // until only the next block's are outstanding, with two stages it waits for all.
+// Matrix-core power bounds the full chip (about 1.7 GHz under this load), so what counts is the cycles in which the
+// cores wait: with the barrier, the loads (each under a lane mask, its address a 64-bit product) and the first fragment
+// reads at the head of a block they did for 8% of the time (512 columns, 30,720 rows, K = 20,992 in four primes: 26.8
+// ms, now 24.8, 2.66 POP/s; 4 columns, 4,352 rows, K = 5,120: 70 us, now 64).
 // lds: STAGES x 5 x (32 WQ + 32 WR) rows x 64 bytes.
 constexpr int kDmaRow = kKB;  // LDS bytes per tile row
-
 
 template <int WR, int WQ, int STAGES>
 __device__ __forceinline__ void tile_dma(const I8Tile& T, int8_t* lds) {
   constexpr int NW = WR * WQ, BR = 32 * WR, BQ = 32 * WQ;
   constexpr int kPA = BQ * kDmaRow, kPB = BR * kDmaRow, kStage = kDigits * (kPA + kPB);
-  constexpr int LA = (BQ / 16 + NW - 1) / NW, LB = (BR / 16 + NW - 1) / NW;  // loads per wave per plane
-  static_assert(STAGES == 2 || (STAGES == 3 && BQ / 16 % NW == 0 && BR / 16 % NW == 0),
-                "three stages need the same load count on every wave");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // The planes of a stage lie one after another, the query's first; load L fills rows 16 L .. 16 L + 15 of them, and
+  // wave w issues loads w, w + NW, ..: the same number for every wave, or one less.
+  constexpr int kLoadsA = kDigits * BQ / 16, kLoads = kLoadsA + kDigits * BR / 16, NL = (kLoads + NW - 1) / NW;
+  static_assert(STAGES == 2 || (STAGES == 3 && kLoads == 10 * NW), "three stages need 10 loads of every wave");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wq = wave % WQ, wr = wave / WQ;
   const size_t planeB = (size_t)T.KB * T.R_pad * kKB, planeA = (size_t)T.KB * T.d3_pad * kKB;
   const size_t stepB = (size_t)T.R_pad * kKB, stepA = (size_t)T.d3_pad * kKB;
-  // load j of a wave fills plane rows 16 (wave + NW j) .. + 15: lane l -> row + l / 4, stored
-  // chunk l % 4, which holds logical chunk (l % 4) ^ ((row >> 2) & 3) (the same for every j,
-  // since 16 NW j is a multiple of 16)
-  const int ld_row = 16 * wave + (lane >> 2);
-  const int ld_chunk = ((lane & 3) ^ ((ld_row >> 2) & 3)) * 16;
-  const int8_t* gA[LA];
-  const int8_t* gB[LB];
-#pragma unroll
-  for (int j = 0; j < LA; ++j) gA[j] = T.Xd + (size_t)(T.c0 + ld_row + 16 * NW * j) * kKB + ld_chunk;
-#pragma unroll
-  for (int j = 0; j < LB; ++j)
-    gB[j] = T.Dd + (size_t)src_row(T.r0 + ld_row + 16 * NW * j, T.n_db, T.row0) * kKB + ld_chunk;
+  // lane l of a load: row l / 4, stored chunk l % 4, which holds logical chunk (l % 4) ^ ((row >> 2) & 3)
+  const int ld_chunk = ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds + wave * 16 * kDmaRow;
-  auto issue = [&](int stage, int64_t kb) {
+  const int8_t* gp[NL];
+  auto issue = [&](int stage) {
     const uint32_t base = lds0 + stage * kStage;
 #pragma unroll
-    for (int t = 0; t < kDigits; ++t) {
+    for (int i = 0; i < NL; ++i)
+      if (NW * (i + 1) <= kLoads || wave + NW * i < kLoads) dma16(gp[i], base + NW * i * 16 * kDmaRow);
+  };
+  // the load addresses move on to the next K-block; past the last one the loads repeat it
+  int32_t left = 0;
+  auto advance = [&]() {
+    const size_t dA = left > 0 ? stepA : 0, dB = left > 0 ? stepB : 0;
+    --left;
 #pragma unroll
-      for (int j = 0; j < LA; ++j)
-        if (16 * (wave + NW * j) < BQ) dma16(gA[j] + t * planeA + kb * stepA, base + t * kPA + 16 * NW * j * kDmaRow);
-#pragma unroll
-      for (int j = 0; j < LB; ++j)
-        if (16 * (wave + NW * j) < BR)
-          dma16(gB[j] + t * planeB + kb * stepB, base + kDigits * kPA + t * kPB + 16 * NW * j * kDmaRow);
-    }
+    for (int i = 0; i < NL; ++i) gp[i] += wave + NW * i < kLoadsA ? dA : dB;
   };
   // fragment reads: row r, logical chunk c -> byte r * 64 + ((c ^ ((r >> 2) & 3)) * 16); the
   // query row wq 32 + l % 32 and database row wr 32 + l % 32 share the swizzle
   const int sw = ((lane & 31) >> 2) & 3;
   const int offA = (wq * 32 + (lane & 31)) * kDmaRow, offB = kDigits * kPA + (wr * 32 + (lane & 31)) * kDmaRow;
   const int c0 = lane >> 5;  // logical chunk of the first K-half; the second half adds 2
+  auto fa = [&](int st, int t, int c) {
+    return *reinterpret_cast<const v4i*>(lds + st * kStage + offA + t * kPA + ((c ^ sw) << 4));
+  };
+  auto fb = [&](int st, int t, int c) {
+    return *reinterpret_cast<const v4i*>(lds + st * kStage + offB + t * kPB + ((c ^ sw) << 4));
+  };
+  // K-block i + 1 has landed for this wave (with three stages block i + 2 may still fly) and its reads of block i are
+  // done, then the same for every wave
+  auto block_wait = [&]() {
+    if constexpr (STAGES == 3)
+      asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
 
   for (int64_t kb0 = 0; kb0 < T.nk; kb0 += kChunkKB) {
     const int64_t kb_end = kb0 + kChunkKB < T.nk ? kb0 + kChunkKB : T.nk;
-    const int64_t n = kb_end - kb0;
-    auto clamp = [&](int64_t i) { return kb0 + (i < n ? i : n - 1); };
+    const int32_t n = (int32_t)(kb_end - kb0);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int L = wave + NW * i < kLoads ? wave + NW * i : kLoads - 1;
+      if (L < kLoadsA) {
+        const int t = L / (BQ / 16), row = 16 * (L % (BQ / 16)) + (lane >> 2);
+        gp[i] = T.Xd + t * planeA + kb0 * stepA + (size_t)(T.c0 + row) * kKB + ld_chunk;
+      } else {
+        const int t = (L - kLoadsA) / (BR / 16), row = 16 * ((L - kLoadsA) % (BR / 16)) + (lane >> 2);
+        gp[i] = T.Dd + t * planeB + kb0 * stepB + (size_t)src_row(T.r0 + row, T.n_db, T.row0) * kKB + ld_chunk;
+      }
+    }
+    left = n - 1;
     v16i acc[9];
 #pragma unroll
     for (int u = 0; u < 9; ++u) acc[u] = (v16i){0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < STAGES - 1; ++j) issue(j, clamp(j));
-    for (int64_t i = 0; i < n; ++i) {
-      const int st = (int)(i % STAGES);
-      // block i complete for this wave (with three stages block i + 1 may still fly), then for
-      // all waves; all waves are also done reading the stage that block i + STAGES - 1 overwrites
-      if constexpr (STAGES == 3) {
-        static_assert(kDigits * (BQ / 16 / NW + BR / 16 / NW) == 10, "vmcnt below assumes 10 loads per block");
-        asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      } else {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      }
-      issue((int)((i + STAGES - 1) % STAGES), clamp(i + STAGES - 1));
-      const int8_t* S = lds + st * kStage;
-      auto fa = [&](int t, int c) { return *reinterpret_cast<const v4i*>(S + offA + t * kPA + ((c ^ sw) << 4)); };
-      auto fb = [&](int t, int c) { return *reinterpret_cast<const v4i*>(S + offB + t * kPB + ((c ^ sw) << 4)); };
-      v4i a0[kDigits], a1[kDigits], b_cur, b_nxt;
+    for (int j = 0; j < STAGES - 1; ++j) {
+      issue(j);
+      advance();
+    }
+    block_wait();
+    issue(STAGES - 1);
+    advance();
+    v4i a0[kDigits], a1[kDigits], b[kDigits * 2];
 #pragma unroll
-      for (int t = 0; t < kDigits; ++t) a0[t] = fa(t, c0);
-      b_cur = fb(0, c0);
+    for (int t = 0; t < kDigits; ++t) a0[t] = fa(0, t, c0);
+    b[0] = fb(0, 0, c0);
+    int st = 0;
+    // Step s of a block multiplies database digit s % 5 of K-half s / 5 with the five query digits.  The next step's
+    // database fragment is read one step ahead, the second half's query fragments during the first.  The barrier
+    // stands before the last step: after it the next block's first fragments are read and the loads of the block that
+    // takes this one's stage are issued while that step's products, and the other wave's, keep the matrix cores busy.
+    for (int32_t i = 0; i < n; ++i) {
+      const int nxt = st + 1 == STAGES ? 0 : st + 1;
 #pragma unroll
       for (int step = 0; step < 2 * kDigits; ++step) {
         const int half = step / kDigits, s = step % kDigits;
-        if (step + 1 < 2 * kDigits) b_nxt = fb((step + 1) % kDigits, c0 + 2 * ((step + 1) / kDigits));
-        if (step < kDigits) a1[step] = fa(step, c0 + 2);
+        if (step + 1 < 2 * kDigits) {
+          b[step + 1] = fb(st, (step + 1) % kDigits, c0 + 2 * ((step + 1) / kDigits));
+          if (step < kDigits) a1[step] = fa(st, step, c0 + 2);
+        } else {
+          __builtin_amdgcn_sched_barrier(0);
+          block_wait();
+#pragma unroll
+          for (int t = 0; t < kDigits; ++t) a0[t] = fa(nxt, t, c0);
+          b[0] = fb(nxt, 0, c0);
+          issue(st);
+          __builtin_amdgcn_sched_barrier(0);
+          advance();
+        }
 #pragma unroll
         for (int t = 0; t < kDigits; ++t)
-          acc[s + t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(half ? a1[t] : a0[t], b_cur, acc[s + t], 0, 0, 0);
-        b_cur = b_nxt;
+          acc[s + t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(half ? a1[t] : a0[t], b[step], acc[s + t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // no reads further ahead than written: the registers are full
       }
+      st = nxt;
     }
-    // drain the clamped loads still in flight before the stages are reused
+    // drain the repeated loads still in flight before the stages are reused
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     store_tile(T, acc, wq, wr, lane, kb0 != 0);
   }
@@ -673,7 +705,7 @@ hipError_t launch_gemm_i8(const GemmArgs& g, int variant, hipStream_t s) {
 // Splitting pays where it shortens the longest chain of K-blocks a CU works through, ceil(tiles / slots) of them
 // whole: the fewest parts within 15% of the shortest (each part costs a prologue and an epilogue), of at least 16
 // K-blocks.  Measured, contraction + sum of the parts: 4 columns, 4,352 rows, K = 5,120 (68 workgroups of the digit
-// tile) 168 -> 71 + 5 us in 3 parts; 48 columns, 4,896 rows, K = 7,563 (77) 288 -> 129 + 5 us in 3; the n^2 tile at a
+// tile) 168 -> 71 + 5 us in 3 parts (64 + 5 now); 48 columns, 4,896 rows, K = 7,563 (77) 288 -> 129 + 5 us in 3; the n^2 tile at a
 // nearly empty last wave 1,032 -> 937 + 27 us; the RNS tile, which streams more bytes per product, 85 -> 75 + 5 us.
 int gemm_splits(int64_t tiles, int64_t slots, int64_t KB) {
   if (tiles <= 0 || slots <= 0) return 1;
