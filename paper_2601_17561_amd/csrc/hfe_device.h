@@ -279,6 +279,32 @@ __device__ __forceinline__ void rescale_from(const uint64_t* src, int64_t zstrid
   rescale_element(src - e, src - e + (int64_t)ra.level * zstride, n, ra, out, e, zstride);
 }
 
+// Database split: thread (row r, quarter h of K-block kb) holds the 16 centered residues of D[k][r], k in its 16 bytes of
+// the block, and writes them as 16 bytes of each plane's row.  Four lanes share a row, so a wave reads 128 consecutive
+// bytes of four k at a time and writes whole 1 KiB runs; a thread to a row (64 residues, a 64-byte row per plane in
+// four 16-byte pieces at 64-byte strides) took 2.93 ms for the digits of 20,992 x 30,720 residues, this takes 1.62 (5.2
+// TB/s: memory bounds it); 11 small moduli of 11,818 x 10,021 923 and 670 us (their reductions), six n^2 bases 405 and 197.
+constexpr int kSplitRows = 64;  // rows of a 256-thread block
+struct SplitAt {
+  int64_t r, kb;
+  int h;
+};
+__device__ __forceinline__ SplitAt split_at() {
+  return {(int64_t)blockIdx.x * kSplitRows + (threadIdx.x >> 2), (int64_t)blockIdx.y, (int)(threadIdx.x & 3)};
+}
+__device__ __forceinline__ void split_load(const SplitAt& at, const uint64_t* Dt, int64_t K, int64_t R, uint64_t q,
+                                           int64_t (&x)[16]) {
+  const int64_t k0 = at.kb * kKB + 16 * at.h;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = at.r < R && k0 + i < K ? centered(Dt[(k0 + i) * R + at.r], q) : 0;
+}
+__device__ __forceinline__ void split_store(const SplitAt& at, int8_t* planes, int64_t plane, int64_t KB, int64_t R_pad,
+                                            const uint32_t (&w)[4]) {
+  *reinterpret_cast<uint4*>(planes + ((plane * KB + at.kb) * R_pad + at.r) * kKB + 16 * at.h) =
+      make_uint4(w[0], w[1], w[2], w[3]);
+}
+inline dim3 split_grid(int64_t R_pad, int64_t KB) { return dim3((unsigned)((R_pad + kSplitRows - 1) / kSplitRows), (unsigned)KB); }
+
 // A contraction's tiles come in groups, the query column tiles of one row tile of one plane, which read the same
 // database rows.  Group g goes to XCD g mod 8, so that its tiles share those rows in one L2 while all XCDs work on one
 // plane or two; the groups beyond the last multiple of 8 are dealt tile by tile in runs of equal length.  No XCD has a

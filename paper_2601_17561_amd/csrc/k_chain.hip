@@ -20,42 +20,28 @@ ChainBase chain_base(int32_t n) {
 }
 
 // ------------------------------------------------------------------ database split
-// Thread (row r, K-block kb): 64 residues Dt[k][r] mod n^2, centered -> one 64-byte row of M (plane 0)
-// and one of M' (plane 1).
+// The digits of each centered residue mod n^2: M in plane 0, M' in plane 1.
 __global__ void __launch_bounds__(256) k_chain_split_db(const uint64_t* Dt, int64_t K, int64_t R, int64_t KB,
                                                         int64_t R_pad, ChainBase b, int8_t* planes) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kb = blockIdx.y;
-  if (r >= R_pad) return;
-  uint4* d0 = reinterpret_cast<uint4*>(planes + ((int64_t)kb * R_pad + r) * kKB);
-  uint4* d1 = reinterpret_cast<uint4*>(planes + (((int64_t)KB + kb) * R_pad + r) * kKB);
+  const SplitAt at = split_at();
+  if (at.r >= R_pad) return;
+  int64_t x[16];
+  split_load(at, Dt, K, R, (uint64_t)b.m, x);
+  uint32_t w0[4] = {}, w1[4] = {};
 #pragma unroll
-  for (int i = 0; i < kKB / 16; ++i) {
-    uint32_t w0[4], w1[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      uint32_t v0 = 0, v1 = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t k = kb * kKB + 16 * i + 4 * t + e;
-        const int64_t x = (r < R && k < K) ? centered(Dt[k * R + r], (uint64_t)b.m) : 0;
-        int32_t M, Mp;
-        p2_digits_by(x, b.n, b.m, b.magic_n, b.rcp_m, M, Mp);
-        v0 |= ((uint32_t)M & 255u) << (8 * e);
-        v1 |= ((uint32_t)Mp & 255u) << (8 * e);
-      }
-      w0[t] = v0;
-      w1[t] = v1;
-    }
-    d0[i] = make_uint4(w0[0], w0[1], w0[2], w0[3]);
-    d1[i] = make_uint4(w1[0], w1[1], w1[2], w1[3]);
+  for (int i = 0; i < 16; ++i) {
+    int32_t M, Mp;
+    p2_digits_by(x[i], b.n, b.m, b.magic_n, b.rcp_m, M, Mp);
+    w0[i >> 2] |= ((uint32_t)M & 255u) << (8 * (i & 3));
+    w1[i >> 2] |= ((uint32_t)Mp & 255u) << (8 * (i & 3));
   }
+  split_store(at, planes, 0, KB, R_pad, w0);
+  split_store(at, planes, 1, KB, R_pad, w1);
 }
 
 hipError_t launch_chain_split_db(const uint64_t* Dt, int64_t K, int64_t R, int64_t KB, int64_t R_pad,
                                  const ChainBase& b, int8_t* planes, hipStream_t s) {
-  dim3 grid((unsigned)((R_pad + 255) / 256), (unsigned)KB);
-  hipLaunchKernelGGL(k_chain_split_db, grid, dim3(256), 0, s, Dt, K, R, KB, R_pad, b, planes);
+  hipLaunchKernelGGL(k_chain_split_db, split_grid(R_pad, KB), dim3(256), 0, s, Dt, K, R, KB, R_pad, b, planes);
   return hipGetLastError();
 }
 

@@ -93,40 +93,28 @@ hipError_t launch_transpose_i8(const int8_t* in, int64_t rows, int64_t cols, int
   return hipGetLastError();
 }
 
-// Thread (row r, block kb): 64 residues Dt[kb*64 + kk][r] -> 64 bytes of each digit plane.
+// The five digits of each residue, one plane each.
 __global__ void __launch_bounds__(256) k_split_db(const uint64_t* Dt, int64_t K, int64_t R, int64_t KB,
                                                   int64_t R_pad, uint64_t q, int8_t* dig) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kb = blockIdx.y;
-  if (r >= R_pad) return;
-  uint32_t w[kDigits][kKB / 4];
+  const SplitAt at = split_at();
+  if (at.r >= R_pad) return;
+  int64_t x[16];
+  split_load(at, Dt, K, R, q, x);
+  uint32_t w[kDigits][4] = {};
 #pragma unroll
-  for (int t = 0; t < kDigits; ++t)
-#pragma unroll
-    for (int i = 0; i < kKB / 4; ++i) w[t][i] = 0;
-#pragma unroll
-  for (int kk = 0; kk < kKB; ++kk) {
-    const int64_t k = kb * kKB + kk;
-    int64_t x = 0;
-    if (r < R && k < K) x = centered(Dt[k * R + r], q);
+  for (int i = 0; i < 16; ++i) {
     int32_t d[kDigits];
-    split5(x, d);
+    split5(x[i], d);
 #pragma unroll
-    for (int t = 0; t < kDigits; ++t) w[t][kk >> 2] |= ((uint32_t)(d[t] & 255)) << (8 * (kk & 3));
+    for (int t = 0; t < kDigits; ++t) w[t][i >> 2] |= ((uint32_t)(d[t] & 255)) << (8 * (i & 3));
   }
 #pragma unroll
-  for (int t = 0; t < kDigits; ++t) {
-    uint4* dst = reinterpret_cast<uint4*>(dig + (((int64_t)t * KB + kb) * R_pad + r) * kKB);
-#pragma unroll
-    for (int i = 0; i < kKB / 16; ++i)
-      dst[i] = make_uint4(w[t][4 * i], w[t][4 * i + 1], w[t][4 * i + 2], w[t][4 * i + 3]);
-  }
+  for (int t = 0; t < kDigits; ++t) split_store(at, dig, t, KB, R_pad, w[t]);
 }
 
 hipError_t launch_split_db(const uint64_t* Dt_prime, int64_t K, int64_t R, int64_t KB, int64_t R_pad,
                            uint64_t q, int8_t* dig_prime, hipStream_t s) {
-  dim3 grid((unsigned)((R_pad + 255) / 256), (unsigned)KB);
-  hipLaunchKernelGGL(k_split_db, grid, dim3(256), 0, s, Dt_prime, K, R, KB, R_pad, q, dig_prime);
+  hipLaunchKernelGGL(k_split_db, split_grid(R_pad, KB), dim3(256), 0, s, Dt_prime, K, R, KB, R_pad, q, dig_prime);
   return hipGetLastError();
 }
 

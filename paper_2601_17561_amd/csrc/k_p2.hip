@@ -9,49 +9,31 @@
 namespace hfe {
 
 // ------------------------------------------------------------------ database split
-// Thread (row r, K-block kb): the 64 centered residues of D[k][r] -> per base one 64-byte row of M
-// (plane 2j) and one of M' (plane 2j + 1).
+// Per base the digits of each centered residue: M in plane 2j, M' in plane 2j + 1.
 __global__ void __launch_bounds__(256) k_split_db_p2(const uint64_t* Dt, int64_t K, int64_t R, int64_t KB,
                                                      int64_t R_pad, uint64_t q, int n_bases, int8_t* planes) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kb = blockIdx.y;
-  if (r >= R_pad) return;
-  int64_t x[kKB];
-#pragma unroll
-  for (int kk = 0; kk < kKB; ++kk) {
-    const int64_t k = kb * kKB + kk;
-    x[kk] = (r < R && k < K) ? centered(Dt[k * R + r], q) : 0;
-  }
+  const SplitAt at = split_at();
+  if (at.r >= R_pad) return;
+  int64_t x[16];
+  split_load(at, Dt, K, R, q, x);
   for (int j = 0; j < n_bases; ++j) {
-    uint4* d0 = reinterpret_cast<uint4*>(planes + (((int64_t)(2 * j) * KB + kb) * R_pad + r) * kKB);
-    uint4* d1 = reinterpret_cast<uint4*>(planes + (((int64_t)(2 * j + 1) * KB + kb) * R_pad + r) * kKB);
+    uint32_t w0[4] = {}, w1[4] = {};
 #pragma unroll
-    for (int i = 0; i < kKB / 16; ++i) {  // 16 bytes of each plane at a time
-      uint32_t w0[4], w1[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        uint32_t v0 = 0, v1 = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          int32_t M, Mp;
-          p2_digits(x[16 * i + 4 * t + b], j, M, Mp);
-          v0 |= ((uint32_t)M & 255u) << (8 * b);
-          v1 |= ((uint32_t)Mp & 255u) << (8 * b);
-        }
-        w0[t] = v0;
-        w1[t] = v1;
-      }
-      d0[i] = make_uint4(w0[0], w0[1], w0[2], w0[3]);
-      d1[i] = make_uint4(w1[0], w1[1], w1[2], w1[3]);
+    for (int i = 0; i < 16; ++i) {
+      int32_t M, Mp;
+      p2_digits(x[i], j, M, Mp);
+      w0[i >> 2] |= ((uint32_t)M & 255u) << (8 * (i & 3));
+      w1[i >> 2] |= ((uint32_t)Mp & 255u) << (8 * (i & 3));
     }
+    split_store(at, planes, 2 * j, KB, R_pad, w0);
+    split_store(at, planes, 2 * j + 1, KB, R_pad, w1);
   }
 }
 
 hipError_t launch_split_db_p2(const uint64_t* Dt_prime, int64_t K, int64_t R, int64_t KB, int64_t R_pad,
                               uint64_t q, int n_bases, int8_t* planes_prime, hipStream_t s) {
   if (n_bases < 1 || n_bases > kP2MaxBases) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((R_pad + 255) / 256), (unsigned)KB);
-  hipLaunchKernelGGL(k_split_db_p2, grid, dim3(256), 0, s, Dt_prime, K, R, KB, R_pad, q, n_bases, planes_prime);
+  hipLaunchKernelGGL(k_split_db_p2, split_grid(R_pad, KB), dim3(256), 0, s, Dt_prime, K, R, KB, R_pad, q, n_bases, planes_prime);
   return hipGetLastError();
 }
 

@@ -9,37 +9,24 @@
 namespace hfe {
 
 // ------------------------------------------------------------------ database split
-// Thread (row r, K-block kb): the 64 centered residues of D[k][r] -> one 64-byte row per modulus.
+// The balanced residues of each centered residue modulo the small moduli, one plane each.
 __global__ void __launch_bounds__(256) k_split_db_rns(const uint64_t* Dt, int64_t K, int64_t R, int64_t KB,
                                                       int64_t R_pad, uint64_t q, int n_mod, int8_t* dig) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kb = blockIdx.y;
-  if (r >= R_pad) return;
-  int64_t x[kKB];
-#pragma unroll
-  for (int kk = 0; kk < kKB; ++kk) {
-    const int64_t k = kb * kKB + kk;
-    x[kk] = (r < R && k < K) ? centered(Dt[k * R + r], q) : 0;
-  }
+  const SplitAt at = split_at();
+  if (at.r >= R_pad) return;
+  int64_t x[16];
+  split_load(at, Dt, K, R, q, x);
   for (int j = 0; j < n_mod; ++j) {
-    uint32_t w[kKB / 4];
+    uint32_t w[4] = {};
 #pragma unroll
-    for (int i = 0; i < kKB / 4; ++i) {
-      uint32_t v = 0;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) v |= ((uint32_t)(balanced_mod(x[4 * i + b], j) & 255)) << (8 * b);
-      w[i] = v;
-    }
-    uint4* dst = reinterpret_cast<uint4*>(dig + (((int64_t)j * KB + kb) * R_pad + r) * kKB);
-#pragma unroll
-    for (int i = 0; i < kKB / 16; ++i) dst[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+    for (int i = 0; i < 16; ++i) w[i >> 2] |= ((uint32_t)(balanced_mod(x[i], j) & 255)) << (8 * (i & 3));
+    split_store(at, dig, j, KB, R_pad, w);
   }
 }
 
 hipError_t launch_split_db_rns(const uint64_t* Dt_prime, int64_t K, int64_t R, int64_t KB, int64_t R_pad,
                                uint64_t q, int n_mod, int8_t* dig_prime, hipStream_t s) {
-  dim3 grid((unsigned)((R_pad + 255) / 256), (unsigned)KB);
-  hipLaunchKernelGGL(k_split_db_rns, grid, dim3(256), 0, s, Dt_prime, K, R, KB, R_pad, q, n_mod, dig_prime);
+  hipLaunchKernelGGL(k_split_db_rns, split_grid(R_pad, KB), dim3(256), 0, s, Dt_prime, K, R, KB, R_pad, q, n_mod, dig_prime);
   return hipGetLastError();
 }
 
