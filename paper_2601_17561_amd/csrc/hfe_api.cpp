@@ -891,13 +891,13 @@ static int64_t d3_bucket(int64_t d3) {
   return b;
 }
 // The forced variant if one is set; else the tuned entry of this level with the nearest column
-// bucket; else the default.
-static int pick_i8_variant(int level, int64_t d3) {
+// bucket; else `untuned`.
+static int pick_i8_variant(int level, int64_t d3, int untuned = kDefaultI8Variant) {
   const int forced = g_i8_variant.load();
   if (forced >= 0) return forced;
   std::lock_guard<std::mutex> l(g_tune_mu);
   const int64_t b = d3_bucket(d3);
-  int best = kDefaultI8Variant;
+  int best = untuned;
   int64_t best_dist = -1;
   for (const auto& kv : g_tuned) {
     if (kv.first.first != level) continue;
@@ -1260,7 +1260,10 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     const size_t planeD = (size_t)D->KB * D->R_pad * kKB;
     int8_t* Xd = nullptr;
     HFE_TRY(W.get((size_t)nz * kDigits * planeX, s, &Xd));
-    const int variant = pick_i8_variant(level, d3);
+    // up to 32 columns: the tile of 32, half the products of the default's 64 (4 columns, 4,352 rows, K = 5,120: 44 us
+    // against 64; 32 columns, 4,079 rows, K = 6,165 in four primes: 116 against 138; one column, 30,720 rows: 2.05 ms,
+    // 6.3 TB/s, against 2.86); batches have their problems' columns side by side
+    const int variant = pick_i8_variant(level, d3, d3 <= 32 ? i8_narrow_variant() : kDefaultI8Variant);
     const int64_t br = i8_variant_tile_rows(variant), bq = i8_variant_tile_cols(variant);
     split_parts(W, ((R_out + br - 1) / br) * ((d3 + bq - 1) / bq) * nz, i8_variant_wgs_per_cu(variant), D->KB,
                 (size_t)nz * d3 * R_out, s, &g.splits, &g.part);

@@ -505,6 +505,7 @@ hipError_t launch_gemm_plain(const GemmArgs& g, hipStream_t s);
 // operands, 3 = v_mad_u64_u32; grid workgroups of 256 threads, sink >= grid * 256 * 8 bytes
 hipError_t launch_probe(int which, int64_t iters, int grid, void* sink, hipStream_t s);
 hipError_t launch_gemm_i8(const GemmArgs& g, int variant, hipStream_t s);
+int i8_narrow_variant();            // the tile of 32 query columns
 constexpr int kMaxI8Variants = 16;  // upper bound of i8_variant_count()
 int i8_variant_count();
 const char* i8_variant_name(int v);

@@ -342,8 +342,8 @@ __device__ __forceinline__ void tile_pipe(const I8Tile& T, int8_t* lds) {
 // WR x WQ waves, each owning a 32 (query) x 32 (database row) output block.  Rows are 64 bytes
 // without padding; the 16-byte chunk c of row r sits at chunk position c ^ ((r >> 2) & 3), which
 // makes the b128 fragment reads of 16 consecutive rows hit 64 distinct banks.  Wait counts are
-// managed here: with three stages every wave issues the same number of loads per block and waits
-// until only the next block's are outstanding, with two stages it waits for all.
+// managed here: with three stages a wave waits until only as many loads are outstanding as every wave
+// issues for the next block, with two stages for all.
 // Matrix-core power bounds the full chip (about 1.7 GHz under this load), so what counts is the cycles in which the
 // cores wait: with the barrier, the loads (each under a lane mask, its address a 64-bit product) and the first fragment
 // reads at the head of a block they did for 8% of the time (512 columns, 30,720 rows, K = 20,992 in four primes: 26.8
@@ -358,7 +358,8 @@ __device__ __forceinline__ void tile_dma(const I8Tile& T, int8_t* lds) {
   // The planes of a stage lie one after another, the query's first; load L fills rows 16 L .. 16 L + 15 of them, and
   // wave w issues loads w, w + NW, ..: the same number for every wave, or one less.
   constexpr int kLoadsA = kDigits * BQ / 16, kLoads = kLoadsA + kDigits * BR / 16, NL = (kLoads + NW - 1) / NW;
-  static_assert(STAGES == 2 || (STAGES == 3 && kLoads == 10 * NW), "three stages need 10 loads of every wave");
+  constexpr int kEvery = kLoads / NW;  // loads per block of every wave (some have one more)
+  static_assert(STAGES == 2 || (STAGES == 3 && (kEvery == 10 || kEvery == 12)), "no block wait for this tile shape");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wq = wave % WQ, wr = wave / WQ;
   const size_t planeB = (size_t)T.KB * T.R_pad * kKB, planeA = (size_t)T.KB * T.d3_pad * kKB;
@@ -395,7 +396,9 @@ __device__ __forceinline__ void tile_dma(const I8Tile& T, int8_t* lds) {
   // K-block i + 1 has landed for this wave (with three stages block i + 2 may still fly) and its reads of block i are
   // done, then the same for every wave
   auto block_wait = [&]() {
-    if constexpr (STAGES == 3)
+    if constexpr (STAGES == 3 && kEvery == 12)
+      asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if constexpr (STAGES == 3)
       asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -680,11 +683,12 @@ static const I8Variant kI8Variants[] = {
     HFE_I8_VARIANT("pipe_w1", 2, 2, 2, 1, 1),
     HFE_I8_VARIANT("r2q2b1w1", 2, 2, 1, 1, 0),    HFE_I8_VARIANT("r2q2b2w1", 2, 2, 2, 1, 0),
     HFE_I8_VARIANT("r2q2b1w2", 2, 2, 1, 2, 0),    HFE_I8_VARIANT("r4q2b1w2", 4, 2, 1, 2, 0),
-    HFE_I8_VARIANT("r2q4b1w2", 2, 4, 1, 2, 0),
+    HFE_I8_VARIANT("r2q4b1w2", 2, 4, 1, 2, 0),    HFE_I8_VARIANT("dma3_q32_w1", 4, 1, 3, 1, 2),
 };
 constexpr int kNumI8Variants = sizeof(kI8Variants) / sizeof(kI8Variants[0]);
 static_assert(kNumI8Variants <= kMaxI8Variants, "raise kMaxI8Variants");
 
+int i8_narrow_variant() { return kNumI8Variants - 1; }
 int i8_variant_count() { return kNumI8Variants; }
 const char* i8_variant_name(int v) { return (v >= 0 && v < kNumI8Variants) ? kI8Variants[v].name : nullptr; }
 int i8_variant_tile_rows(int v) { return kI8Variants[v].br; }
@@ -705,7 +709,7 @@ hipError_t launch_gemm_i8(const GemmArgs& g, int variant, hipStream_t s) {
 // Splitting pays where it shortens the longest chain of K-blocks a CU works through, ceil(tiles / slots) of them
 // whole: the fewest parts within 15% of the shortest (each part costs a prologue and an epilogue), of at least 16
 // K-blocks.  Measured, contraction + sum of the parts: 4 columns, 4,352 rows, K = 5,120 (68 workgroups of the digit
-// tile) 168 -> 71 + 5 us in 3 parts (64 + 5 now); 48 columns, 4,896 rows, K = 7,563 (77) 288 -> 129 + 5 us in 3; the n^2 tile at a
+// tile) 168 -> 71 + 5 us in 3 parts; 48 columns, 4,896 rows, K = 7,563 (77) 288 -> 129 + 5 us in 3; the n^2 tile at a
 // nearly empty last wave 1,032 -> 937 + 27 us; the RNS tile, which streams more bytes per product, 85 -> 75 + 5 us.
 int gemm_splits(int64_t tiles, int64_t slots, int64_t KB) {
   if (tiles <= 0 || slots <= 0) return 1;

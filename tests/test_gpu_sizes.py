@@ -168,3 +168,18 @@ def test_batched_rns_jobs_give_every_request_its_single_result(spans):
         one = H.hfe_ccmm(db, q, row0, rows, H.HFE_FORM_RNS_I8)
         assert np.array_equal(H.hfe_export(outs[i], 0), H.hfe_export(one, 0)), f"request {i}"
         _check(keys, outs[i], mqs[i], mdb[row0:row0 + rows], f"request {i}")
+
+
+# the 32-column digit tile's last column, the next width's first; row tiles of 128 with a remainder of one row
+@pytest.mark.parametrize("cols", [1, 31, 32, 33])
+def test_few_columns_of_the_digit_form_equal_the_small_moduli(cols):
+    d1, d2 = 193, 700
+    rng = np.random.default_rng(500 + cols)
+    keys = H.hfe_keygen(H.hfe_default_params(6, 7, 2, d2, d1), 5)
+    mdb, mq = _ternary(rng, d1, d2), _ternary(rng, cols, d2)
+    db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, H.HFE_FORM_I8_MFMA | H.HFE_FORM_RNS_I8)
+    q = H.hfe_encrypt(keys, torch.from_numpy(mq).cuda(), 2, 7)
+    _say(f"[gpu-sizes] digit form, {cols} columns")
+    r = H.hfe_ccmm(db, q, 0, d1, H.HFE_FORM_I8_MFMA)
+    assert np.array_equal(H.hfe_export(r, 0), H.hfe_export(H.hfe_ccmm(db, q, 0, d1, H.HFE_FORM_RNS_I8), 0))
+    _check(keys, r, mq, mdb, "all rows")
