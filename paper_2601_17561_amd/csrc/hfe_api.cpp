@@ -1158,7 +1158,8 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     HFE_LAUNCH(launch_gemm_plain(g, s));
   } else if (form == HFE_FORM_RNS_I8) {
     const int n = D->n_rns;
-    const int tq = rns_tile_q(&d3, &R_out, &nz, 1);  // query tile width by padded work
+    // in a fixed region the widths that its capacity was laid out for
+    const int tq = W.base ? std::max(rns_tile_q(d3), 128) : rns_tile_q(d3);
     const int64_t d3_pad = (d3 + tq - 1) / tq * tq;   // whole query tiles
     const size_t planeX = (size_t)D->KB * d3_pad * kKB;
     const size_t planeD = (size_t)D->KB * D->R_pad * kKB;

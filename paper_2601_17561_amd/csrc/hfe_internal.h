@@ -311,7 +311,7 @@ struct RnsGemmArgs {
 hipError_t launch_gemm_rns(const RnsGemmArgs& g, int tq, hipStream_t s);
 // the tile width with less padded work for problems of d3 columns, R_out rows and nz prime slots
 int64_t rns_tiles(int64_t d3, int64_t R_out, int tq);  // workgroups of one (prime, modulus)
-int rns_tile_q(const int64_t* d3, const int64_t* R_out, const int* nz, int n);
+int rns_tile_q(int64_t d3);
 struct RnsCrtArgs {
   int n;                                       // moduli in use
   int32_t m[kRnsMaxMods];

@@ -58,21 +58,24 @@ hipError_t launch_lift_rns(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB
 //     K-blocks are in flight while one is multiplied (three stages measured 6% slower, five no faster).
 //   TQ = 128: 2 x 2 waves, three stages of 24 KiB, two workgroups per CU.  About 9% slower per
 //     column than TQ = 256, but it pads query columns to 128 instead of 256; the host picks the
-//     width per call or batch by padded work.
+//     width per call by padded work.
+//   TQ = 64, 32: 1 x 4 waves of 2 x 2 and 1 x 2 blocks, three and four stages of 20 and 18 KiB, two workgroups per CU:
+//     for calls that only stream the database.
 // Exactness: |S| over the K-range <= K * 128 * 128 < 2^31 for K < 2^17 (checked by the host).
 template <int TQ>
 struct RnsCfg {
-  static_assert(TQ == 128 || TQ == 256, "query tile of 128 or 256 columns");
-  static constexpr int WQB = 2, WRB = 4, WPE = 2;  // 32 x 32 blocks per wave; waves per SIMD
+  static_assert(TQ == 32 || TQ == 64 || TQ == 128 || TQ == 256, "no such query tile");
+  static constexpr int WQB = TQ == 32 ? 1 : 2, WRB = TQ < 128 ? 2 : 4, WPE = 2;  // 32 x 32 blocks per wave; waves per SIMD
   static constexpr int TR = kRnsTileR;
   static constexpr int NQ = TQ / (32 * WQB), NR = TR / (32 * WRB), NW = NQ * NR;
-  static constexpr int STAGES = TQ == 256 ? 4 : 3;
+  static constexpr int STAGES = TQ == 256 || TQ == 32 ? 4 : 3;
   static constexpr int PA = TQ * kKB, PB = TR * kKB, STAGE = PA + PB;
-  static constexpr int LA = TQ / 16 / NW, LB = TR / 16 / NW;  // loads per wave per K-block
-  static constexpr int VM = (LA + LB) * (STAGES - 2);         // loads a wave may leave in flight at a wait
+  // 16-row loads of a stage, dealt to the waves by index: EVERY of each wave, and one more of the first waves
+  static constexpr int LOADS_A = TQ / 16, LOADS = LOADS_A + TR / 16, EVERY = LOADS / NW, NL = (LOADS + NW - 1) / NW;
+  static constexpr int VM = EVERY * (STAGES - 2);  // loads a wave may leave in flight at a wait
   static constexpr int LDS = STAGES * STAGE;
-  static_assert(TQ % (16 * NW) == 0 && TR % (16 * NW) == 0, "whole loads per wave");
   static_assert(STAGES >= 3, "the K-block wait leaves STAGES - 2 blocks in flight");
+  static_assert(NW == (TQ == 256 ? 8 : 4), "the launch's block size");
 };
 
 // One output tile (rows r0.., query columns c0..) of one (prime, modulus) product: X and D are that
@@ -90,15 +93,13 @@ struct RnsTile {
 // and its LDS reads are done; then the same for every wave
 template <int VM>
 __device__ __forceinline__ void rns_wait_block() {
-  static_assert(VM == 4 || VM == 6 || VM == 8 || VM == 12, "no K-block wait for this tile shape");
-  if constexpr (VM == 4)
-    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  static_assert(VM == 5 || VM == 6 || VM == 8, "no K-block wait for this tile shape");
+  if constexpr (VM == 5)
+    asm volatile("s_waitcnt vmcnt(5) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   else if constexpr (VM == 6)
     asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else if constexpr (VM == 8)
-    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   else
-    asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // A query column of a job's tile: its planes, its results' entry of the job's row 0, and the rows that are its own.
@@ -119,30 +120,30 @@ __device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds, const Rn
   const int8_t* X = g.X;
   const int8_t* D = g.D;
   const size_t stepA = (size_t)g.d3_pad * kKB, stepB = (size_t)g.R_pad * kKB;
-  // load i of a wave fills tile rows 16 (wave + NW i) .. + 15 (lane l: row + l / 4, stored chunk
-  // l % 4 holding logical chunk (l % 4) ^ ((row >> 2) & 3))
-  const int ld_row = 16 * wave + (lane >> 2);
-  const int ld_chunk = ((lane & 3) ^ ((ld_row >> 2) & 3)) * 16;
-  const int8_t* gA[C::LA];
-  size_t colstep[JOB ? C::LA : 1];  // columns of several problems: each its own stride
-  const int8_t* gB[C::LB];
+  // load L fills stage rows 16 L .. 16 L + 15, the query's and then the database's (lane l: row + l / 4, stored chunk
+  // l % 4 holding logical chunk (l % 4) ^ ((row >> 2) & 3)); wave w issues loads w, w + NW, ..
+  const int ld_chunk = ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
+  const int8_t* gp[C::NL];
+  size_t colstep[JOB ? C::NL : 1];  // columns of several problems: each its own stride
 #pragma unroll
-  for (int i = 0; i < C::LA; ++i) {
-    const int c = ld_row + 16 * C::NW * i;
-    gA[i] = (JOB ? col[c].X : X + (size_t)(c0 + c) * kKB) + ld_chunk;
-    if constexpr (JOB) colstep[i] = col[c].step;
+  for (int i = 0; i < C::NL; ++i) {
+    const int L = wave + C::NW * i < C::LOADS ? wave + C::NW * i : C::LOADS - 1;
+    if (L < C::LOADS_A) {
+      const int c = 16 * L + (lane >> 2);
+      gp[i] = (JOB ? col[c].X : X + (size_t)(c0 + c) * kKB) + ld_chunk;
+      if constexpr (JOB) colstep[i] = col[c].step;
+    } else {
+      const int64_t r = r0 + 16 * (L - C::LOADS_A) + (lane >> 2);
+      gp[i] = D + (size_t)(JOB ? r : src_row(r, g.n_db, g.row0)) * kKB + ld_chunk;
+      if constexpr (JOB) colstep[i] = stepB;
+    }
   }
-#pragma unroll
-  for (int i = 0; i < C::LB; ++i)
-    gB[i] = D + (size_t)(JOB ? r0 + ld_row + 16 * C::NW * i
-                             : src_row(r0 + ld_row + 16 * C::NW * i, g.n_db, g.row0)) * kKB + ld_chunk;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds + wave * 16 * kKB;
   auto issue = [&](int stage) {
     const uint32_t base = lds0 + stage * C::STAGE;
 #pragma unroll
-    for (int i = 0; i < C::LA; ++i) dma16(gA[i], base + 16 * C::NW * i * kKB);
-#pragma unroll
-    for (int i = 0; i < C::LB; ++i) dma16(gB[i], base + C::PA + 16 * C::NW * i * kKB);
+    for (int i = 0; i < C::NL; ++i)
+      if (C::NW * (i + 1) <= C::LOADS || wave + C::NW * i < C::LOADS) dma16(gp[i], base + 16 * C::NW * i * kKB);
   };
   // The load addresses move on to the next K-block; past the last one the loads repeat it.  One 64-bit addition each,
   // issued among the matrix instructions: the products of block index and stride that stood at the barrier instead
@@ -153,9 +154,8 @@ __device__ __forceinline__ void rns_tile(const RnsTile& g, int8_t* lds, const Rn
     const size_t dA = left > 0 ? stepA : 0, dB = left > 0 ? stepB : 0;
     --left;
 #pragma unroll
-    for (int i = 0; i < C::LA; ++i) gA[i] += JOB ? (left >= 0 ? colstep[i] : 0) : dA;
-#pragma unroll
-    for (int i = 0; i < C::LB; ++i) gB[i] += dB;
+    for (int i = 0; i < C::NL; ++i)
+      gp[i] += JOB ? (left >= 0 ? colstep[i] : 0) : wave + C::NW * i < C::LOADS_A ? dA : dB;
   };
   const int sw = ((lane & 31) >> 2) & 3, cl = lane >> 5;
   const int offA = (wq * 32 * C::WQB + (lane & 31)) * kKB;
@@ -357,30 +357,27 @@ static int wgs_per_cu() {
   const int w = by_lds < by_waves ? by_lds : by_waves;
   return w > 0 ? w : 1;
 }
-int rns_wgs_per_cu(int tq) { return tq == 128 ? wgs_per_cu<128>() : wgs_per_cu<256>(); }
+int rns_wgs_per_cu(int tq) {
+  return tq == 32 ? wgs_per_cu<32>() : tq == 64 ? wgs_per_cu<64>() : tq == 128 ? wgs_per_cu<128>() : wgs_per_cu<256>();
+}
 
-// Query tile of the RNS contraction for a set of problems (d3, R_out, slots): the width whose
-// padded work, weighted by its measured speed per column, is smaller (ties: 256).
-int rns_tile_q(const int64_t* d3, const int64_t* R_out, const int* nz, int n) {
-  double w128 = 0, w256 = 0;
-  for (int i = 0; i < n; ++i) {
-    const double rows = (double)((R_out[i] + kRnsTileR - 1) / kRnsTileR * kRnsTileR) * nz[i];
-    w128 += rows * ((d3[i] + 127) / 128 * 128) * 1.09;
-    w256 += rows * ((d3[i] + 255) / 256 * 256);
-  }
-  return w128 < w256 ? 128 : 256;
+// Query tile of the RNS contraction of d3 columns: 32 or 64 if that holds them all (16 columns, 30,720 rows, K = 20,992
+// in four primes 4.56 ms, 6.2 TB/s, against 4.93 in the 128-column tile, whose products for padding cost power that
+// the loads need; 32 columns, 644 rows 25 us against 37; 48 columns, 4,878 rows 96 against 106); else of 128 and 256
+// the width whose padded work, weighted by its measured time per column, is smaller (ties: 256).
+int rns_tile_q(int64_t d3) {
+  if (d3 <= 64) return d3 <= 32 ? 32 : 64;
+  return (d3 + 127) / 128 * 128 * 1.09 < (d3 + 255) / 256 * 256 ? 128 : 256;
 }
 
 hipError_t launch_gemm_rns(const RnsGemmArgs& g, int tq, hipStream_t s) {
   if (g.R_out <= 0 || g.d3 <= 0) return hipSuccess;
-  if ((tq != 128 && tq != 256) || g.d3_pad % tq != 0) return hipErrorInvalidValue;
+  if ((tq != 32 && tq != 64 && tq != 128 && tq != 256) || g.d3_pad % tq != 0) return hipErrorInvalidValue;
   const int64_t n_ct = (g.d3 + tq - 1) / tq, n_rt = (g.R_out + kRnsTileR - 1) / kRnsTileR;
   if (g.splits < 1 || g.splits > g.KB) return hipErrorInvalidValue;
   const dim3 grid = xcd_grid(n_rt * g.n_mod * g.splits * g.nz, n_ct);
-  if (tq == 128)
-    hipLaunchKernelGGL(k_gemm_rns<128>, grid, dim3(64 * RnsCfg<128>::NW), 0, s, g);
-  else
-    hipLaunchKernelGGL(k_gemm_rns<256>, grid, dim3(64 * RnsCfg<256>::NW), 0, s, g);
+  auto kern = tq == 32 ? k_gemm_rns<32> : tq == 64 ? k_gemm_rns<64> : tq == 128 ? k_gemm_rns<128> : k_gemm_rns<256>;
+  hipLaunchKernelGGL(kern, grid, dim3(tq == 256 ? 64 * RnsCfg<256>::NW : 64 * RnsCfg<128>::NW), 0, s, g);
   return hipGetLastError();
 }
 
