@@ -852,20 +852,20 @@ static LiftArgs make_lift_args(const hfe_keys* K, int level) {
   LiftArgs la;
   std::memset(&la, 0, sizeof(la));
   la.level = level;
-  for (int i = 0; i < level; ++i) {
-    la.q[i] = K->primes[i];
-    la.mu[i] = K->mods[i].mu;
-  }
-  la.p = K->P.p;
-  la.mu_p = K->mods[K->L].mu;
-  garner_consts(K, level, la.garner, la.half_digits);
+  uint64_t garner[HFE_MAX_QPRIMES][HFE_MAX_QPRIMES] = {}, half[HFE_MAX_QPRIMES] = {};
+  garner_consts(K, level, garner, half);
+  la.p = (double)K->P.p;
+  la.pinv = 1.0 / la.p;
   uint64_t prod = 1;
   for (int i = 0; i < level; ++i) {
-    la.mprod_p[i] = prod;
+    la.q[i] = (double)K->primes[i];
+    la.qinv[i] = 1.0 / la.q[i];
+    for (int j = 0; j <= i; ++j) la.garner[i][j] = (double)garner[i][j];
+    la.half_digits[i] = (double)half[i];
+    la.mprod_p[i] = (double)prod;
     prod = mulmod(prod, K->primes[i] % K->P.p, K->P.p);
   }
-  la.mprod_p[level] = prod;
-  la.Q_mod_p = prod;
+  la.Q_mod_p = (double)prod;
   return la;
 }
 
@@ -1837,7 +1837,7 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
       r.elem_begin = resc_e;
       r.ra = make_rescale_args(K, level);
     }
-    lift_e += (cols * D->KB * kKB + 255) / 256 * 256;
+    lift_e += (cols * D->KB * kKB / 4 + 255) / 256 * 256;  // the lift's unit: 4 elements
     resc_e += (d3 * R_item + 255) / 256 * 256;
     z.out_elems += (size_t)level * d3 * R_item;
     z.cols += d3;

@@ -99,24 +99,44 @@ __device__ __forceinline__ bool above_half(const uint64_t* v, const uint64_t* ha
   return gt;
 }
 
+// The centered representative in [-(q - 1)/2, (q - 1)/2] of an integer -(1/2 + 2^-11) q <= x < q, q odd.
+__device__ __forceinline__ double center_c(double x, double q) {
+  const double h = 0.5 * q;
+  x = x > h ? x - q : x;
+  return x < -h ? x + q : x;
+}
+
 // Query element (c, k) of XT ([level][d3][K]): the residues y_i of the lift L(x) = centered
-// CRT value in (-Q/2, Q/2), and lp = L mod p.  Returns false for padding positions (c >= d3 or
-// k >= K), where the lifted value is 0.
+// CRT value in (-Q/2, Q/2), centered, and lp = L mod p, centered.  Returns false, and zeros, for
+// padding positions (c >= d3 or k >= K).  Mixed radix (Garner) on integers held as doubles: a
+// product of two residues is six operations at full rate, where 64-bit integers take eight 32-bit
+// products at a quarter of it and as many again to reduce.
 __device__ __forceinline__ bool lift_residues(const uint64_t* XT, int64_t d3, int64_t K, const LiftArgs& la,
-                                              int64_t c, int64_t k, uint64_t* y, uint64_t& lp) {
-  lp = 0;
+                                              int64_t c, int64_t k, double* y, double& lp) {
+  lp = 0.0;
   if (c >= d3 || k >= K) return false;
+  // loops unrolled to the maximum level, so that y and v stay in registers
+  double v[HFE_MAX_QPRIMES] = {};
 #pragma unroll
-  for (int i = 0; i < HFE_MAX_QPRIMES; ++i)
-    if (i < la.level) y[i] = XT[((int64_t)i * d3 + c) * K + k];
-  uint64_t v[HFE_MAX_QPRIMES] = {};
-  garner_digits(y, la.level, la.garner, la.q, la.mu, v);
-  const uint64_t p = la.p;
-  const uint64_t mup = la.mu_p;
+  for (int i = 0; i < HFE_MAX_QPRIMES; ++i) {
+    if (i >= la.level) break;
+    const double q = la.q[i], qinv = la.qinv[i];
+    y[i] = u2d(XT[((int64_t)i * d3 + c) * K + k]);
+    double s = y[i];
 #pragma unroll
-  for (int i = 0; i < HFE_MAX_QPRIMES; ++i)
-    if (i < la.level) lp = add_mod(lp, mul_mod(barrett64(v[i], p, mup), la.mprod_p[i], p, mup), p);
-  if (above_half(v, la.half_digits, la.level)) lp = sub_mod(lp, la.Q_mod_p, p);
+    for (int j = 0; j < i; ++j) s -= mulmod_c_d(v[j], la.garner[i][j], q, qinv);
+    v[i] = i == 0 ? s : residue_of_c(mulmod_c_d(s, la.garner[i][i], q, qinv), q);
+    lp += i == 0 ? s : mulmod_c_d(v[i], la.mprod_p[i], la.p, la.pinv);
+    y[i] = center_c(y[i], q);
+  }
+  bool neg = false, decided = false;  // L = Y - Q for Y above (Q - 1) / 2
+#pragma unroll
+  for (int i = HFE_MAX_QPRIMES - 1; i >= 0; --i)
+    if (i < la.level && !decided && v[i] != la.half_digits[i]) {
+      neg = v[i] > la.half_digits[i];
+      decided = true;
+    }
+  lp = center_c(reduce_c_d(neg ? lp - la.Q_mod_p : lp, la.p, la.pinv), la.p);
   return true;
 }
 
@@ -125,14 +145,14 @@ __device__ __forceinline__ bool lift_residues(const uint64_t* XT, int64_t d3, in
 __constant__ static RnsModConsts kRnsC = make_rns_mod_consts();
 __constant__ static P2BaseConsts kP2C = make_p2_base_consts();
 
-// x (|x| < 2^40) -> x mod m_j in [-floor(m_j/2), ceil(m_j/2) - 1] for the modulus kRnsMods[j].
-__device__ __forceinline__ int32_t balanced_mod(int64_t x, int j) {
-  return balanced_mod_by(x, kRnsC.m[j], kRnsC.magic[j], kRnsC.t24[j]);
+// An integer |x| < 2^50 -> the byte of its balanced residue modulo kRnsMods[j].
+__device__ __forceinline__ uint32_t balanced_byte(double x, int j) {
+  return (uint32_t)(int32_t)balanced_d(x, kRnsC.md[j], kRnsC.rcp[j]) & 255u;
 }
 
-// Centered x (|x| < 2^48) -> the n^2-form digits (M, M') of base n = kP2Bases[j].
-__device__ __forceinline__ void p2_digits(int64_t x, int j, int32_t& M, int32_t& Mp) {
-  p2_digits_by(x, kP2C.n[j], kP2C.m[j], kP2C.magic_n[j], kP2C.rcp_m[j], M, Mp);
+// An integer |x| < 2^50 -> the n^2-form digits (M, M') of base n = kP2Bases[j].
+__device__ __forceinline__ void p2_digits(double x, int j, int32_t& M, int32_t& Mp) {
+  p2_digits_d(x, kP2C.n[j], kP2C.rcp_n[j], kP2C.m[j], kP2C.rcp_m[j], M, Mp);
 }
 
 // The bytes b of the 4 lanes of a lane quad (lanes 4i .. 4i + 3, lane 4i + e holding byte e),
@@ -155,21 +175,21 @@ __device__ __forceinline__ uint32_t quad_word(uint32_t b) {
 __device__ __forceinline__ void lift_lane(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB, int64_t d3_pad,
                                           const LiftArgs& la, int form, uint64_t* Xp, int8_t* X, int64_t c,
                                           int64_t k) {
-  uint64_t y[HFE_MAX_QPRIMES] = {};
-  uint64_t lp;
+  double y[HFE_MAX_QPRIMES] = {};
+  double lp;
   const bool valid = lift_residues(XT, d3, K, la, c, k, y, lp);
-  if (valid && Xp) Xp[c * K + k] = lp;
+  if (valid && Xp) Xp[c * K + k] = d2u(residue_of_c(lp, la.p));
   if (!X) return;
   const bool writer = (threadIdx.x & 3) == 0;
   const int64_t kb = k / kKB, kk = k % kKB - (k & 3);
   const int planes = form == 0 ? kDigits : form > 0 ? form : -2 * form;
   const int64_t pstride = KB * d3_pad * kKB / 4;  // words between consecutive planes
   // the planes of prime slot z (the level's primes, then p) for centered value x
-  auto emit = [&](int z, int64_t x) {
+  auto emit = [&](int z, double x) {
     uint32_t* row = reinterpret_cast<uint32_t*>(X + (((int64_t)z * planes * KB + kb) * d3_pad + c) * kKB + kk);
     if (form == 0) {
       int32_t d[kDigits];
-      split5(x, d);
+      split5(d2i(x), d);
 #pragma unroll
       for (int t = 0; t < kDigits; ++t) {
         const uint32_t w = quad_word((uint32_t)d[t]);
@@ -177,7 +197,7 @@ __device__ __forceinline__ void lift_lane(const uint64_t* XT, int64_t d3, int64_
       }
     } else if (form > 0) {
       for (int j = 0; j < form; ++j) {
-        const uint32_t w = quad_word((uint32_t)balanced_mod(x, j));
+        const uint32_t w = quad_word(balanced_byte(x, j));
         if (writer) row[j * pstride] = w;
       }
     } else {
@@ -195,11 +215,77 @@ __device__ __forceinline__ void lift_lane(const uint64_t* XT, int64_t d3, int64_
 #pragma unroll
   for (int z = 0; z < HFE_MAX_QPRIMES; ++z) {
     if (z >= la.level) break;
-    emit(z, valid ? centered(y[z], la.q[z]) : 0);
+    emit(z, y[z]);
   }
-  emit(la.level, valid ? centered(lp, la.p) : 0);
+  emit(la.level, lp);
 }
 
+// The same for elements (c, k .. k + 3), k a multiple of 4, by one lane, which makes a wave's store 256 consecutive bytes
+// of a column instead of 64.  The stores bound the forms of many planes: 44 planes of 512 columns, K = 20,992 281 us a
+// lane to an element, 224 by this (501 with both in 64-bit integers); twelve requests' 784 columns in a batch 1,015 and
+// 573 (1,210).  The longer chain of a lane costs the five digit planes and small calls more than that: 5,120 x 128
+// digits 6 and 9 us, 11 planes x 3 of 5,312 x 32 elements 9 and 12; from 2^18 elements on it pays (15,488 x 32: 16.1
+// and 14.6).
+__device__ __forceinline__ void lift_quad(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB, int64_t d3_pad,
+                                          const LiftArgs& la, int form, uint64_t* Xp, int8_t* X, int64_t c,
+                                          int64_t k) {
+  double y[4][HFE_MAX_QPRIMES] = {};
+  double lp[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const bool valid = lift_residues(XT, d3, K, la, c, k + e, y[e], lp[e]);
+    if (valid && Xp) Xp[c * K + k + e] = d2u(residue_of_c(lp[e], la.p));
+  }
+  if (!X) return;
+  const int64_t kb = k / kKB, kk = k % kKB;
+  const int planes = form == 0 ? kDigits : form > 0 ? form : -2 * form;
+  const int64_t pstride = KB * d3_pad * kKB / 4;  // words between consecutive planes
+  // the planes of prime slot z (the level's primes, then p) for four centered values
+  auto emit = [&](int z, double x0, double x1, double x2, double x3) {
+    const double x[4] = {x0, x1, x2, x3};
+    uint32_t* row = reinterpret_cast<uint32_t*>(X + (((int64_t)z * planes * KB + kb) * d3_pad + c) * kKB + kk);
+    if (form == 0) {
+      uint32_t w[kDigits] = {};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int32_t d[kDigits];
+        split5(d2i(x[e]), d);
+#pragma unroll
+        for (int t = 0; t < kDigits; ++t) w[t] |= ((uint32_t)d[t] & 255u) << (8 * e);
+      }
+#pragma unroll
+      for (int t = 0; t < kDigits; ++t) row[t * pstride] = w[t];
+    } else if (form > 0) {
+      for (int j = 0; j < form; ++j) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w |= balanced_byte(x[e], j) << (8 * e);
+        row[j * pstride] = w;
+      }
+    } else {
+      for (int j = 0; j < -form; ++j) {
+        uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          int32_t M, Mp;
+          p2_digits(x[e], j, M, Mp);
+          w0 |= ((uint32_t)M & 255u) << (8 * e);
+          w1 |= ((uint32_t)Mp & 255u) << (8 * e);
+        }
+        row[2 * j * pstride] = w0;
+        row[(2 * j + 1) * pstride] = w1;
+      }
+    }
+  };
+#pragma unroll
+  for (int z = 0; z < HFE_MAX_QPRIMES; ++z) {
+    if (z >= la.level) break;
+    emit(z, y[0][z], y[1][z], y[2][z], y[3][z]);
+  }
+  emit(la.level, lp[0], lp[1], lp[2], lp[3]);
+}
+
+constexpr int64_t kLiftQuadFrom = 1 << 18;  // elements of a call
 
 // CRT of one entry (see k_crt_rns): residues r[j n] mod m_j -> the exact centered sum mod the prime
 // of database slot `slot`.
@@ -293,10 +379,11 @@ __device__ __forceinline__ SplitAt split_at() {
   return {(int64_t)blockIdx.x * kSplitRows + (threadIdx.x >> 2), (int64_t)blockIdx.y, (int)(threadIdx.x & 3)};
 }
 __device__ __forceinline__ void split_load(const SplitAt& at, const uint64_t* Dt, int64_t K, int64_t R, uint64_t q,
-                                           int64_t (&x)[16]) {
+                                           double (&x)[16]) {
   const int64_t k0 = at.kb * kKB + 16 * at.h;
+  const double qd = (double)q;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) x[i] = at.r < R && k0 + i < K ? centered(Dt[(k0 + i) * R + at.r], q) : 0;
+  for (int i = 0; i < 16; ++i) x[i] = at.r < R && k0 + i < K ? center_c(u2d(Dt[(k0 + i) * R + at.r]), qd) : 0.0;
 }
 __device__ __forceinline__ void split_store(const SplitAt& at, int8_t* planes, int64_t plane, int64_t KB, int64_t R_pad,
                                             const uint32_t (&w)[4]) {

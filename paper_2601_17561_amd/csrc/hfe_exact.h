@@ -15,6 +15,19 @@
 namespace hfe {
 
 // ------------------------------------------------------------------ fp64 residues mod q < 2^36
+// Integers in [0, 2^52) between uint64 and double through the bits of 2^52 + x (two instructions; the
+// compiler's general 64-bit conversions take about ten).
+HFE_HD double u2d(uint64_t x) {
+  return __builtin_bit_cast(double, x | 0x4330000000000000ull) - 4503599627370496.0;
+}
+HFE_HD uint64_t d2u(double x) {
+  return __builtin_bit_cast(uint64_t, x + 4503599627370496.0) & 0xfffffffffffffull;
+}
+
+// an integer of magnitude below 2^51
+HFE_HD int64_t d2i(double x) {
+  return __builtin_bit_cast(int64_t, x + 6755399441055744.0) - 0x4338000000000000ll;
+}
 // Residues as doubles holding exact integers in [0, q).
 // a w mod q for a, w in [0, q), q < 2^36, qinv = RN(1/q): hi = RN(a w) is an integer and
 // lo = a w - hi (|lo| <= 2^18) is exact from one fused multiply-add; t = floor(hi qinv) is within one
@@ -113,9 +126,10 @@ constexpr int kRnsMaxMods = 16;
 constexpr int32_t kRnsMods[kRnsMaxMods] = {256, 255, 253, 251, 247, 241, 239, 233,
                                            229, 227, 223, 211, 199, 197, 193, 191};
 
-// Per small modulus m_j: m_j, ceil(2^32 / m_j) and 2^24 mod m_j.
+// Per small modulus m_j: m_j, ceil(2^32 / m_j), 2^24 mod m_j, and m_j and RN(1 / m_j) as doubles.
 struct RnsModConsts {
   uint32_t m[kRnsMaxMods], magic[kRnsMaxMods], t24[kRnsMaxMods];
+  double md[kRnsMaxMods], rcp[kRnsMaxMods];
 };
 constexpr RnsModConsts make_rns_mod_consts() {
   RnsModConsts c{};
@@ -124,8 +138,20 @@ constexpr RnsModConsts make_rns_mod_consts() {
     c.m[j] = (uint32_t)m;
     c.magic[j] = (uint32_t)(((1ull << 32) + m - 1) / m);
     c.t24[j] = (uint32_t)((1ull << 24) % m);
+    c.md[j] = (double)m;
+    c.rcp[j] = 1.0 / (double)m;
   }
   return c;
+}
+
+// The same residues in double precision, four operations at the full rate where the integer form (which the CPU checks
+// compare this with) takes five 32-bit products at a quarter of it: for an integer |x| < 2^50, x rcp is within 2^-51 |x|
+// / m of x / m, less than the 1 / (2m) by which x / m of an odd m stays away from every half-integer, so rint gives the
+// nearest multiple and the fused multiply-add the exact balanced residue.  For m = 256 the product is exact and a tie
+// may give +128 for -128, which is the same byte.
+HFE_HD double balanced_d(double x, double m, double rcp) {
+#pragma clang fp contract(off)
+  return __builtin_fma(-__builtin_rint(x * rcp), m, x);
 }
 
 // x (|x| < 2^40) -> x mod m in [-floor(m/2), ceil(m/2) - 1]: |x| = hi 2^24 + lo (hi < 2^16), and
@@ -196,6 +222,17 @@ HFE_HD void p2_digits_by(int64_t x, int32_t n, int32_t nsq, uint32_t magic, doub
   int32_t t = (int32_t)umulhi32(rm, magic);         // (r - M) / n, exact
   if (t == n) t = 0;
   Mp = t > h ? t - n : t;
+}
+
+// The same digits in double precision, for an odd n <= 251 and an integer |x| < 2^50: r = x - n^2 rint(x / n^2) is the
+// balanced residue (balanced_d), t = rint(r / n) its nearest multiple of n, M = r - n t; |t| <= (n - 1)/2 because |r| <=
+// (n^2 - 1)/2, so M' = t.
+HFE_HD void p2_digits_d(double x, double n, double rcp_n, double nsq, double rcp_nsq, int32_t& M, int32_t& Mp) {
+#pragma clang fp contract(off)
+  const double r = balanced_d(x, nsq, rcp_nsq);
+  const double t = __builtin_rint(r * rcp_n);
+  M = (int32_t)__builtin_fma(-t, n, r);
+  Mp = (int32_t)t;
 }
 
 // The contraction epilogue of the n^2 form: from the int32 sums G0 = sum M N and G1 = sum (M N' + M' N),

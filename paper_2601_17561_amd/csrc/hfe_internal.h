@@ -276,15 +276,14 @@ hipError_t launch_split_db(const uint64_t* Dt_prime, int64_t K, int64_t R, int64
 // Centered CRT lift of the query from Q_level to p, plus the int8 digit planes of every
 // prime of the level and p.  XT: [level][d3][K].  Outputs: Xp [d3][K] (lift mod p, may be
 // null) and Xd [level+1][5][KB][d3_pad][64] (may be null).
-struct LiftArgs {
+struct LiftArgs {  // integers, held as doubles
   int level;
-  uint64_t q[HFE_MAX_QPRIMES];
-  uint64_t mu[HFE_MAX_QPRIMES];                       // floor(2^64 / q_i)
-  uint64_t p, mu_p;
-  uint64_t garner[HFE_MAX_QPRIMES][HFE_MAX_QPRIMES];  // [i][j<i]: q_0..q_{j-1} mod q_i; [i][i]: inverse
-  uint64_t mprod_p[HFE_MAX_QPRIMES + 1];              // q_0..q_{i-1} mod p
-  uint64_t half_digits[HFE_MAX_QPRIMES];              // mixed-radix digits of (Q-1)/2
-  uint64_t Q_mod_p;
+  double q[HFE_MAX_QPRIMES], qinv[HFE_MAX_QPRIMES];
+  double p, pinv;
+  double garner[HFE_MAX_QPRIMES][HFE_MAX_QPRIMES];    // [i][j<i]: q_0..q_{j-1} mod q_i; [i][i]: inverse
+  double mprod_p[HFE_MAX_QPRIMES];                    // q_0..q_{i-1} mod p
+  double half_digits[HFE_MAX_QPRIMES];                // mixed-radix digits of (Q-1)/2
+  double Q_mod_p;
 };
 hipError_t launch_lift(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB, int64_t d3_pad,
                        const LiftArgs& la, uint64_t* Xp, int8_t* Xd, hipStream_t s);
@@ -607,7 +606,7 @@ struct BatchLiftDesc {               // one per item
   int8_t* Xd;                     // its problem's [level + 1][planes][KB][d3_pad][64]
   int64_t d3, c0, cols;           // item columns, first column in the problem, columns written
                                   // (d3, plus the problem's padding for its last item)
-  int64_t d3_pad, elem_begin;     // elements: cols x KB*64
+  int64_t d3_pad, elem_begin;     // elements: cols x KB*64, four to each
   LiftArgs la;
 };
 struct BatchRescaleDesc {            // one per item

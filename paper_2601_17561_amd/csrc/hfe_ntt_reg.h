@@ -42,19 +42,6 @@ __device__ __forceinline__ gptr<T> as_global(const T* p) {
   return (gptr<T>)(p);
 }
 
-// Integers in [0, 2^52) between uint64 and double through the bits of 2^52 + x (two instructions; the
-// compiler's general 64-bit conversions take about ten).
-__device__ __forceinline__ double u2d(uint64_t x) {
-  return __longlong_as_double((long long)(x | 0x4330000000000000ull)) - 4503599627370496.0;
-}
-__device__ __forceinline__ uint64_t d2u(double x) {
-  return (uint64_t)__double_as_longlong(x + 4503599627370496.0) & 0xfffffffffffffull;
-}
-
-// an integer of magnitude below 2^51
-__device__ __forceinline__ int64_t d2i(double x) {
-  return (int64_t)__double_as_longlong(x + 6755399441055744.0) - 0x4338000000000000ll;
-}
 // the residue in [0, q) of an integer below 2^47 in magnitude
 __device__ __forceinline__ uint64_t d2residue(double x, double q, double qinv) {
   return d2u(residue_of_c(reduce_c_d(x, q, qinv), q));

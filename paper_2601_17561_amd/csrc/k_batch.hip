@@ -30,16 +30,23 @@ __global__ void __launch_bounds__(kChunk) k_lift_batched(const BatchElemHeader* 
   const int n = hdr->n;
   for (int i = threadIdx.x; i < n; i += blockDim.x) begins[i] = d[i].elem_begin;
   __syncthreads();
-  const int64_t total = hdr->total, kpad = KB * kKB;
+  const int64_t total = hdr->total, kq = KB * kKB / 4;  // four elements to a thread
+  const double rcp = 1.0 / (double)kq;  // e < 2^53 and a quotient below 2^50: the product is within one of it
   for (int64_t base = (int64_t)blockIdx.x * kChunk; base < total; base += (int64_t)gridDim.x * kChunk) {
     const int b = find_problem(begins, n, base);
     const BatchLiftDesc& p = d[b];
     const int64_t e = base + threadIdx.x - p.elem_begin;
-    // whole lane quads pass (cols x kpad is a multiple of 4), as the lift's packing needs
-    if (e >= p.cols * kpad) continue;
+    if (e >= p.cols * kq) continue;
     // columns c >= p.d3 are the problem's padding: lift_residues reports them invalid (zero)
-    const int64_t c = e / kpad;
-    lift_lane(p.XT, p.d3, K, KB, p.d3_pad, p.la, form, nullptr, p.Xd + p.c0 * kKB, c, e - c * kpad);
+    int64_t c = (int64_t)((double)e * rcp), k = e - c * kq;  // e / kq within one, corrected
+    if (k < 0) {
+      --c;
+      k += kq;
+    } else if (k >= kq) {
+      ++c;
+      k -= kq;
+    }
+    lift_quad(p.XT, p.d3, K, KB, p.d3_pad, p.la, form, nullptr, p.Xd + p.c0 * kKB, c, 4 * k);
   }
 }
 

@@ -25,13 +25,13 @@ __global__ void __launch_bounds__(256) k_chain_split_db(const uint64_t* Dt, int6
                                                         int64_t R_pad, ChainBase b, int8_t* planes) {
   const SplitAt at = split_at();
   if (at.r >= R_pad) return;
-  int64_t x[16];
+  double x[16];
   split_load(at, Dt, K, R, (uint64_t)b.m, x);
   uint32_t w0[4] = {}, w1[4] = {};
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     int32_t M, Mp;
-    p2_digits_by(x[i], b.n, b.m, b.magic_n, b.rcp_m, M, Mp);
+    p2_digits_d(x[i], b.n, b.rcp_n, b.m, b.rcp_m, M, Mp);
     w0[i >> 2] |= ((uint32_t)M & 255u) << (8 * (i & 3));
     w1[i >> 2] |= ((uint32_t)Mp & 255u) << (8 * (i & 3));
   }

@@ -98,13 +98,13 @@ __global__ void __launch_bounds__(256) k_split_db(const uint64_t* Dt, int64_t K,
                                                   int64_t R_pad, uint64_t q, int8_t* dig) {
   const SplitAt at = split_at();
   if (at.r >= R_pad) return;
-  int64_t x[16];
+  double x[16];
   split_load(at, Dt, K, R, q, x);
   uint32_t w[kDigits][4] = {};
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     int32_t d[kDigits];
-    split5(x[i], d);
+    split5(d2i(x[i]), d);
 #pragma unroll
     for (int t = 0; t < kDigits; ++t) w[t][i >> 2] |= ((uint32_t)(d[t] & 255)) << (8 * (i & 3));
   }

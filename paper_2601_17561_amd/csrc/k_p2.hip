@@ -14,7 +14,7 @@ __global__ void __launch_bounds__(256) k_split_db_p2(const uint64_t* Dt, int64_t
                                                      int64_t R_pad, uint64_t q, int n_bases, int8_t* planes) {
   const SplitAt at = split_at();
   if (at.r >= R_pad) return;
-  int64_t x[16];
+  double x[16];
   split_load(at, Dt, K, R, q, x);
   for (int j = 0; j < n_bases; ++j) {
     uint32_t w0[4] = {}, w1[4] = {};
@@ -41,18 +41,24 @@ hipError_t launch_split_db_p2(const uint64_t* Dt_prime, int64_t K, int64_t R, in
 // Element (c, k): the lift of the query residues (as for the digit form), then for every prime of
 // the level and p the digits M, M' of the centered value for each base: Xq[z][2j + t][kb][c][kk],
 // zero in the padding.
+template <bool QUAD>
 __global__ void __launch_bounds__(256) k_lift_p2(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB,
                                                  int64_t d3_pad, LiftArgs la, int n_bases, int8_t* Xq) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = (QUAD ? 4 : 1) * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (k >= KB * kKB) return;
-  lift_lane(XT, d3, K, KB, d3_pad, la, -n_bases, nullptr, Xq, blockIdx.y, k);
+  if constexpr (QUAD)
+    lift_quad(XT, d3, K, KB, d3_pad, la, -n_bases, nullptr, Xq, blockIdx.y, k);
+  else
+    lift_lane(XT, d3, K, KB, d3_pad, la, -n_bases, nullptr, Xq, blockIdx.y, k);
 }
 
 hipError_t launch_lift_p2(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB, int64_t d3_pad,
                           const LiftArgs& la, int n_bases, int8_t* Xq, hipStream_t s) {
   if (n_bases < 1 || n_bases > kP2MaxBases) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((KB * kKB + 255) / 256), (unsigned)d3_pad);
-  hipLaunchKernelGGL(k_lift_p2, grid, dim3(256), 0, s, XT, d3, K, KB, d3_pad, la, n_bases, Xq);
+  const bool quad = KB * kKB * d3_pad >= kLiftQuadFrom;
+  const int64_t per_block = quad ? 1024 : 256;
+  dim3 grid((unsigned)((KB * kKB + per_block - 1) / per_block), (unsigned)d3_pad);
+  hipLaunchKernelGGL(quad ? k_lift_p2<true> : k_lift_p2<false>, grid, dim3(256), 0, s, XT, d3, K, KB, d3_pad, la, n_bases, Xq);
   return hipGetLastError();
 }
 

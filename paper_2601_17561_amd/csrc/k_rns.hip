@@ -14,12 +14,12 @@ __global__ void __launch_bounds__(256) k_split_db_rns(const uint64_t* Dt, int64_
                                                       int64_t R_pad, uint64_t q, int n_mod, int8_t* dig) {
   const SplitAt at = split_at();
   if (at.r >= R_pad) return;
-  int64_t x[16];
+  double x[16];
   split_load(at, Dt, K, R, q, x);
   for (int j = 0; j < n_mod; ++j) {
     uint32_t w[4] = {};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w[i >> 2] |= ((uint32_t)(balanced_mod(x[i], j) & 255)) << (8 * (i & 3));
+    for (int i = 0; i < 16; ++i) w[i >> 2] |= balanced_byte(x[i], j) << (8 * (i & 3));
     split_store(at, dig, j, KB, R_pad, w);
   }
 }
@@ -34,17 +34,23 @@ hipError_t launch_split_db_rns(const uint64_t* Dt_prime, int64_t K, int64_t R, i
 // Element (c, k): the lift of the query residues (as for the digit form), then for every prime of
 // the level and p the balanced residues of the centered value modulo each small modulus:
 // Xr[z][j][kb][c][kk], zero in the padding.
+template <bool QUAD>
 __global__ void __launch_bounds__(256) k_lift_rns(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB,
                                                   int64_t d3_pad, LiftArgs la, int n_mod, int8_t* Xr) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = (QUAD ? 4 : 1) * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
   if (k >= KB * kKB) return;
-  lift_lane(XT, d3, K, KB, d3_pad, la, n_mod, nullptr, Xr, blockIdx.y, k);
+  if constexpr (QUAD)
+    lift_quad(XT, d3, K, KB, d3_pad, la, n_mod, nullptr, Xr, blockIdx.y, k);
+  else
+    lift_lane(XT, d3, K, KB, d3_pad, la, n_mod, nullptr, Xr, blockIdx.y, k);
 }
 
 hipError_t launch_lift_rns(const uint64_t* XT, int64_t d3, int64_t K, int64_t KB, int64_t d3_pad,
                            const LiftArgs& la, int n_mod, int8_t* Xr, hipStream_t s) {
-  dim3 grid((unsigned)((KB * kKB + 255) / 256), (unsigned)d3_pad);
-  hipLaunchKernelGGL(k_lift_rns, grid, dim3(256), 0, s, XT, d3, K, KB, d3_pad, la, n_mod, Xr);
+  const bool quad = KB * kKB * d3_pad >= kLiftQuadFrom;
+  const int64_t per_block = quad ? 1024 : 256;
+  dim3 grid((unsigned)((KB * kKB + per_block - 1) / per_block), (unsigned)d3_pad);
+  hipLaunchKernelGGL(quad ? k_lift_rns<true> : k_lift_rns<false>, grid, dim3(256), 0, s, XT, d3, K, KB, d3_pad, la, n_mod, Xr);
   return hipGetLastError();
 }
 

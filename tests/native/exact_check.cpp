@@ -250,4 +250,13 @@ void xc_crt(const uint32_t* s, int64_t cnt, int nm, const uint32_t* m, const uin
   }
 }
 
+
+// the double-precision forms of the small-modulus residues and of the n^2-form digits
+void xc_balanced_d(const int64_t* x, int64_t n, int j, int32_t* out) {
+  for (int64_t i = 0; i < n; ++i) out[i] = (int32_t)balanced_d((double)x[i], kRns.md[j], kRns.rcp[j]);
+}
+void xc_p2_digits_d(const int64_t* x, int64_t n, int32_t base, int32_t* M, int32_t* Mp) {
+  const double b = base, m = b * b;
+  for (int64_t i = 0; i < n; ++i) p2_digits_d((double)x[i], b, 1.0 / b, m, 1.0 / m, M[i], Mp[i]);
+}
 }  // extern "C"

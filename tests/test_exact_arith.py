@@ -402,3 +402,39 @@ def test_transform_domain_order_is_a_permutation(log_n, acc):
     point, back = np.empty(n, dtype=np.int32), np.empty(n, dtype=np.int32)
     _L.xc_ntt_order(log_n, acc, _ptr(point), _ptr(back))
     assert np.array_equal(np.sort(point), np.arange(n)) and np.array_equal(back[point], np.arange(n))
+
+
+_L.xc_balanced_d.argtypes = [_p, ctypes.c_int64, ctypes.c_int, _p]
+_L.xc_balanced_d.restype = None
+_L.xc_p2_digits_d.argtypes = [_p, ctypes.c_int64, ctypes.c_int32, _p, _p]
+_L.xc_p2_digits_d.restype = None
+
+
+# every form of the range: around multiples and half-multiples of the modulus, to the documented end 2^50
+@pytest.mark.parametrize("j", range(16))
+def test_balanced_residue_in_doubles_is_the_integer_form_byte_for_byte(j):
+    m = RNS_MODS[j]
+    rng = np.random.default_rng(600 + j)
+    k = rng.integers(-((1 << 40) // m), (1 << 40) // m, 40_000, dtype=np.int64) * m
+    X = np.concatenate([k + d for d in (-1, 0, 1, m // 2 - 1, m // 2, m // 2 + 1)] + [rng.integers(-(1 << 40) + 1, 1 << 40, 100_000)])
+    X = X[np.abs(X) < 1 << 40]
+    got, want = np.empty(len(X), dtype=np.int32), np.empty(len(X), dtype=np.int32)
+    _L.xc_balanced_d(_ptr(X), len(X), j, _ptr(got))
+    _L.xc_balanced_mod(_ptr(X), len(X), j, _ptr(want))
+    assert np.array_equal(got & 255, want & 255)
+    big = rng.integers(-(1 << 50) + 1, 1 << 50, 50_000)
+    out = np.empty(len(big), dtype=np.int32)
+    _L.xc_balanced_d(_ptr(big), len(big), j, _ptr(out))
+    assert np.abs(out).max() <= m // 2 and not ((big - out) % m).any()
+
+
+@pytest.mark.parametrize("n", [3, 5, 127, 199, 211, 239, 249, 251])
+def test_p2_digits_in_doubles_are_the_integer_form(n):
+    rng = np.random.default_rng(700 + n)
+    k = rng.integers(-((1 << 47) // (n * n)), (1 << 47) // (n * n), 20_000, dtype=np.int64) * (n * n)
+    h = n * n // 2
+    X = np.concatenate([k + d for d in (-1, 0, 1, n // 2, n // 2 + 1, h, h + 1)] + [np.arange(n * n, dtype=np.int64) - h])
+    got, want = np.empty((2, len(X)), dtype=np.int32), np.empty((2, len(X)), dtype=np.int32)
+    _L.xc_p2_digits_d(_ptr(X), len(X), n, _ptr(got[0]), _ptr(got[1]))
+    _L.xc_p2_digits_n(_ptr(X), len(X), n, _ptr(want[0]), _ptr(want[1]))
+    assert np.array_equal(got, want)
