@@ -16,6 +16,8 @@
 // register-resident NTT (hfe_ntt_reg.h) of d_r per (digit, part, slot) and a pointwise multiply-accumulate held in
 // registers, and one inverse transform per result.  Every value is the exact residue that the full
 // key switch followed by the extraction gives.
+#include <algorithm>
+
 #include "hfe_ntt_reg.h"
 
 namespace hfe {
@@ -273,30 +275,27 @@ hipError_t launch_fs_tx(const FsConsts& C, uint64_t seed, const int8_t* m_q, int
 // ------------------------------------------------------------------ the switch
 // Digits d_i = [a (Q'/q_i)^-1]_{q_i} of every mask a, in polyphase order: Dg[col][i][r][u] is the
 // digit of coefficient rho u + r.
-__global__ void k_fs_digits(FsConsts C, const uint64_t* T, int64_t ncols, double* Dg) {
-  const int nq = 1 << C.logn_q;
-  const int64_t nt = (int64_t)nq * C.rho;
+// A thread takes RUN = min(rho, 8) coefficients rho u + RUN b .. of one u, consecutive threads consecutive u, and writes
+// part r at r N_Q + u: both sides in whole lines.  Fewer than 4,096 polynomials are split over blockIdx.y, at least four
+// items to a thread: a block to a polynomial of 2^16 left the chip idle, and rho != 8 scattered its writes (302
+// polynomials of 2^16 in parts of 2^11 240 us, now 67; 1,206 in parts of 2^10 1,289 and 366).
+template <int RUN>
+__global__ void __launch_bounds__(256) k_fs_digits(FsConsts C, const uint64_t* T, int64_t ncols, double* Dg) {
+  const int64_t nt = (int64_t)C.rho << C.logn_q;
   const int64_t col = blockIdx.x / (C.level + 1);
   const int i = (int)(blockIdx.x - col * (C.level + 1));
   const double q = C.zd[i], qinv = C.zinv[i], g = C.ghat[i];
   const uint64_t* a = T + ((size_t)i * ncols + col) * 2 * nt;
   double* o = Dg + ((size_t)col * (C.level + 1) + i) * nt;
-  // thread u takes the rho coefficients u rho .. u rho + rho - 1 (contiguous across the wavefront) and writes
-  // part r at r N_Q + u (consecutive u across the wavefront): both sides coalesced
-  if (C.rho == 8) {
-    for (int u = threadIdx.x; u < nq; u += blockDim.x) {
-      const uint64_t* src = a + (int64_t)u * 8;
-      uint64_t x[8];
+  const int items = (int)(nt / RUN);
+  for (int t = blockIdx.y * 256 + threadIdx.x; t < items; t += gridDim.y * 256) {
+    const int u = t & ((1 << C.logn_q) - 1), r0 = (t >> C.logn_q) * RUN;
+    const uint64_t* src = a + (int64_t)u * C.rho + r0;
+    uint64_t x[RUN];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) x[r] = src[r];
+    for (int r = 0; r < RUN; ++r) x[r] = src[r];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) o[(int64_t)r * nq + u] = mulmod_d(to_d(x[r]), g, q, qinv);
-    }
-    return;
-  }
-  for (int64_t t = threadIdx.x; t < nt; t += blockDim.x) {
-    const int64_t u = t / C.rho, r = t - u * C.rho;
-    o[r * nq + u] = mulmod_d(to_d(a[t]), g, q, qinv);
+    for (int r = 0; r < RUN; ++r) o[((int64_t)(r0 + r) << C.logn_q) + u] = mulmod_d(to_d(x[r]), g, q, qinv);
   }
 }
 
@@ -500,7 +499,10 @@ hipError_t launch_fs_switch(const FsConsts& C, const uint64_t* T, int64_t d3, co
   const int nq = 1 << C.logn_q;
   if (ev) (void)hipEventRecord(ev[0], s);
   {
-    hipLaunchKernelGGL(k_fs_digits, dim3((unsigned)(ncols * (C.level + 1))), dim3(256), 0, s, C, T, ncols, w.Dg);
+    auto kern = C.rho >= 8 ? k_fs_digits<8> : C.rho == 4 ? k_fs_digits<4> : C.rho == 2 ? k_fs_digits<2> : k_fs_digits<1>;
+    const int run = C.rho >= 8 ? 8 : C.rho, items = C.rho / run << C.logn_q;
+    const int64_t polys = ncols * (C.level + 1), parts = std::clamp<int64_t>(4096 / polys, 1, (items + 1023) / 1024);
+    hipLaunchKernelGGL(kern, dim3((unsigned)polys, (unsigned)parts), dim3(256), 0, s, C, T, ncols, w.Dg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
