@@ -15,6 +15,8 @@ constexpr NttPlan ntt_plan(int L, int e) {
          : L == 14 && e == 4 ? NttPlan{4, {4, 4, 3, 3}, {10, 6, 3}, {0, 8, 1}}
          : L == 13 && e == 5 ? NttPlan{3, {5, 4, 4, 0}, {8, 4, 0}, {16, 1, 0}}
          : L == 13 && e == 4 ? NttPlan{4, {4, 3, 3, 3}, {9, 6, 3}, {0, 8, 1}}
+         : L == 11 && e == 3 ? NttPlan{4, {3, 3, 3, 2}, {8, 5, 4}, {0, 4, 1}}
+         : L == 10 && e == 3 ? NttPlan{4, {3, 3, 2, 2}, {5, 5, 2}, {4, 4, 1}}
          : L == 12           ? NttPlan{3, {4, 4, 4, 0}, {8, 4, 0}, {16, 1, 0}}
          : L == 11           ? NttPlan{3, {4, 4, 3, 0}, {7, 5, 0}, {8, 1, 0}}
          : L == 10           ? NttPlan{3, {4, 3, 3, 0}, {6, 3, 0}, {8, 1, 0}}
@@ -25,7 +27,7 @@ constexpr int kRegLogMin = 9, kRegLogMax = 14;
 
 // The bit-reversed point that index i (r TH + t) of the transform domain holds, in by_ntt's order (acc = false) or
 // by_ntt_acc's, and the index of a point.
-__host__ __device__ constexpr int ntt_e(int logn, bool acc) { return acc && logn >= 13 ? 4 : ntt_def_e(logn); }
+__host__ __device__ constexpr int ntt_e(int logn, bool acc) { return acc && logn >= 13 ? 4 : acc && (logn == 10 || logn == 11) ? 3 : ntt_def_e(logn); }
 __host__ __device__ inline int ntt_point(int logn, bool acc, int i) {
   if (logn < kRegLogMin || logn > kRegLogMax) return i;
   const int e = ntt_e(logn, acc), lt = logn - e;

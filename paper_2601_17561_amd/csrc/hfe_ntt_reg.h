@@ -385,7 +385,10 @@ constexpr int ntt_waves(int E, int polys) {
 
 // f(X{}, block size) with the transform of degree 2^logn (logn <= kRegLogMax).  by_ntt_acc: at most 16 values per
 // thread (four rounds at 2^13 and 2^14), for the kernels that keep sums of two or more polynomials in registers
-// beside the transform.  The two differ in the order of the transform domain at 2^13 and 2^14.
+// beside the transform, and 8 at 2^10 and 2^11 (four rounds), where 16 left 64 and 128 threads to a polynomial and the
+// chip short of waves: ring switch of 151 columns at 2^11, 64 terms 336 and 253 us, conversion of 113 columns 88 and 54;
+// of 56 columns at 2^10 50 and 36, 32 and 17 (402 columns: 1,007 and 1,059, 62 and 45).  At 2^12 8 values lose (ring
+// switch 96 and 134 us).  The two differ in the order of the transform domain at 2^10, 2^11, 2^13 and 2^14.
 template <class F>
 static hipError_t by_ntt_upto12(int logn, F f) {
   switch (logn) {
@@ -408,6 +411,8 @@ static hipError_t by_ntt(int logn, F f) {
 template <class F>
 static hipError_t by_ntt_acc(int logn, F f) {
   switch (logn) {
+    case 10: return f(RegNtt<10, 3>{}, RegNtt<10, 3>::TH);
+    case 11: return f(RegNtt<11, 3>{}, RegNtt<11, 3>::TH);
     case 13: return f(RegNtt<13, 4>{}, RegNtt<13, 4>::TH);
     case 14: return f(RegNtt<14, 4>{}, RegNtt<14, 4>::TH);
     default: return by_ntt_upto12(logn, f);
