@@ -79,7 +79,7 @@ typedef enum { HFE_FORM_PLAIN_U64 = 1, HFE_FORM_I8_MFMA = 2, HFE_FORM_RNS_I8 = 4
 
 typedef struct {
   uint32_t log_n_db;              /* N_DB = 2^log_n_db, database ring degree, 1..16 (up  */
-                                  /* to 2^14 one LDS-resident transform per polynomial,  */
+                                  /* to 2^14 one workgroup's transform per polynomial,   */
                                   /* 2^15 and 2^16 two passes through device memory)     */
   uint32_t log_n_q;               /* N_Q = 2^log_n_q, query ring degree, 1..16           */
   uint32_t n_q_primes;            /* L, query primes carried by the database, 1..8       */

@@ -369,7 +369,8 @@ __device__ __forceinline__ void rescale_from(const uint64_t* src, int64_t zstrid
 // the block, and writes them as 16 bytes of each plane's row.  Four lanes share a row, so a wave reads 128 consecutive
 // bytes of four k at a time and writes whole 1 KiB runs; a thread to a row (64 residues, a 64-byte row per plane in
 // four 16-byte pieces at 64-byte strides) took 2.93 ms for the digits of 20,992 x 30,720 residues, this takes 1.62 (5.2
-// TB/s: memory bounds it); 11 small moduli of 11,818 x 10,021 923 and 670 us (their reductions), six n^2 bases 405 and 197.
+// TB/s: memory bounds it); 11 small moduli of 11,818 x 10,021 923 and, with the residues in doubles, 471 us; six n^2
+// bases 405 and 115.
 constexpr int kSplitRows = 64;  // rows of a 256-thread block
 struct SplitAt {
   int64_t r, kb;
@@ -390,7 +391,9 @@ __device__ __forceinline__ void split_store(const SplitAt& at, int8_t* planes, i
   *reinterpret_cast<uint4*>(planes + ((plane * KB + at.kb) * R_pad + at.r) * kKB + 16 * at.h) =
       make_uint4(w[0], w[1], w[2], w[3]);
 }
-inline dim3 split_grid(int64_t R_pad, int64_t KB) { return dim3((unsigned)((R_pad + kSplitRows - 1) / kSplitRows), (unsigned)KB); }
+inline dim3 split_grid(int64_t R_pad, int64_t KB) {
+  return dim3((unsigned)((R_pad + kSplitRows - 1) / kSplitRows), (unsigned)KB);
+}
 
 // A contraction's tiles come in groups, the query column tiles of one row tile of one plane, which read the same
 // database rows.  Group g goes to XCD g mod 8, so that its tiles share those rows in one L2 while all XCDs work on one

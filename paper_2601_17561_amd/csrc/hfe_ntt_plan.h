@@ -27,7 +27,9 @@ constexpr int kRegLogMin = 9, kRegLogMax = 14;
 
 // The bit-reversed point that index i (r TH + t) of the transform domain holds, in by_ntt's order (acc = false) or
 // by_ntt_acc's, and the index of a point.
-__host__ __device__ constexpr int ntt_e(int logn, bool acc) { return acc && logn >= 13 ? 4 : acc && (logn == 10 || logn == 11) ? 3 : ntt_def_e(logn); }
+__host__ __device__ constexpr int ntt_e(int logn, bool acc) {
+  return acc && logn >= 13 ? 4 : acc && (logn == 10 || logn == 11) ? 3 : ntt_def_e(logn);
+}
 __host__ __device__ inline int ntt_point(int logn, bool acc, int i) {
   if (logn < kRegLogMin || logn > kRegLogMax) return i;
   const int e = ntt_e(logn, acc), lt = logn - e;

@@ -629,7 +629,8 @@ k_gemm_i8_batched(BatchGemmArgs a) {
   const int n = a.hdr->n;
   // Tiles are claimed in order from one counter per XCD (workgroup b runs on XCD b mod 8), so
   // the workgroups of an XCD always work on a contiguous window of tiles that share database
-  // and query blocks in L2, however unevenly tiles finish.  The claim is passed to the workgroup through the first LDS word, which no tile uses between tiles.
+  // and query blocks in L2, however unevenly tiles finish.  The claim is passed to the workgroup
+  // through the first LDS word, which no tile uses between tiles.
   const int xcd = blockIdx.x % kXcds;
   const int64_t per_xcd = a.hdr->total_tiles / kXcds;
   for (;;) {
