@@ -183,3 +183,17 @@ def test_few_columns_of_the_digit_form_equal_the_small_moduli(cols):
     r = H.hfe_ccmm(db, q, 0, d1, H.HFE_FORM_I8_MFMA)
     assert np.array_equal(H.hfe_export(r, 0), H.hfe_export(H.hfe_ccmm(db, q, 0, d1, H.HFE_FORM_RNS_I8), 0))
     _check(keys, r, mq, mdb, "all rows")
+
+
+# the digits' runs of 1, 4 and 8 coefficients, ratios of 8 and above, and polynomials split over several blocks
+@pytest.mark.parametrize("log_n_q,log_n_t", [(7, 7), (7, 9), (7, 10), (7, 12), (10, 14), (11, 15)])
+def test_format_switch_decrypts_exactly_at_every_ring_ratio(log_n_q, log_n_t):
+    d1, d2 = 40, (1 << log_n_q) + 5
+    rng = np.random.default_rng(700 + log_n_t)
+    mdb, mq = _ternary(rng, d1, d2), _ternary(rng, 2, d2)
+    keys = H.hfe_keygen(H.hfe_default_params(7, log_n_q, 3, d2, d1), 5)
+    _say(f"[gpu-sizes] format switch 2^{log_n_t} to 2^{log_n_q}")
+    db = H.hfe_encrypt_db(keys, torch.from_numpy(mdb).cuda(), 6, H.HFE_FORM_RNS_I8)
+    fk = H.hfe_fs_keygen(keys, 2, log_n_t, 7)
+    q = H.hfe_format_switch(fk, H.hfe_fs_encrypt(fk, torch.from_numpy(mq).cuda(), 8), len(mq))
+    _check(keys, H.hfe_ccmm(db, q, 0, d1, H.HFE_FORM_RNS_I8), mq, mdb, "switched query")
