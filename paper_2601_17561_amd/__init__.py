@@ -328,6 +328,16 @@ def hfe_fs_transmit_count(fk: Handle, d3: int) -> int:
     return int(n.value)
 
 
+def _transmission_ptr(fk: Handle, T, d3: int) -> int:
+    """T's pointer; the library cannot see how long T is, so one below d3 columns' residues is refused here."""
+    torch = _torch()
+    ptr = _dev_ptr(T, torch.int64)
+    need = hfe_fs_transmit_count(fk, d3)
+    if T.numel() < need:
+        raise ValueError(f"T holds {T.numel()} residues, {d3} query columns have {need}")
+    return ptr
+
+
 def hfe_fs_encrypt(fk: Handle, m_q, seed: int, T=None, stream=None):
     """Transmission ciphertexts of M_Q (d3 x d2 int8 GPU tensor): uint64 residues as an int64 GPU tensor,
     layout [prime i <= level][d3 k][a | b][N_T] (flat)."""
@@ -335,16 +345,15 @@ def hfe_fs_encrypt(fk: Handle, m_q, seed: int, T=None, stream=None):
     d3 = m_q.shape[0]
     if T is None:
         T = torch.empty(hfe_fs_transmit_count(fk, d3), dtype=torch.int64, device=m_q.device)
-    _check(_lib.hfe_fs_encrypt(fk.ptr, _dev_ptr(m_q, torch.int8), d3, seed, _dev_ptr(T, torch.int64),
+    _check(_lib.hfe_fs_encrypt(fk.ptr, _dev_ptr(m_q, torch.int8), d3, seed, _transmission_ptr(fk, T, d3),
                                _stream(stream)), "hfe_fs_encrypt")
     return T
 
 
 def hfe_format_switch(fk: Handle, T, d3: int, stream=None) -> Handle:
     """Query ciphertext (for hfe_ccmm) from the transmission ciphertexts T of d3 query columns."""
-    torch = _torch()
     out = _vp()
-    _check(_lib.hfe_format_switch(fk.ptr, _dev_ptr(T, torch.int64), d3, _stream(stream), ctypes.byref(out)),
+    _check(_lib.hfe_format_switch(fk.ptr, _transmission_ptr(fk, T, d3), d3, _stream(stream), ctypes.byref(out)),
            "hfe_format_switch")
     return Handle(out.value, (fk,))
 
