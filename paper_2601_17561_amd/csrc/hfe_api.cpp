@@ -1020,15 +1020,16 @@ static hfe_status chain_ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t ro
   HFE_TRY(W.get((size_t)slots * 2 * planeX, s, &Xd));
   uint16_t* res = nullptr;
   HFE_TRY(W.get(sizeof(uint16_t) * (size_t)slots * d3 * R_out, s, &res));
-  int splits = 1;
-  uint16_t* part = nullptr;
-  split_parts(W, p2_tiles(d3, R_out, tq) * slots, 1, D->KB, (size_t)slots * d3 * R_out, s, &splits, &part);
   if (out_ext) {
     R->outp = out_ext;
   } else if (!C_ext) {
     HFE_TRY(R->out.alloc(sizeof(uint64_t) * (size_t)level * d3 * R_out, s));
     R->outp = R->out.as<uint64_t>();
   }
+  // after the buffers that the call cannot do without
+  int splits = 1;
+  uint16_t* part = nullptr;
+  split_parts(W, p2_tiles(d3, R_out, tq) * slots, 1, D->KB, (size_t)slots * d3 * R_out, s, &splits, &part);
   const bool prof = g_profile.load() != 0 && W.base == nullptr && !C_ext;
   if (prof)
     for (auto& e : R->ev) HFE_LAUNCH(hipEventCreate(&e));
