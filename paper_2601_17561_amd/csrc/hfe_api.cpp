@@ -597,6 +597,20 @@ static P2CrtArgs make_p2_crt_args(const hfe_keys* K, int level, int n) {
   return ra;
 }
 
+// The database errors are the same integers for every modulus: drawn once, into T's row-major copy `spare`, which
+// nothing reads any more, if it holds them, else into `errs`.  Without memory for that (3% of the peak) each modulus'
+// encryption draws them for itself.
+static hfe_status draw_db_errors(const hfe_keys* K, const DevBuf& spare, DevBuf& errs, hipStream_t s, DbEncArgs& a) {
+  if (K->P.log_n_db > (uint32_t)kMaxLogN) return HFE_OK;
+  const size_t need = (size_t)a.K * a.d1;
+  int8_t* e = need <= spare.bytes ? spare.as<int8_t>() : errs.alloc(need, s) == HFE_OK ? errs.as<int8_t>() : nullptr;
+  if (!e) return HFE_OK;
+  HFE_LAUNCH(launch_errors(a.seed, kDbE, a.cdt, a.K, a.d1, e, a.d1, 0, s));
+  a.e = e;
+  a.e_col = a.d1;
+  return HFE_OK;
+}
+
 // The database over the n^2 chain: T through the NTT prime, then for each modulus (query moduli,
 // then the special part's) the encryption with scale P and the split into that modulus' slot of
 // the n^2 planes (special moduli first).  The plain form keeps every modulus' residues.
@@ -647,13 +661,8 @@ static hfe_status chain_encrypt_db_impl(const hfe_keys* K, const int8_t* m_db, i
   a.R = D->R;
   a.k_db = K->k_db;
   a.p = K->cP;
-  // the errors are the same integers for every modulus: drawn once
   DevBuf errs;
-  if (P.log_n_db <= (uint32_t)kMaxLogN) {
-    HFE_TRY(errs.alloc((size_t)D->K * d1, s));
-    HFE_LAUNCH(launch_errors(seed, kDbE, a.cdt, D->K, d1, errs.as<int8_t>(), s));
-    a.e = errs.as<int8_t>();
-  }
+  HFE_TRY(draw_db_errors(K, Trow, errs, s, a));
   for (int i = 0; i < nm; ++i) {
     uint64_t* Di = keep_plain ? D->Dt.as<uint64_t>() + (size_t)i * prime_elems : one.as<uint64_t>();
     HFE_LAUNCH(launch_db_encrypt(a, Di, chain_stream(K->cbase[i]), K->cmod[i], K->tab_db[0].tab,
@@ -724,13 +733,8 @@ static hfe_status encrypt_db_impl(const hfe_keys* K, const int8_t* m_db, int64_t
   a.R = D->R;
   a.k_db = K->k_db;
   a.p = P.p;
-  // the errors are the same integers for every modulus: drawn once
   DevBuf errs;
-  if (P.log_n_db <= (uint32_t)kMaxLogN) {
-    HFE_TRY(errs.alloc((size_t)D->K * d1, s));
-    HFE_LAUNCH(launch_errors(seed, kDbE, a.cdt, D->K, d1, errs.as<int8_t>(), s));
-    a.e = errs.as<int8_t>();
-  }
+  HFE_TRY(draw_db_errors(K, Trow, errs, s, a));
   for (int z = 0; z < np; ++z) {
     uint64_t* Dz = keep_plain ? D->Dt.as<uint64_t>() + (size_t)z * prime_elems : one.as<uint64_t>();
     HFE_LAUNCH(launch_db_encrypt(a, Dz, K->prime_id[z], K->mods[z], K->tab_db[z].tab,
@@ -807,19 +811,17 @@ hfe_status hfe_encrypt(const hfe_keys* keys, const int8_t* m_q, int64_t d3, uint
   a.d2 = P.d2;
   a.K = Q->K;
   a.k = K->k;
-  // the errors are the same integers for every prime: drawn once (the two-pass transforms draw their own)
+  // the errors are the same integers for every prime: drawn once, or, without memory for that, by launch_q_encrypt for
+  // each (the two-pass transforms draw their own)
   DevBuf errs;
-  if (P.log_n_q <= (uint32_t)kMaxLogN) {
-    st = errs.alloc((size_t)d3 * P.d2, s);
-    if (st == HFE_OK) {
-      const hipError_t e = launch_errors(seed, kQE, a.cdt, d3, P.d2, errs.as<int8_t>(), s);
-      if (e != hipSuccess) st = hip_fail(e, "launch_errors");
-    }
-    if (st != HFE_OK) {
+  if (P.log_n_q <= (uint32_t)kMaxLogN && errs.alloc((size_t)d3 * P.d2, s) == HFE_OK) {
+    const hipError_t e = launch_errors(seed, kQE, a.cdt, d3, P.d2, errs.as<int8_t>(), P.d2, 0, s);
+    if (e != hipSuccess) {
       delete Q;
-      return st;
+      return hip_fail(e, "launch_errors");
     }
     a.e = errs.as<int8_t>();
+    a.e_col = P.d2;
   }
   const int dl = delta_log(K, (int)level);
   QEncModuli b;

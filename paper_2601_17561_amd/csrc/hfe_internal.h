@@ -217,8 +217,12 @@ struct DbEncArgs {
   int64_t d1, d2, K, R;
   int k_db;
   uint64_t p;
-  const int8_t* e = nullptr;  // the errors e(i, c), K x d1, the same for every prime (the two-pass transforms of
-                              // larger rings draw their own)
+  // The errors e(i, c), the same for every prime, at e[c e_col + (i << e_shift)].  nullptr: launch_db_encrypt draws them
+  // for its prime into the words that the column's body is then written to, so that they take no memory (the two-pass
+  // transforms of larger rings draw their own).
+  const int8_t* e = nullptr;
+  int64_t e_col = 0;
+  int e_shift = 0;
 };
 // Per prime: columns of D (Dt rows): [a_c (N_DB) | B[:, c] (d1)].
 hipError_t launch_db_encrypt(const DbEncArgs& a, uint64_t* Dt_prime, uint32_t prime_id,
@@ -231,8 +235,10 @@ struct QEncArgs {
   const uint64_t* cdt;
   int64_t d3, d2, K;
   int k;
-  const int8_t* e = nullptr;  // the query errors e(t, c), d3 x d2, the same for every prime (the two-pass
-                              // transforms of larger rings draw their own)
+  // the query errors e(t, c), as the database's: at e[z e_mod + c e_col + (t << e_shift)] for the level's modulus z
+  const int8_t* e = nullptr;
+  int64_t e_mod = 0, e_col = 0;
+  int e_shift = 0;
 };
 // The moduli of a query encryption and of a decryption, the level's in order: stream id, modulus (the table's
 // prime, or n^2 of the chain, whose products go through the table's prime), scale, tables, transformed secrets.
@@ -248,11 +254,11 @@ struct DecModuli {
   NttTab T[HFE_MAX_QPRIMES];
   const uint64_t* s_hat[HFE_MAX_QPRIMES];
 };
-// The Gaussian errors of a stream purpose (sub 0), elements (u, c) with u < per and c < cols, as e[c][u] (|e| <= 19
-// fits int8), two positions from each Philox block.
+// The Gaussian errors of a stream purpose (sub 0), elements (u, c) with u < per and c < cols, to e[c col + (u << shift)]
+// (|e| <= 19 fits int8), two positions from each Philox block.
 hipError_t launch_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
-                         hipStream_t s);
-// XT[level][d3][K]; a.e is needed up to ring degree 2^14.
+                         int64_t col, int shift, hipStream_t s);
+// XT[level][d3][K]
 hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, uint64_t* XT, hipStream_t s);
 
 // The same operations for ring degrees above 2^14 (k_ntt_big.hip): two-pass transforms through

@@ -142,7 +142,7 @@ k_db_encrypt(DbEncArgs A, uint64_t* Dt, uint32_t prime_id, Mod M, NttTab T, cons
   X::fwd(ahat, lds, T);  // signed, uncorrected: below 9.1q
   const double q = T.qd, qinv = T.qinv;
   const uint64_t pm = barrett64(A.p, M.q, M.mu);
-  const int8_t* errs = A.e + c * A.d1;
+  const int8_t* errs = A.e + c * A.e_col;
   const int chunks = ONE ? 1 : (int)((A.d1 + n - 1) / n);
   for (int j = 0; j < chunks; ++j) {
     const uint64_t* w = sdb_hat + (int64_t)j * 2 * n;
@@ -159,7 +159,7 @@ k_db_encrypt(DbEncArgs A, uint64_t* Dt, uint32_t prime_id, Mod M, NttTab T, cons
       if (!X::has(r, n) || v >= left) continue;
       const int64_t i = lo + v;
       const int32_t pl = c < A.d2 ? (int32_t)A.MT[c * A.d1 + i] : A.Tt[(c - A.d2) * A.d1 + i];
-      const int32_t e = errs[i];
+      const int32_t e = (errs + ((lo + X::base(r)) << A.e_shift))[threadIdx.x << A.e_shift];
       if constexpr (CHAIN)  // |p pl| < 2^16 2^31
         col[n + i] = from_signed((int64_t)pm * pl - d2i(x[r]) + e, M.q, M.mu);
       else
@@ -168,11 +168,19 @@ k_db_encrypt(DbEncArgs A, uint64_t* Dt, uint32_t prime_id, Mod M, NttTab T, cons
   }
 }
 
-hipError_t launch_db_encrypt(const DbEncArgs& a, uint64_t* Dt_prime, uint32_t prime_id, const Mod& m,
+hipError_t launch_db_encrypt(const DbEncArgs& args, uint64_t* Dt_prime, uint32_t prime_id, const Mod& m,
                              NttTab tab_db, const uint64_t* sdb_hat_prime, hipStream_t s) {
+  DbEncArgs a = args;
   if (a.K <= 0) return hipSuccess;
   if (tab_db.logn > kMaxLogN) return launch_db_encrypt_big(a, Dt_prime, prime_id, m, tab_db, sdb_hat_prime, s);
-  if (!a.e) return hipErrorInvalidValue;
+  if (!a.e) {  // into the body's words, the low byte of each
+    int8_t* e = reinterpret_cast<int8_t*>(Dt_prime + (1ll << tab_db.logn));
+    a.e = e;
+    a.e_col = a.R * 8;
+    a.e_shift = 3;
+    const hipError_t err = launch_errors(a.seed, kDbE, a.cdt, a.K, a.d1, e, a.e_col, a.e_shift, s);
+    if (err != hipSuccess) return err;
+  }
   const bool chain = m.q != tab_db.q;  // residues mod n^2, products through the table's prime
   const bool one = a.d1 <= (1ll << tab_db.logn);
   return by_ntt(tab_db.logn, [&](auto xc, int block) -> hipError_t {

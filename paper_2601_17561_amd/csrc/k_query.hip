@@ -27,7 +27,7 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
   X::fwd(ahat, lds, T);  // signed, uncorrected: below 9.1q
   const double q = T.qd, qinv = T.qinv, delta = u2d(B.delta[z]);
   const int8_t* m = A.m_q + c * A.d2;
-  const int8_t* errs = A.e + c * A.d2;
+  const int8_t* errs = A.e + z * A.e_mod + c * A.e_col;
   const int j0 = ONE ? (int)blockIdx.z : 0, j1 = ONE ? j0 + 1 : A.k;
   for (int j = j0; j < j1; ++j) {
     const gptr<uint64_t> w = as_global(B.s_hat[z]) + (int64_t)j * 2 * n;
@@ -43,7 +43,7 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
       const int v = X::base(r) + (int)threadIdx.x;
       if (!X::has(r, n) || v >= left) continue;
       const int64_t t = lo + v;
-      const double mv = (double)(int)m[t], e = (double)(int)errs[t];
+      const double mv = (double)(int)m[t], e = (double)(int)(errs + ((lo + X::base(r)) << A.e_shift))[threadIdx.x << A.e_shift];
       if constexpr (CHAIN)
         row[t] = from_signed(d2i(mv * delta - x[r] + e), M.q, M.mu);
       else
@@ -52,30 +52,33 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
   }
 }
 
-// The Gaussians of stream key_e at elements (u, c), u < per, c < cols, as e[c][u]: |e| <= 19 fits int8; two
-// positions from each Philox block.
-__global__ void k_errors(uint64_t seed, uint64_t key_e, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e) {
+// The Gaussians of stream key_e at elements (u, c), u < per, c < cols, to e[c col + (u << shift)]: |e| <= 19 fits int8;
+// two positions from each Philox block.
+__global__ void k_errors(uint64_t seed, uint64_t key_e, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
+                         int64_t col, int shift) {
   const int64_t half = (per + 1) / 2, n = cols * half;
   for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
     const int64_t c = x / half, u = x - c * half;
     int32_t e0, e1;
     gaussian_pair_at(seed, key_e, (uint64_t)u, (uint64_t)c, cdt, e0, e1);
-    e[c * per + 2 * u] = (int8_t)e0;
-    if (2 * u + 1 < per) e[c * per + 2 * u + 1] = (int8_t)e1;
+    int8_t* at = e + c * col + (2 * u << shift);
+    at[0] = (int8_t)e0;
+    if (2 * u + 1 < per) at[(int64_t)1 << shift] = (int8_t)e1;
   }
 }
 
 hipError_t launch_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
-                         hipStream_t s) {
+                         int64_t col, int shift, hipStream_t s) {
   const int64_t n = cols * ((per + 1) / 2);
   if (n <= 0) return hipSuccess;
   const int64_t blocks = (n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192;
   hipLaunchKernelGGL(k_errors, dim3((unsigned)blocks), dim3(256), 0, s, seed, stream_tag(purpose, 0), cdt, cols, per,
-                     e);
+                     e, col, shift);
   return hipGetLastError();
 }
 
-hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, uint64_t* XT, hipStream_t s) {
+hipError_t launch_q_encrypt(const QEncArgs& args, const QEncModuli& b, int level, uint64_t* XT, hipStream_t s) {
+  QEncArgs a = args;
   if (a.d3 <= 0) return hipSuccess;
   if (level < 1 || level > HFE_MAX_QPRIMES) return hipErrorInvalidValue;
   if (b.T[0].logn > kMaxLogN) {
@@ -86,7 +89,17 @@ hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, u
     }
     return hipSuccess;
   }
-  if (!a.e) return hipErrorInvalidValue;
+  if (!a.e) {  // each modulus' into its own body words, the low byte of each
+    a.e = reinterpret_cast<const int8_t*>(XT);
+    a.e_mod = a.d3 * a.K * 8;
+    a.e_col = a.K * 8;
+    a.e_shift = 3;
+    for (int i = 0; i < level; ++i) {
+      const hipError_t e = launch_errors(a.seed, kQE, a.cdt, a.d3, a.d2, reinterpret_cast<int8_t*>(XT + i * a.d3 * a.K),
+                                         a.e_col, a.e_shift, s);
+      if (e != hipSuccess) return e;
+    }
+  }
   const bool chain = b.M[0].q != b.T[0].q;  // residues mod n^2, products through the table's prime
   // up to two workgroups per CU the chunks run side by side (each repeats the mask's draw and transform)
   const bool one = a.k == 1 || a.d3 * level * a.k <= 512;

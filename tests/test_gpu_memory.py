@@ -79,3 +79,43 @@ def test_split_contraction_gives_its_parts_up_without_memory(form):
         r = H.hfe_ccmm(db, q, 0, rows, f)
         assert np.array_equal(H.hfe_export(r, 0), want)
         r.free()
+
+
+# code lengths below three query rings, where the errors lie in a buffer that is free by then, and above
+@pytest.mark.parametrize("d2,spare", [(700, True), (1600, False), (2500, False)])
+@pytest.mark.parametrize("family", ["primes", "chain"])
+def test_database_errors_need_no_memory_of_their_own(family, d2, spare):
+    log_n, d1 = 9, 700
+    m_db = _ternary(np.random.default_rng(12), d1, d2)
+    keys, _ = _keys(family, log_n, d2, d1)
+    forms = H.HFE_FORM_PLAIN_U64 | H.HFE_FORM_P2_I8
+    with _Limited() as free:
+        db = H.hfe_encrypt_db(keys, m_db, 6, forms)
+        want = H.hfe_export(db, 0)
+        db.free()
+    errors = (d2 + (1 << log_n)) * d1
+    _say(f"[memory] enrol {family} d2 {d2}: {free.log}, errors {errors}")
+    assert (errors in free.log) == (not spare)
+    if not spare:
+        with _Limited(free.peak - 1):
+            db = H.hfe_encrypt_db(keys, m_db, 6, forms)
+            assert np.array_equal(H.hfe_export(db, 0), want)
+            db.free()
+
+
+# one column and chunk, several chunks side by side in small calls and one after the other in large ones
+@pytest.mark.parametrize("d2,cols", [(301, 1), (1290, 5), (1290, 200)])
+@pytest.mark.parametrize("family,level", [("primes", 1), ("primes", 3), ("chain", 5)])
+def test_query_errors_need_no_memory_of_their_own(family, level, d2, cols):
+    m_q = _ternary(np.random.default_rng(13), cols, d2)
+    keys, _ = _keys(family, 9, d2, 64)
+    with _Limited() as free:
+        q = H.hfe_encrypt(keys, m_q, level, 7)
+        want = H.hfe_export(q, 0)
+        q.free()
+    _say(f"[memory] encrypt {family} level {level} d2 {d2} columns {cols}: {free.log}")
+    assert cols * d2 in free.log
+    with _Limited(free.peak - 1):
+        q = H.hfe_encrypt(keys, m_q, level, 7)
+        assert np.array_equal(H.hfe_export(q, 0), want)
+        q.free()
