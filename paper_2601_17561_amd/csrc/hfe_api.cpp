@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "hfe_internal.h"
+#include "hfe_split.h"
 
 namespace hfe {
 
@@ -957,9 +958,9 @@ static int device_cus() {
 // The buffer of a split contraction's parts: `splits` times the bytes of one result (*part).  One part, and no buffer,
 // when the workspace is a fixed region, whose capacity decides what it accepts, or when the memory is not there.
 template <class T>
-static void split_parts(Workspace& W, int64_t tiles, int wgs_per_cu, int64_t KB, size_t elems, hipStream_t s,
-                        int* splits, T** part) {
-  *splits = W.base ? 1 : gemm_splits(tiles, (int64_t)device_cus() * wgs_per_cu, KB);
+static void split_parts(Workspace& W, int64_t tiles, int edge, int64_t KB, size_t elems, hipStream_t s, int* splits,
+                        T** part) {
+  *splits = W.base ? 1 : gemm_splits(tiles, device_cus(), KB, edge, sizeof(T) * elems);
   if (*splits > 1 && W.get(sizeof(T) * elems * (size_t)*splits, s, part) != HFE_OK) *splits = 1;
 }
 static AddPartsArgs add_parts_args(int planes, int splits, int64_t n) {
@@ -1031,7 +1032,7 @@ static hfe_status chain_ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t ro
   // after the buffers that the call cannot do without
   int splits = 1;
   uint16_t* part = nullptr;
-  split_parts(W, p2_tiles(d3, R_out, tq) * slots, 1, D->KB, (size_t)slots * d3 * R_out, s, &splits, &part);
+  split_parts(W, p2_tiles(d3, R_out, tq) * slots, edge_p2(d3), D->KB, (size_t)slots * d3 * R_out, s, &splits, &part);
   const bool prof = g_profile.load() != 0 && W.base == nullptr && !C_ext;
   if (prof)
     for (auto& e : R->ev) HFE_LAUNCH(hipEventCreate(&e));
@@ -1172,8 +1173,7 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     HFE_TRY(W.get((size_t)nz * n * d3 * R_out, s, &res));
     int splits = 1;
     uint8_t* part = nullptr;
-    split_parts(W, rns_tiles(d3, R_out, tq) * n * nz, rns_wgs_per_cu(tq), D->KB, (size_t)nz * n * d3 * R_out, s,
-                &splits, &part);
+    split_parts(W, rns_tiles(d3, R_out, tq) * n * nz, edge_rns(d3), D->KB, (size_t)nz * n * d3 * R_out, s, &splits, &part);
     HFE_LAUNCH(launch_lift_rns(Qc->XT.as<uint64_t>(), d3, D->K, D->KB, d3_pad, la, n, Xd, s));
     RnsGemmArgs rg;
     std::memset(&rg, 0, sizeof(rg));
@@ -1221,7 +1221,7 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     HFE_TRY(W.get(sizeof(uint16_t) * (size_t)nz * n * d3 * R_out, s, &res));
     int splits = 1;
     uint16_t* part = nullptr;
-    split_parts(W, p2_tiles(d3, R_out, tq) * n * nz, 1, D->KB, (size_t)nz * n * d3 * R_out, s, &splits, &part);
+    split_parts(W, p2_tiles(d3, R_out, tq) * n * nz, edge_p2(d3), D->KB, (size_t)nz * n * d3 * R_out, s, &splits, &part);
     HFE_LAUNCH(launch_lift_p2(Qc->XT.as<uint64_t>(), d3, D->K, D->KB, d3_pad, la, n, Xd, s));
     P2GemmArgs pg;
     std::memset(&pg, 0, sizeof(pg));
@@ -1269,7 +1269,7 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     // 6.3 TB/s, against 2.86); batches have their problems' columns side by side
     const int variant = pick_i8_variant(level, d3, d3 <= 32 ? i8_narrow_variant() : kDefaultI8Variant);
     const int64_t br = i8_variant_tile_rows(variant), bq = i8_variant_tile_cols(variant);
-    split_parts(W, ((R_out + br - 1) / br) * ((d3 + bq - 1) / bq) * nz, i8_variant_wgs_per_cu(variant), D->KB,
+    split_parts(W, ((R_out + br - 1) / br) * ((d3 + bq - 1) / bq) * nz, edge_i8(d3), D->KB,
                 (size_t)nz * d3 * R_out, s, &g.splits, &g.part);
     HFE_LAUNCH(launch_lift(Qc->XT.as<uint64_t>(), d3, D->K, D->KB, g.d3_pad, la, nullptr, Xd, s));
     for (int z = 0; z < nz; ++z) {

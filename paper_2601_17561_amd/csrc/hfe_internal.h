@@ -309,7 +309,7 @@ struct RnsGemmArgs {
   int32_t m[kRnsMaxMods];
   uint32_t magic[kRnsMaxMods];                 // ceil(2^32 / m): x mod m by multiply-high, x < 2^24
   uint8_t* res;                                // [splits][nz][n_mod][d3][R_out], residues < m_j <= 256
-  int splits;                                  // parts of the K-blocks, see gemm_splits
+  int splits;                                  // parts of the K-blocks, see hfe_split.h
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
@@ -348,7 +348,7 @@ struct P2GemmArgs {
   int32_t n[kP2ArgBases], m[kP2ArgBases];      // base j: n_j and n_j^2
   double rn[kP2ArgBases], rm[kP2ArgBases];     // RN(1 / n_j), RN(1 / n_j^2)
   uint16_t* res;                               // [splits][nz][n_bases][d3][R_out], residues < n^2
-  int splits;                                  // parts of the K-blocks, see gemm_splits
+  int splits;                                  // parts of the K-blocks, see hfe_split.h
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;  // d3_pad a multiple of the query tile width
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
@@ -483,13 +483,9 @@ struct GemmArgs {
   uint64_t* C[kMaxPrimes];
   Mod mod[kMaxPrimes];
   int64_t K, KB, R_db, R_pad, n_db, row0, rows, R_out, d3, d3_pad;
-  int splits;                                  // parts of the K-blocks, see gemm_splits
+  int splits;                                  // parts of the K-blocks, see hfe_split.h
   uint64_t* part;                              // [splits][nz][d3][R_out] when splits > 1
 };
-// Parts to cut the K-blocks of a contraction into when its `tiles` workgroups do not fill the chip's `slots`
-// resident ones, or leave a last wave nearly empty: each part's workgroups give residues of their own, and one
-// pass adds them (launch_add_parts).
-int gemm_splits(int64_t tiles, int64_t slots, int64_t KB);
 // Launch grid of `groups` groups of n_ct tiles (xcd_tile), in rows of a multiple of 8.
 inline dim3 xcd_grid(int64_t groups, int64_t n_ct) {
   const int64_t rest = groups % kXcds * n_ct;

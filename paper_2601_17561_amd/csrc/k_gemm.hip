@@ -707,20 +707,6 @@ hipError_t launch_gemm_i8(const GemmArgs& g, int variant, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Splitting pays where it shortens the longest chain of K-blocks a CU works through, ceil(tiles / slots) of them
-// whole: the fewest parts within 15% of the shortest (each part costs a prologue and an epilogue), of at least 16
-// K-blocks.  Measured, contraction + sum of the parts: 4 columns, 4,352 rows, K = 5,120 (68 workgroups of the digit
-// tile) 168 -> 71 + 5 us in 3 parts; 48 columns, 4,896 rows, K = 7,563 (77) 288 -> 129 + 5 us in 3; the n^2 tile at a
-// nearly empty last wave 1,032 -> 937 + 27 us; the RNS tile, which streams more bytes per product, 85 -> 75 + 5 us.
-int gemm_splits(int64_t tiles, int64_t slots, int64_t KB) {
-  if (tiles <= 0 || slots <= 0) return 1;
-  auto cost = [&](int64_t s) { return (double)((tiles * s + slots - 1) / slots) / (double)s; };
-  int best = 1;
-  for (int s = 2; s <= 16 && s * 16 <= KB; ++s)
-    if (cost(s) < 0.85 * cost(best)) best = s;
-  return best;
-}
-
 template <class T>
 __global__ void __launch_bounds__(256) k_add_parts(AddPartsArgs a, const T* part, T* out) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -6,6 +6,7 @@
 
 #include "../../paper_2601_17561_amd/csrc/hfe_exact.h"
 #include "../../paper_2601_17561_amd/csrc/hfe_slots.h"
+#include "../../paper_2601_17561_amd/csrc/hfe_split.h"
 
 using namespace hfe;
 
@@ -15,6 +16,12 @@ static constexpr P2BaseConsts kP2 = make_p2_base_consts();
 #include "../../paper_2601_17561_amd/csrc/hfe_ntt_plan.h"
 
 extern "C" {
+
+// The parts of a contraction of form 0 (digit), 1 (n^2) or 2 (RNS).
+int xc_gemm_splits(int64_t tiles, int64_t cus, int64_t KB, int64_t cols, int form, int64_t bytes) {
+  const int edge = form == 0 ? hfe::edge_i8(cols) : form == 1 ? hfe::edge_p2(cols) : hfe::edge_rns(cols);
+  return hfe::gemm_splits(tiles, cus, KB, edge, (size_t)bytes);
+}
 
 // signed64_mod of x[i] mod q.
 void xc_signed64_mod(const int64_t* x, int64_t n, uint64_t q, double* out) {
