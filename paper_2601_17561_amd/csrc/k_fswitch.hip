@@ -41,6 +41,12 @@ __device__ __forceinline__ int64_t xcd_item(int64_t b, int64_t G) {
 }
 static unsigned xcd_grid(int64_t G) { return (unsigned)(((G + 7) / 8) * 8); }
 
+// acc + x w with the centered product (|x| <= 16q): acc stays an exact integer, below (1/2 + 2^-11) q
+// times the number of terms (at most 4096 here) in magnitude.
+__device__ __forceinline__ double mac_c(double acc, double x, double w, double q, double qinv) {
+  return acc + mulmod_c_d(x, w, q, qinv);
+}
+
 // ------------------------------------------------------------------ ring-switching keys
 // Coefficients of K~_r for slot z, digit i: the mask k_i (stream RkA of slot z, element (t, i)) and
 // g_i s_T + e_i (stream RkE, element (t, i)) at t = rho u' + src, src = 0 for r = 0 and rho - r
@@ -178,15 +184,30 @@ hipError_t launch_fs_ck_finish(const FsConsts& C, const uint64_t* coef_hat, cons
 // part c' of the product is sum_{r <= c'} S_r A_{c'-r} + Y sum_{r > c'} S_r A_{c'+rho-r}.
 // T layout: [i <= l][col][a | b][N_T].
 
-// Workgroup (col, i rho + r): draws part r of a, writes its coefficients to T, and its transform.
+// Column, prime and part of this workgroup, or false: the parts of one column and prime run together on one XCD, whose L2
+// then holds what they share (the transforms of a's parts and of s_T's, and the lines of T, where each part has
+// every rho-th coefficient).
+__device__ __forceinline__ bool tx_part(const FsConsts& C, int64_t ncols, int64_t& col, int& i, int& part) {
+  const int64_t per = (int64_t)(C.level + 1) * C.rho, G = ncols * per;
+  const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, f = xcd_item(b, G);
+  if (b >= (G + 7) / 8 * 8 || f >= G) return false;
+  col = f / per;
+  const int ip = (int)(f - col * per);
+  i = ip / C.rho;
+  part = ip - i * C.rho;
+  return true;
+}
+
+// Workgroup (col, i, r): draws part r of a, writes its coefficients to T, and its transform.
 template <class X>
 __global__ void __launch_bounds__(X::MAXT) __attribute__((amdgpu_waves_per_eu(ntt_waves(X::E, 1), ntt_waves(X::E, 1))))
 k_fs_tx_a(FsConsts C, uint64_t seed, int64_t ncols, double* Ahat, uint64_t* T) {
   extern __shared__ double lds[];
   const int nq = 1 << C.logn_q;
   const int64_t nt = (int64_t)nq * C.rho;
-  const int64_t col = blockIdx.x;
-  const int i = blockIdx.y / C.rho, p = blockIdx.y - i * C.rho;
+  int64_t col;
+  int i, p;
+  if (!tx_part(C, ncols, col, i, p)) return;
   const Mod& M = C.mod[i];
   uint64_t* a = T + ((size_t)i * ncols + col) * 2 * nt;
   double x[X::E];
@@ -208,7 +229,10 @@ k_fs_tx_a(FsConsts C, uint64_t seed, int64_t ncols, double* Ahat, uint64_t* T) {
       (o + X::base(r))[threadIdx.x] = residue_of_c(reduce_c_d(x[r], tab.qd, tab.qinv), tab.qd);
 }
 
-// Workgroup (col, i rho + c'): part c' of s_T a, then b at the coefficients rho u + c'.
+// Workgroup (col, i, c'): part c' of s_T a, then b at the coefficients rho u + c'.  A term's loads for all of a thread's
+// values are issued together, the terms beyond c' first, whose sum takes the factor Y; sums are signed (mac_c).  Bound by
+// the operands' way from L2: 56 columns of 2^16 in 64 parts of 2^10, two chunks each, 3.46 ms with a value's terms one
+// after the other and a workgroup's columns over all XCDs, now 2.07; 113 columns in parts of 2^12 2.38 and 1.24.
 template <class X>
 __global__ void __launch_bounds__(X::MAXT) __attribute__((amdgpu_waves_per_eu(ntt_waves(X::E, 1), ntt_waves(X::E, 1))))
 k_fs_tx_b(FsConsts C, uint64_t seed, const int8_t* m_q, int64_t ncols, const uint64_t* st_hat,
@@ -216,29 +240,35 @@ k_fs_tx_b(FsConsts C, uint64_t seed, const int8_t* m_q, int64_t ncols, const uin
   extern __shared__ double lds[];
   const int nq = 1 << C.logn_q;
   const int64_t nt = (int64_t)nq * C.rho;
-  const int64_t col = blockIdx.x;
-  const int i = blockIdx.y / C.rho, cp = blockIdx.y - i * C.rho;
+  int64_t col;
+  int i, cp;
+  if (!tx_part(C, ncols, col, i, cp)) return;
   const double q = C.zd[i], qinv = C.zinv[i];
   const double* A = Ahat + ((size_t)col * (C.level + 1) + i) * C.rho * nq;
   const uint64_t* S = st_hat + (size_t)i * C.rho * nq;
   double acc[X::E];
 #pragma unroll
-  for (int k = 0; k < X::E; ++k) {
-    acc[k] = 0.0;
-    if (!X::has(k, nq)) continue;
-    const int v = X::base(k) + (int)threadIdx.x;
-    double lo = 0.0, hi = 0.0;
-    for (int r = 0; r < C.rho; ++r) {
-      const bool wrap = r > cp;
-      const int src = wrap ? cp + C.rho - r : cp - r;
-      const double pr = mulmod_d(u2d(S[(size_t)r * nq + v]), A[(size_t)src * nq + v], q, qinv);
-      if (wrap)
-        hi = addmod_d(hi, pr, q);
-      else
-        lo = addmod_d(lo, pr, q);
+  for (int k = 0; k < X::E; ++k) acc[k] = 0.0;
+  auto add = [&](int r, int src) {
+    const gptr<uint64_t> sp = as_global(S + (size_t)r * nq);
+    const gptr<double> ap = as_global(A + (size_t)src * nq);
+    double x[X::E], w[X::E];
+#pragma unroll
+    for (int k = 0; k < X::E; ++k) {
+      x[k] = X::has(k, nq) ? (ap + X::base(k))[threadIdx.x] : 0.0;
+      w[k] = X::has(k, nq) ? u2d((sp + X::base(k))[threadIdx.x]) : 0.0;
     }
-    acc[k] = addmod_d(lo, mulmod_d(hi, u2d(y_hat[(size_t)i * nq + v]), q, qinv), q);
+#pragma unroll
+    for (int k = 0; k < X::E; ++k) acc[k] = mac_c(acc[k], x[k], w[k], q, qinv);
+  };
+  for (int r = cp + 1; r < C.rho; ++r) add(r, cp + C.rho - r);
+  if (cp + 1 < C.rho) {
+    const gptr<uint64_t> y = as_global(y_hat + (size_t)i * nq);
+#pragma unroll
+    for (int k = 0; k < X::E; ++k)
+      if (X::has(k, nq)) acc[k] = mulmod_c_d(reduce_c_d(acc[k], q, qinv), u2d((y + X::base(k))[threadIdx.x]), q, qinv);
   }
+  for (int r = 0; r <= cp; ++r) add(r, cp - r);
   X::inv(acc, lds, C.tab[i]);  // centered
   const int64_t c = col / C.k, j = col - c * C.k;
   const double sc = C.scale[i];
@@ -259,7 +289,8 @@ hipError_t launch_fs_tx(const FsConsts& C, uint64_t seed, const int8_t* m_q, int
                         const uint64_t* y_hat, const uint64_t* cdt, double* Ahat, uint64_t* T, hipStream_t s) {
   const int64_t ncols = d3 * C.k;
   if (ncols <= 0) return hipSuccess;
-  const dim3 grid((unsigned)ncols, (unsigned)((C.level + 1) * C.rho));
+  const unsigned wgs = xcd_grid(ncols * (C.level + 1) * C.rho), gx = wgs < (1u << 20) ? wgs : 1u << 20;
+  const dim3 grid(gx, (wgs + gx - 1) / gx);  // rows of a multiple of 8
   return by_ntt_acc(C.logn_q, [&](auto xc, int block) -> hipError_t {
     using X = decltype(xc);
     const size_t lds = sizeof(double) * X::LDS;
@@ -301,12 +332,6 @@ __global__ void __launch_bounds__(256) k_fs_digits(FsConsts C, const uint64_t* T
 
 // The forward transforms take their inputs straight from global memory into registers and leave their outputs
 // there, where the keys multiply; the inverse transforms start from the accumulators.
-
-// acc + x w with the centered product (|x| <= 16q): acc stays an exact integer, below (1/2 + 2^-11) q
-// times the number of terms (at most 4096 here) in magnitude.
-__device__ __forceinline__ double mac_c(double acc, double x, double w, double q, double qinv) {
-  return acc + mulmod_c_d(x, w, q, qinv);
-}
 
 // Inverse transform of the accumulators x (below 2^47 in magnitude), written to out as residues.
 template <class X>
