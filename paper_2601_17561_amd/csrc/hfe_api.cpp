@@ -1420,24 +1420,30 @@ FormShape hfe::form_shape(const hfe_db* D, int form) {
 
 namespace {
 // Byte layout of the descriptor tables of a batch of up to `items` items and `problems` problems
-// (256-byte aligned parts): contraction (per problem), lift (per item), rescale (per item), RNS
-// reconstruction (per problem), RNS contraction (jobs and their segments).
+// (256-byte aligned parts): contraction (per problem; RNS form: jobs and their segments), lift (per item), rescale (per
+// item), reconstruction of the small-modulus forms (per problem).  A plan uploads all of it on every run, so a form has
+// no part that its kernels do not read.
 struct BlobLayout {
   size_t gh, gd, lh, ld, rh, rd, ch, cd, jd, sd, bytes;
-  int max_jobs, max_segs;  // RNS form: at least what any batch needs request by request
-  BlobLayout(int items, int problems) {
+  // RNS form: room for the jobs of 2 items + 1 runs of rows in every prime slot and both tile widths, and at least the
+  // segments that any batch needs request by request
+  int max_jobs = 0, max_segs = 0;
+  BlobLayout(const hfe_db* D, int form, int items, int problems) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+    const bool rns = form == HFE_FORM_RNS_I8;
+    if (rns) {
+      max_jobs = D->keys->n_primes * 4 * (items + 1);
+      max_segs = 10 * (items + problems);
+    }
     gh = 0;
     gd = al(gh + sizeof(BatchHeader));
-    lh = al(gd + sizeof(BatchDesc) * problems);
+    lh = al(gd + (rns ? 0 : sizeof(BatchDesc) * problems));
     ld = al(lh + sizeof(BatchElemHeader));
     rh = al(ld + sizeof(BatchLiftDesc) * items);
     rd = al(rh + sizeof(BatchElemHeader));
     ch = al(rd + sizeof(BatchRescaleDesc) * items);
     cd = al(ch + sizeof(BatchElemHeader));
-    max_jobs = kMaxPrimes * 4 * (items + 1);
-    max_segs = 10 * (items + problems);
-    jd = al(cd + sizeof(BatchCrtDesc) * problems);
+    jd = al(cd + (form == HFE_FORM_I8_MFMA ? 0 : sizeof(BatchCrtDesc) * problems));
     sd = al(jd + sizeof(RnsJob) * max_jobs);
     bytes = al(sd + sizeof(RnsSeg) * max_segs);
   }
@@ -1749,7 +1755,7 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
     const int64_t d3 = P.d3;
     c_off[b] = z.c_elems;
     res_off[b] = z.res_bytes;
-    if (blob) {
+    if (blob && !rns) {
       BatchDesc& g = reinterpret_cast<BatchDesc*>(blob + L.gd)[k];
       std::memset(&g, 0, sizeof(g));
       g.Xd = xd_base + xd_off[P.owner] + P.xc0 * kKB;
@@ -1768,17 +1774,17 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
         g.slot[zz] = zz < level ? zz : K->L;
         g.mod[zz] = K->mods[g.slot[zz]];
       }
-      if (small) {
-        BatchCrtDesc& c = reinterpret_cast<BatchCrtDesc*>(blob + L.cd)[k];
-        std::memset(&c, 0, sizeof(c));
-        c.res = g.res;
-        c.C = g.C;
-        c.n = d3 * R_out[b];
-        c.elem_begin = crt_e;
-        c.nz = nz;
-        c.level = level;
-        c.pslot = K->L;
-      }
+    }
+    if (blob && small) {
+      BatchCrtDesc& c = reinterpret_cast<BatchCrtDesc*>(blob + L.cd)[k];
+      std::memset(&c, 0, sizeof(c));
+      c.res = res_base + res_off[b];
+      c.C = c_base + c_off[b];
+      c.n = d3 * R_out[b];
+      c.elem_begin = crt_e;
+      c.nz = nz;
+      c.level = level;
+      c.pslot = K->L;
     }
     int64_t groups = 0;
     tiles += rns     ? 0  // its jobs' are counted below
@@ -1997,7 +2003,7 @@ hfe_status hfe_ccmm_batched(const hfe_db* db, const hfe_batch_item* items, int32
     return HFE_OK;
   }
   // all problems of one batch use one tile configuration
-  const BlobLayout L(n, max_problems(n));
+  const BlobLayout L(D, form, n, max_problems(n));
   const BatchSizes sz0 = batch_fill(D, items, n, form, 0, nullptr, nullptr, nullptr, nullptr, nullptr, L);
   const int variant = form == HFE_FORM_I8_MFMA ? choose_batch_variant(D, items, n, sz0.max_level, sz0.cols / n) : 0;
   const hfe_keys* K = D->keys;
@@ -2075,7 +2081,7 @@ static hfe_status plan_alloc(const hfe_db* D, int form, int32_t max_items, int64
   P->c_cap = c_cap;
   P->res_cap = res_cap;
   P->out_cap = out_cap;
-  const BlobLayout L(max_items, max_problems(max_items));
+  const BlobLayout L(D, form, max_items, max_problems(max_items));
   P->blob_bytes = L.bytes;
   hfe_status st = P->ws_xd.alloc(P->xd_cap, nullptr);
   if (st == HFE_OK) st = P->ws_c.alloc(sizeof(uint64_t) * P->c_cap, nullptr);
@@ -2152,7 +2158,7 @@ hfe_status hfe_plan_create_for(const hfe_db* db, const hfe_batch_item* items, in
   HFE_TRY(check_plan_form(D, form));
   if (!items || n < 1 || n > kMaxBatch) return fail(HFE_EINVAL, "a batch holds 1 .. 256 items");
   for (int i = 0; i < n; ++i) HFE_TRY(check_item(D, items[i]));
-  const BlobLayout L(n, max_problems(n));
+  const BlobLayout L(D, form, n, max_problems(n));
   const BatchSizes sz = batch_fill(D, items, n, form, 0, nullptr, nullptr, nullptr, nullptr, nullptr, L);
   return plan_alloc(D, form, n, sz.cols, sz.max_level, sz.xd_bytes, sz.c_elems, sz.res_bytes, sz.out_elems, out);
 }
@@ -2167,7 +2173,7 @@ hfe_status hfe_plan_run(hfe_plan* plan, const hfe_batch_item* items, int32_t n, 
     if (static_cast<const hfe_qct*>(items[i].q)->level > P->max_level)
       return fail(HFE_ELEVEL, "item level above the plan's maximum");
   }
-  const BlobLayout L(P->max_items, max_problems(P->max_items));
+  const BlobLayout L(D, P->form, P->max_items, max_problems(P->max_items));
   const BatchSizes sz = batch_fill(D, items, n, P->form, 0, nullptr, nullptr, nullptr, nullptr, nullptr, L);
   const int variant =
       P->form == HFE_FORM_I8_MFMA ? choose_batch_variant(D, items, n, sz.max_level, sz.cols / n) : 0;

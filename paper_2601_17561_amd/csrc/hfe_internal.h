@@ -514,14 +514,14 @@ int i8_variant_tile_rows(int v);
 int i8_variant_tile_cols(int v);
 int i8_variant_wgs_per_cu(int v);  // resident workgroups per CU the configuration is sized for
 
-// Batched contraction: a device-resident table of problems sharing one database.
+// Batched contraction of the digit and n^2 forms: a device-resident table of problems sharing one database.
 // A batch's problems: items with the same level and database row range are merged into one
 // problem (their query columns side by side), so that only a problem, not every item, pads its
 // columns to whole tiles.
 struct BatchDesc {
   const int8_t* Xd;               // [nz][planes][KB][d3_pad][64] query planes of this problem
   uint64_t* C;                    // [nz][d3][R_out] contraction output
-  uint8_t* res;                   // RNS form: [nz][n_mod][d3][R_out] residues by small modulus
+  uint8_t* res;                   // n^2 form: [nz][n_bases][d3][R_out] residues (uint16) by base
   int64_t n_db, row0, R_out, d3;  // output row r < n_db: database row r; r >= n_db: n_db + row0 + (r - n_db)
   int64_t d3_pad;                 // columns of the query planes Xd points into (their row stride)
   int64_t tile_begin;             // first tile slot of this problem in the launch (multiple of 8)
@@ -533,7 +533,7 @@ struct BatchHeader {
   int64_t total_tiles;            // tile slots, multiple of kXcds
   int32_t n, pad_;
   uint32_t next[kXcds];           // tiles claimed per XCD; zero in every uploaded table
-  // RNS and n^2 forms: problems [0, n_wide) use 256-column query tiles (tiles [0, tiles_wide)),
+  // RNS form (jobs) and n^2 form (problems): [0, n_wide) use 256-column query tiles (tiles [0, tiles_wide)),
   // the rest 128-column tiles, claimed by a second launch through next_narrow
   uint32_t next_narrow[kXcds];
   int64_t tiles_wide;
