@@ -1412,7 +1412,7 @@ FormShape hfe::form_shape(const hfe_db* D, int form) {
   f.rns = form == HFE_FORM_RNS_I8;
   f.p2 = form == HFE_FORM_P2_I8;
   f.planes = f.rns ? D->n_rns : f.p2 ? 2 * D->n_p2 : kDigits;
-  f.qpad = f.rns ? kRnsTileQ : f.p2 ? kP2TileQ : kQueryPad;
+  f.qpad = f.rns ? 1 : f.p2 ? kP2TileQ : kQueryPad;  // the RNS form's jobs look their columns up, and read no others
   f.res_bytes = f.rns ? 1 : f.p2 ? 2 : 0;
   f.lift_form = f.rns ? D->n_rns : f.p2 ? -D->n_p2 : 0;
   return f;
@@ -1737,8 +1737,8 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
     if (fs.p2) tq[b] = p2_tile_q(&gr.p[b].d3, &R_out[b], &nzb, 1);
   }
   if (fs.p2) std::stable_partition(ord.begin(), ord.end(), [&](int b) { return tq[b] == 256; });
-  // query planes of the owners: whole tiles, and for an owner that feeds split problems room for
-  // their last tile, which may reach qpad - 1 columns past the owner's columns
+  // query planes of the owners.  Digit and n^2 forms: whole tiles, and for an owner that feeds split problems room for
+  // their last tile, which may reach qpad - 1 columns past the owner's columns.  RNS form: the columns (qpad = 1)
   for (int b = 0; b < np; ++b) {
     const Problem& P = gr.p[b];
     if (P.owner != b) continue;
@@ -1811,7 +1811,7 @@ BatchSizes batch_fill(const hfe_db* D, const hfe_batch_item* items, int n, int f
     const int64_t d3 = Qc->d3;
     const int a = gr.pa[i], bb = gr.pb[i];  // the A problem is the owner of the item's planes
     const int64_t R_item = ndb + items[i].rows;
-    // the owner's last item also writes the padding columns (zeros)
+    // the owner's last item also writes the padding columns (zeros), where the form has any
     const int64_t cols = d3 + (gr.p[a].last_item == i ? d3_pad[a] - (gr.ca[i] + d3) : 0);
     if (blob) {
       BatchLiftDesc& l = reinterpret_cast<BatchLiftDesc*>(blob + L.ld)[i];

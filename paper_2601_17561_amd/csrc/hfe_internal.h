@@ -666,7 +666,7 @@ struct hfe_plan : hfe::HandleBase {
 };
 
 namespace hfe {
-// Batch parameters of an int8 form of a database: int8 planes per prime slot, query column padding,
+// Batch parameters of an int8 form of a database: int8 planes per prime slot, multiple that query columns are padded to,
 // bytes per residue of the small-modulus contraction (0: the contraction writes C itself), and the
 // form code of the query lift (0 digits, n RNS moduli, -n n^2 bases).
 struct FormShape {

@@ -119,3 +119,24 @@ def test_query_errors_need_no_memory_of_their_own(family, level, d2, cols):
         q = H.hfe_encrypt(keys, m_q, level, 7)
         assert np.array_equal(H.hfe_export(q, 0), want)
         q.free()
+
+
+# a plan holds the batch's own query columns: the RNS contraction reads no padding
+def test_rns_plan_holds_its_columns_only():
+    d1, d2, level = 300, 500, 2
+    rng = np.random.default_rng(14)
+    keys = H.hfe_keygen(H.hfe_default_params(6, 6, level, d2, d1), 5)
+    db = H.hfe_encrypt_db(keys, _ternary(rng, d1, d2), 6, H.HFE_FORM_RNS_I8)
+    row = H.hfe_db_bytes(db, H.HFE_FORM_RNS_I8) // ((d1 + 64 + 63) // 64 * 64 + 256)  # every plane of one row
+    items = [(H.hfe_encrypt(keys, _ternary(rng, c, d2), level, 7 + c), r0, rows)
+             for c, r0, rows in ((5, 0, 300), (130, 0, 300), (3, 100, 90))]
+    with _Limited() as free:
+        plan = H.hfe_plan_create_for(db, items, H.HFE_FORM_RNS_I8)
+        _say(f"[memory] plan {free.log}, a column {row}")
+        assert 138 * row in free.log
+        H.hfe_plan_run(plan, items, use_graph=False)
+        for i, (q, row0, rows) in enumerate(items):
+            one = H.hfe_ccmm(db, q, row0, rows, H.HFE_FORM_RNS_I8)
+            assert np.array_equal(H.hfe_export(H.hfe_plan_result(plan, i), 0), H.hfe_export(one, 0))
+            one.free()
+        plan.free()
