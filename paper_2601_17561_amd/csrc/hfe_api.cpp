@@ -1558,9 +1558,8 @@ Grouping group_items(const hfe_batch_item* items, int n) {
 // job of every problem that includes them, whatever its level.  The B rows are cut where the set of problems on a tile
 // of kRnsTileR rows changes, so that rows several problems share are read once and their columns padded once; or each
 // problem keeps a job of its own where that is less work, as with many short ranges that share only a tile's padding.
-// Work: padded rows times padded columns, the narrow tile's 128 counting as 180, since with so few columns it takes the
-// time of reading its rows (16 columns, 30,720 rows: 4.97 ms; 512: 14.2).  Segments come by falling level, so that those
-// of a prime slot are the first of each job.
+// Work: row tiles times RunSlot::work.  Segments come by falling level, so that those of a prime slot are the first of
+// each job.
 struct RowRun {
   int64_t db_row = 0, rows = 0;
   struct Part {
@@ -1624,11 +1623,23 @@ struct RunSlot {
       cols += gr.p[part.p].d3;
     }
   }
-  // the columns of its tiles of width tq: whole 256-column tiles, and a rest of up to 128 in a narrow one
+  // the columns of its tiles of width tq: whole 256-column tiles and a rest of up to 128 in a narrow one, or all in
+  // narrow ones, which share the rows that one alone would read for its few columns, where that is less work (257 to
+  // 384 columns)
   int64_t cols_in(int tq) const {
-    const int64_t rest = cols % kRnsTileQ, narrow = rest <= 128 ? rest : 0;
+    const int64_t rest = cols % kRnsTileQ, mixed = rest <= 128 ? rest : 0;
+    const int64_t narrow = work_of(cols) < work_of(mixed) ? cols : mixed;
     return tq == 128 ? narrow : cols - narrow;
   }
+  // Work of a row tile, in columns of the wide tile, with `narrow` of its columns in narrow tiles: 256 a wide tile, 180
+  // a narrow one alone, since with so few columns it takes the time of reading its rows (16 columns, 30,720 rows: 4.97
+  // ms; 512: 14.2), 140 where several share them (300 columns, 13,097 rows, K = 13,696 in three primes: 1,714 + 1,083 us in a
+  // wide and a narrow tile, 2,636 in three narrow ones).
+  double work_of(int64_t narrow) const {
+    const int64_t n = (narrow + 127) / 128;
+    return 256.0 * ((cols - narrow + kRnsTileQ - 1) / kRnsTileQ) + (n == 1 ? 180.0 : 140.0 * n);
+  }
+  double work() const { return work_of(cols_in(128)); }
 };
 
 // Jobs and segments of a batch into the tables at blob; the tile slots of the 256-column jobs, and of all.
@@ -1646,9 +1657,8 @@ void fill_rns_jobs(const hfe_db* D, const Grouping& gr, int max_level, const std
       for (int slot = 0; slot <= max_level; ++slot) {
         const RunSlot rs(gr, r, slot, slot == max_level);
         if (!rs.n_parts) continue;
-        const int64_t wide = (rs.cols_in(256) + kRnsTileQ - 1) / kRnsTileQ, narrow = rs.cols_in(128) > 0;
-        jobs += (wide > 0) + narrow;
-        cost += (double)((r.rows + kRnsTileR - 1) / kRnsTileR) * (256.0 * wide + 180.0 * narrow);
+        jobs += (rs.cols_in(256) > 0) + (rs.cols_in(128) > 0);
+        cost += (double)((r.rows + kRnsTileR - 1) / kRnsTileR) * rs.work();
       }
     }
     if (jobs > L.max_jobs || segs > L.max_segs) continue;  // request by request always fits
