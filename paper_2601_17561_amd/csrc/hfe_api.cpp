@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "hfe_internal.h"
+#include "hfe_per_device.h"
 #include "hfe_split.h"
 
 namespace hfe {
@@ -942,17 +943,16 @@ struct Workspace {
 }  // extern "C++"
 
 extern "C++" {
+// CUs of the calling thread's device.
 static int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-    else
-      cus = 256;
-  }
-  return cus;
+  static PerDevice cus;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  const int n = cus.get(dev, [](int d) {
+    int v = 0;
+    return d >= 0 && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, d) == hipSuccess ? v : 0;
+  });
+  return n > 0 ? n : 256;
 }
 
 // The buffer of a split contraction's parts: `splits` times the bytes of one result (*part).  One part, and no buffer,

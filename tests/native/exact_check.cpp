@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../paper_2601_17561_amd/csrc/hfe_exact.h"
+#include "../../paper_2601_17561_amd/csrc/hfe_per_device.h"
 #include "../../paper_2601_17561_amd/csrc/hfe_slots.h"
 #include "../../paper_2601_17561_amd/csrc/hfe_split.h"
 
@@ -16,6 +17,19 @@ static constexpr P2BaseConsts kP2 = make_p2_base_consts();
 #include "../../paper_2601_17561_amd/csrc/hfe_ntt_plan.h"
 
 extern "C" {
+
+// The values of the devices dev[0 .. n) in turn, out[i] of dev[i], from a cache over counts[d]; asked[i]: queries so far.
+void xc_per_device(const int32_t* dev, int32_t n, const int32_t* counts, int32_t* out, int32_t* asked) {
+  hfe::PerDevice cache;
+  int queries = 0;
+  for (int i = 0; i < n; ++i) {
+    out[i] = cache.get(dev[i], [&](int d) {
+      ++queries;
+      return d < 0 ? 0 : (int)counts[d];
+    });
+    asked[i] = queries;
+  }
+}
 
 // The parts of a contraction of form 0 (digit), 1 (n^2) or 2 (RNS).
 int xc_gemm_splits(int64_t tiles, int64_t cus, int64_t KB, int64_t cols, int form, int64_t bytes) {

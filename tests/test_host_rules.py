@@ -12,6 +12,10 @@ _i64 = ctypes.c_int64
 _L.xc_gemm_splits.argtypes = [_i64, _i64, _i64, _i64, ctypes.c_int, _i64]
 _L.xc_gemm_splits.restype = ctypes.c_int
 
+_ints = ctypes.POINTER(ctypes.c_int32)
+_L.xc_per_device.argtypes = [_ints, ctypes.c_int32, _ints, _ints, _ints]
+_L.xc_per_device.restype = None
+
 DIGIT, N2, RNS = 0, 1, 2
 TILE = 64 << 10  # bytes of one tile's results, every form
 
@@ -34,3 +38,15 @@ def test_parts_are_few_and_their_buffer_bounded(form, cus):
             s = _L.xc_gemm_splits(tiles, cus, KB, cols, form, tiles * TILE)
             assert 1 <= s <= max(1, KB // 16) and s <= (16 if tiles <= cus else 4)
             assert s == 1 or s * tiles * TILE <= 256 << 20
+
+
+def test_each_device_has_its_own_value_asked_for_once():
+    def call(devs, counts):
+        n, arr = len(devs), lambda v: (ctypes.c_int32 * len(v))(*v)
+        out, asked = arr([0] * n), arr([0] * n)
+        _L.xc_per_device(arr(devs), n, arr(counts), out, asked)
+        return list(out), list(asked)
+
+    assert call([0, 1, 0, 1, 0], [256, 304]) == ([256, 304, 256, 304, 256], [1, 2, 2, 2, 2])
+    assert call([1, 1, -1, -1], [256, 0]) == ([0, 0, 0, 0], [1, 2, 3, 4])  # a failed query is not kept
+    assert call([70, 70], [0] * 70 + [128]) == ([128, 128], [1, 2])        # beyond the table: asked each time
