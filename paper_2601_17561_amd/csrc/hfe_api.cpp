@@ -601,13 +601,17 @@ static P2CrtArgs make_p2_crt_args(const hfe_keys* K, int level, int n) {
 
 // The database errors are the same integers for every modulus: drawn once, into T's row-major copy `spare`, which
 // nothing reads any more, if it holds them, else into `errs`.  Without memory for that (3% of the peak) each modulus'
-// encryption draws them for itself.
+// encryption takes one column of zeros for them, in `spare`, and adds its own afterwards.
 static hfe_status draw_db_errors(const hfe_keys* K, const DevBuf& spare, DevBuf& errs, hipStream_t s, DbEncArgs& a) {
   if (K->P.log_n_db > (uint32_t)kMaxLogN) return HFE_OK;
   const size_t need = (size_t)a.K * a.d1;
-  int8_t* e = need <= spare.bytes ? spare.as<int8_t>() : errs.alloc(need, s) == HFE_OK ? errs.as<int8_t>() : nullptr;
-  if (!e) return HFE_OK;
-  HFE_LAUNCH(launch_errors(a.seed, kDbE, a.cdt, a.K, a.d1, e, a.d1, 0, s));
+  if (need > spare.bytes && errs.alloc(need, s) != HFE_OK) {
+    HFE_LAUNCH(hipMemsetAsync(spare.ptr, 0, (size_t)a.d1, s));
+    a.e = spare.as<int8_t>();
+    return HFE_OK;
+  }
+  int8_t* e = need <= spare.bytes ? spare.as<int8_t>() : errs.as<int8_t>();
+  HFE_LAUNCH(launch_errors(a.seed, kDbE, a.cdt, a.K, a.d1, e, s));
   a.e = e;
   a.e_col = a.d1;
   return HFE_OK;
@@ -813,17 +817,16 @@ hfe_status hfe_encrypt(const hfe_keys* keys, const int8_t* m_q, int64_t d3, uint
   a.d2 = P.d2;
   a.K = Q->K;
   a.k = K->k;
-  // the errors are the same integers for every prime: drawn once, or, without memory for that, by launch_q_encrypt for
-  // each (the two-pass transforms draw their own)
+  // the errors are the same integers for every prime: drawn once, or, without memory for that, added by launch_q_encrypt
+  // to each (the two-pass transforms draw their own)
   DevBuf errs;
   if (P.log_n_q <= (uint32_t)kMaxLogN && errs.alloc((size_t)d3 * P.d2, s) == HFE_OK) {
-    const hipError_t e = launch_errors(seed, kQE, a.cdt, d3, P.d2, errs.as<int8_t>(), P.d2, 0, s);
+    const hipError_t e = launch_errors(seed, kQE, a.cdt, d3, P.d2, errs.as<int8_t>(), s);
     if (e != hipSuccess) {
       delete Q;
       return hip_fail(e, "launch_errors");
     }
     a.e = errs.as<int8_t>();
-    a.e_col = P.d2;
   }
   const int dl = delta_log(K, (int)level);
   QEncModuli b;

@@ -217,12 +217,11 @@ struct DbEncArgs {
   int64_t d1, d2, K, R;
   int k_db;
   uint64_t p;
-  // The errors e(i, c), the same for every prime, at e[c e_col + (i << e_shift)].  nullptr: launch_db_encrypt draws them
-  // for its prime into the words that the column's body is then written to, so that they take no memory (the two-pass
-  // transforms of larger rings draw their own).
+  // The errors e(i, c), the same for every prime, at e[c e_col + i] (the two-pass transforms of larger rings draw their
+  // own).  With e_col = 0 they are zeros, and launch_db_encrypt adds its own to the finished body, so that they take no
+  // memory.
   const int8_t* e = nullptr;
   int64_t e_col = 0;
-  int e_shift = 0;
 };
 // Per prime: columns of D (Dt rows): [a_c (N_DB) | B[:, c] (d1)].
 hipError_t launch_db_encrypt(const DbEncArgs& a, uint64_t* Dt_prime, uint32_t prime_id,
@@ -235,10 +234,9 @@ struct QEncArgs {
   const uint64_t* cdt;
   int64_t d3, d2, K;
   int k;
-  // the query errors e(t, c), as the database's: at e[z e_mod + c e_col + (t << e_shift)] for the level's modulus z
+  // the query errors e(t, c), d3 x d2, the same for every prime; nullptr: launch_q_encrypt adds them afterwards, without
+  // memory for them (the two-pass transforms of larger rings draw their own)
   const int8_t* e = nullptr;
-  int64_t e_mod = 0, e_col = 0;
-  int e_shift = 0;
 };
 // The moduli of a query encryption and of a decryption, the level's in order: stream id, modulus (the table's
 // prime, or n^2 of the chain, whose products go through the table's prime), scale, tables, transformed secrets.
@@ -254,10 +252,13 @@ struct DecModuli {
   NttTab T[HFE_MAX_QPRIMES];
   const uint64_t* s_hat[HFE_MAX_QPRIMES];
 };
-// The Gaussian errors of a stream purpose (sub 0), elements (u, c) with u < per and c < cols, to e[c col + (u << shift)]
-// (|e| <= 19 fits int8), two positions from each Philox block.
+// The Gaussian errors of a stream purpose (sub 0), elements (u, c) with u < per and c < cols, as e[c][u] (|e| <= 19
+// fits int8), two positions from each Philox block.
 hipError_t launch_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
-                         int64_t col, int shift, hipStream_t s);
+                         hipStream_t s);
+// The same errors, less minus[c][u] (ternary; nullptr: zeros), added to the residues x[c col + u] mod q.
+hipError_t launch_add_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per,
+                             const int8_t* minus, uint64_t* x, int64_t col, uint64_t q, hipStream_t s);
 // XT[level][d3][K]
 hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, uint64_t* XT, hipStream_t s);
 

@@ -159,7 +159,7 @@ k_db_encrypt(DbEncArgs A, uint64_t* Dt, uint32_t prime_id, Mod M, NttTab T, cons
       if (!X::has(r, n) || v >= left) continue;
       const int64_t i = lo + v;
       const int32_t pl = c < A.d2 ? (int32_t)A.MT[c * A.d1 + i] : A.Tt[(c - A.d2) * A.d1 + i];
-      const int32_t e = (errs + ((lo + X::base(r)) << A.e_shift))[threadIdx.x << A.e_shift];
+      const int32_t e = errs[i];
       if constexpr (CHAIN)  // |p pl| < 2^16 2^31
         col[n + i] = from_signed((int64_t)pm * pl - d2i(x[r]) + e, M.q, M.mu);
       else
@@ -168,19 +168,11 @@ k_db_encrypt(DbEncArgs A, uint64_t* Dt, uint32_t prime_id, Mod M, NttTab T, cons
   }
 }
 
-hipError_t launch_db_encrypt(const DbEncArgs& args, uint64_t* Dt_prime, uint32_t prime_id, const Mod& m,
+hipError_t launch_db_encrypt(const DbEncArgs& a, uint64_t* Dt_prime, uint32_t prime_id, const Mod& m,
                              NttTab tab_db, const uint64_t* sdb_hat_prime, hipStream_t s) {
-  DbEncArgs a = args;
   if (a.K <= 0) return hipSuccess;
   if (tab_db.logn > kMaxLogN) return launch_db_encrypt_big(a, Dt_prime, prime_id, m, tab_db, sdb_hat_prime, s);
-  if (!a.e) {  // into the body's words, the low byte of each
-    int8_t* e = reinterpret_cast<int8_t*>(Dt_prime + (1ll << tab_db.logn));
-    a.e = e;
-    a.e_col = a.R * 8;
-    a.e_shift = 3;
-    const hipError_t err = launch_errors(a.seed, kDbE, a.cdt, a.K, a.d1, e, a.e_col, a.e_shift, s);
-    if (err != hipSuccess) return err;
-  }
+  if (!a.e) return hipErrorInvalidValue;
   const bool chain = m.q != tab_db.q;  // residues mod n^2, products through the table's prime
   const bool one = a.d1 <= (1ll << tab_db.logn);
   return by_ntt(tab_db.logn, [&](auto xc, int block) -> hipError_t {
@@ -191,7 +183,9 @@ hipError_t launch_db_encrypt(const DbEncArgs& args, uint64_t* Dt_prime, uint32_t
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)a.K), dim3(block), sizeof(double) * X::LDS, s, a, Dt_prime, prime_id, m,
                        tab_db, sdb_hat_prime);
-    return hipGetLastError();
+    e = hipGetLastError();
+    if (e != hipSuccess || a.e_col) return e;
+    return launch_add_errors(a.seed, kDbE, a.cdt, a.K, a.d1, nullptr, Dt_prime + (1ll << tab_db.logn), a.R, m.q, s);
   });
 }
 

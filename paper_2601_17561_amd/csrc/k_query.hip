@@ -27,7 +27,7 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
   X::fwd(ahat, lds, T);  // signed, uncorrected: below 9.1q
   const double q = T.qd, qinv = T.qinv, delta = u2d(B.delta[z]);
   const int8_t* m = A.m_q + c * A.d2;
-  const int8_t* errs = A.e + z * A.e_mod + c * A.e_col;
+  const int8_t* errs = A.e + c * A.d2;
   const int j0 = ONE ? (int)blockIdx.z : 0, j1 = ONE ? j0 + 1 : A.k;
   for (int j = j0; j < j1; ++j) {
     const gptr<uint64_t> w = as_global(B.s_hat[z]) + (int64_t)j * 2 * n;
@@ -43,7 +43,7 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
       const int v = X::base(r) + (int)threadIdx.x;
       if (!X::has(r, n) || v >= left) continue;
       const int64_t t = lo + v;
-      const double mv = (double)(int)m[t], e = (double)(int)(errs + ((lo + X::base(r)) << A.e_shift))[threadIdx.x << A.e_shift];
+      const double mv = (double)(int)m[t], e = (double)(int)errs[t];
       if constexpr (CHAIN)
         row[t] = from_signed(d2i(mv * delta - x[r] + e), M.q, M.mu);
       else
@@ -52,28 +52,53 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
   }
 }
 
-// The Gaussians of stream key_e at elements (u, c), u < per, c < cols, to e[c col + (u << shift)]: |e| <= 19 fits int8;
-// two positions from each Philox block.
-__global__ void k_errors(uint64_t seed, uint64_t key_e, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
-                         int64_t col, int shift) {
+// The Gaussians of stream key_e at elements (u, c), u < per, c < cols, as e[c][u]: |e| <= 19 fits int8; two
+// positions from each Philox block.
+__global__ void k_errors(uint64_t seed, uint64_t key_e, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e) {
   const int64_t half = (per + 1) / 2, n = cols * half;
   for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
     const int64_t c = x / half, u = x - c * half;
     int32_t e0, e1;
     gaussian_pair_at(seed, key_e, (uint64_t)u, (uint64_t)c, cdt, e0, e1);
-    int8_t* at = e + c * col + (2 * u << shift);
-    at[0] = (int8_t)e0;
-    if (2 * u + 1 < per) at[(int64_t)1 << shift] = (int8_t)e1;
+    e[c * per + 2 * u] = (int8_t)e0;
+    if (2 * u + 1 < per) e[c * per + 2 * u + 1] = (int8_t)e1;
   }
 }
 
 hipError_t launch_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per, int8_t* e,
-                         int64_t col, int shift, hipStream_t s) {
+                         hipStream_t s) {
   const int64_t n = cols * ((per + 1) / 2);
   if (n <= 0) return hipSuccess;
   const int64_t blocks = (n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192;
   hipLaunchKernelGGL(k_errors, dim3((unsigned)blocks), dim3(256), 0, s, seed, stream_tag(purpose, 0), cdt, cols, per,
-                     e, col, shift);
+                     e);
+  return hipGetLastError();
+}
+
+// The same Gaussians added to finished residues, less what the encryption had in their place.
+__global__ void k_add_errors(uint64_t seed, uint64_t key_e, const uint64_t* cdt, int64_t cols, int64_t per,
+                             const int8_t* minus, uint64_t* x, int64_t col, int64_t q) {
+  const int64_t half = (per + 1) / 2, n = cols * half;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t c = i / half, u = i - c * half;
+    int32_t e[2];
+    gaussian_pair_at(seed, key_e, (uint64_t)u, (uint64_t)c, cdt, e[0], e[1]);
+    for (int k = 0; k < 2 && 2 * u + k < per; ++k) {
+      const int64_t at = 2 * u + k;
+      int64_t v = (int64_t)x[c * col + at] + e[k] - (minus ? minus[c * per + at] : 0);  // within 20 of [0, q)
+      v = v < 0 ? v + q : v >= q ? v - q : v;
+      x[c * col + at] = (uint64_t)v;
+    }
+  }
+}
+
+hipError_t launch_add_errors(uint64_t seed, uint64_t purpose, const uint64_t* cdt, int64_t cols, int64_t per,
+                             const int8_t* minus, uint64_t* x, int64_t col, uint64_t q, hipStream_t s) {
+  const int64_t n = cols * ((per + 1) / 2);
+  if (n <= 0) return hipSuccess;
+  const int64_t blocks = (n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192;
+  hipLaunchKernelGGL(k_add_errors, dim3((unsigned)blocks), dim3(256), 0, s, seed, stream_tag(purpose, 0), cdt, cols,
+                     per, minus, x, col, (int64_t)q);
   return hipGetLastError();
 }
 
@@ -89,17 +114,8 @@ hipError_t launch_q_encrypt(const QEncArgs& args, const QEncModuli& b, int level
     }
     return hipSuccess;
   }
-  if (!a.e) {  // each modulus' into its own body words, the low byte of each
-    a.e = reinterpret_cast<const int8_t*>(XT);
-    a.e_mod = a.d3 * a.K * 8;
-    a.e_col = a.K * 8;
-    a.e_shift = 3;
-    for (int i = 0; i < level; ++i) {
-      const hipError_t e = launch_errors(a.seed, kQE, a.cdt, a.d3, a.d2, reinterpret_cast<int8_t*>(XT + i * a.d3 * a.K),
-                                         a.e_col, a.e_shift, s);
-      if (e != hipSuccess) return e;
-    }
-  }
+  const bool after = a.e == nullptr;
+  if (after) a.e = a.m_q;  // in the errors' place, of their shape; taken off again where they are added
   const bool chain = b.M[0].q != b.T[0].q;  // residues mod n^2, products through the table's prime
   // up to two workgroups per CU the chunks run side by side (each repeats the mask's draw and transform)
   const bool one = a.k == 1 || a.d3 * level * a.k <= 512;
@@ -111,7 +127,10 @@ hipError_t launch_q_encrypt(const QEncArgs& args, const QEncModuli& b, int level
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)a.d3, (unsigned)level, one ? (unsigned)a.k : 1u), dim3(block),
                        sizeof(double) * X::LDS, s, a, b, XT);
-    return hipGetLastError();
+    e = hipGetLastError();
+    for (int i = 0; after && i < level && e == hipSuccess; ++i)
+      e = launch_add_errors(a.seed, kQE, a.cdt, a.d3, a.d2, a.m_q, XT + i * a.d3 * a.K, a.K, b.M[i].q, s);
+    return e;
   });
 }
 
