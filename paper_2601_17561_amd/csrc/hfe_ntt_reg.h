@@ -297,7 +297,6 @@ struct RegNtt {
   }
 
   // ---- the interface shared with LdsNtt
-  __device__ __forceinline__ static constexpr int threads() { return TH; }
   // whether register r of this thread holds a value, and the offset of register 0 .. E - 1's values from the
   // thread's first
   __device__ __forceinline__ static constexpr bool has(int, int) { return true; }
@@ -334,7 +333,6 @@ struct RegNtt {
 // natural order on both sides; a value is present where its index lies below n).
 struct LdsNtt {
   static constexpr int E = 2, LDS = 256, MAXT = 128;
-  __device__ __forceinline__ static int threads() { return blockDim.x; }
   __device__ __forceinline__ static bool has(int r, int n) { return (int)(threadIdx.x + r * blockDim.x) < n; }
   __device__ __forceinline__ static int base(int r) { return r * blockDim.x; }
   template <bool SM = false>
@@ -390,11 +388,9 @@ constexpr int ntt_waves(int E, int polys) {
 // of 56 columns at 2^10 50 and 36, 32 and 17 (402 columns: 1,007 and 1,059, 62 and 45).  At 2^12 8 values lose (ring
 // switch 96 and 134 us).  The two differ in the order of the transform domain at 2^10, 2^11, 2^13 and 2^14.
 template <class F>
-static hipError_t by_ntt_upto12(int logn, F f) {
+static hipError_t by_ntt_common(int logn, F f) {
   switch (logn) {
     case 9: return f(RegNtt<9>{}, RegNtt<9>::TH);
-    case 10: return f(RegNtt<10>{}, RegNtt<10>::TH);
-    case 11: return f(RegNtt<11>{}, RegNtt<11>::TH);
     case 12: return f(RegNtt<12>{}, RegNtt<12>::TH);
     default: return logn < kRegLogMin ? f(LdsNtt{}, ntt_block(logn)) : hipErrorInvalidValue;
   }
@@ -403,9 +399,11 @@ static hipError_t by_ntt_upto12(int logn, F f) {
 template <class F>
 static hipError_t by_ntt(int logn, F f) {
   switch (logn) {
+    case 10: return f(RegNtt<10>{}, RegNtt<10>::TH);
+    case 11: return f(RegNtt<11>{}, RegNtt<11>::TH);
     case 13: return f(RegNtt<13>{}, RegNtt<13>::TH);
     case 14: return f(RegNtt<14>{}, RegNtt<14>::TH);
-    default: return by_ntt_upto12(logn, f);
+    default: return by_ntt_common(logn, f);
   }
 }
 template <class F>
@@ -415,7 +413,7 @@ static hipError_t by_ntt_acc(int logn, F f) {
     case 11: return f(RegNtt<11, 3>{}, RegNtt<11, 3>::TH);
     case 13: return f(RegNtt<13, 4>{}, RegNtt<13, 4>::TH);
     case 14: return f(RegNtt<14, 4>{}, RegNtt<14, 4>::TH);
-    default: return by_ntt_upto12(logn, f);
+    default: return by_ntt_common(logn, f);
   }
 }
 
