@@ -288,9 +288,10 @@ hfe_status hfe_plan_result(const hfe_plan* plan, int32_t i, const hfe_rct** view
 /* Autotuner of the int8 contraction tiles: times every tile configuration (see hfe_i8_variants)
  * on this problem (one untimed run each, then reps rounds that time every configuration once,
  * keeping each configuration's best), records the fastest for the
- * problem's (level, query-column bucket; buckets are powers of two from 64) and returns it in
+ * problem's (level, query-column bucket; buckets are powers of two from 32) and returns it in
  * *best.  Later hfe_ccmm calls, batches (by their largest level and mean column count) and plans
- * (at creation) use the entry of their level with the nearest bucket, else the default.  The
+ * (at creation) use the entry of their level with the nearest bucket, else the default; calls of
+ * up to 32 columns and larger ones do not use each other's entries.  The
  * table can be saved and loaded as text ("<level> <column bucket> <configuration name>" per
  * line). */
 hfe_status hfe_autotune(const hfe_db* db, const hfe_qct* q, int64_t row0, int64_t rows, int32_t reps,

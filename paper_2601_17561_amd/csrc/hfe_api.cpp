@@ -3,7 +3,6 @@
 // decryption and the match decision.
 #include <algorithm>
 #include <cstdio>
-#include <map>
 #include <atomic>
 #include <cstring>
 #include <functional>
@@ -15,6 +14,7 @@
 #include "hfe_internal.h"
 #include "hfe_per_device.h"
 #include "hfe_split.h"
+#include "hfe_tuned.h"
 
 namespace hfe {
 
@@ -889,32 +889,14 @@ static RescaleArgs make_rescale_args(const hfe_keys* K, int level) {
   return ra;
 }
 
-// Autotuned tile configurations: (level, d3 bucket) -> variant.
 static std::mutex g_tune_mu;
-static std::map<std::pair<int, int64_t>, int> g_tuned;
-static int64_t d3_bucket(int64_t d3) {
-  int64_t b = 64;
-  while (b < d3) b <<= 1;
-  return b;
-}
-// The forced variant if one is set; else the tuned entry of this level with the nearest column
-// bucket; else `untuned`.
+static TunedTiles g_tuned;
+// The forced variant if one is set; else the tuned one (tuned_tile); else `untuned`.
 static int pick_i8_variant(int level, int64_t d3, int untuned = kDefaultI8Variant) {
   const int forced = g_i8_variant.load();
   if (forced >= 0) return forced;
   std::lock_guard<std::mutex> l(g_tune_mu);
-  const int64_t b = d3_bucket(d3);
-  int best = untuned;
-  int64_t best_dist = -1;
-  for (const auto& kv : g_tuned) {
-    if (kv.first.first != level) continue;
-    const int64_t dist = kv.first.second > b ? kv.first.second / b : b / kv.first.second;
-    if (best_dist < 0 || dist < best_dist) {
-      best_dist = dist;
-      best = kv.second;
-    }
-  }
-  return best;
+  return tuned_tile(g_tuned, level, d3, untuned);
 }
 
 // Device buffers of one call: from the allocator (released in stream order when the workspace goes
@@ -1270,7 +1252,7 @@ static hfe_status ccmm_impl(const hfe_db* D, const hfe_qct* Qc, int64_t row0, in
     // up to 32 columns: the tile of 32, half the products of the default's 64 (4 columns, 4,352 rows, K = 5,120: 44 us
     // against 64; 32 columns, 4,079 rows, K = 6,165 in four primes: 116 against 138; one column, 30,720 rows: 2.05 ms,
     // 6.3 TB/s, against 2.86); batches have their problems' columns side by side
-    const int variant = pick_i8_variant(level, d3, d3 <= 32 ? i8_narrow_variant() : kDefaultI8Variant);
+    const int variant = pick_i8_variant(level, d3, d3 <= kNarrowCols ? i8_narrow_variant() : kDefaultI8Variant);
     const int64_t br = i8_variant_tile_rows(variant), bq = i8_variant_tile_cols(variant);
     split_parts(W, ((R_out + br - 1) / br) * ((d3 + bq - 1) / bq) * nz, edge_i8(d3), D->KB,
                 (size_t)nz * d3 * R_out, s, &g.splits, &g.part);
@@ -1969,12 +1951,15 @@ hfe_status batch_enqueue(const hfe_db* D, const uint8_t* dblob, const BlobLayout
 // Digit tile configuration of a batch: the forced one if set; else, of the configuration tuned for
 // the batch's largest level and mean column count and the default one, the one whose tiles pad the
 // batch's problems least (MFMA work including padded rows and columns); ties go to the tuned one.
+// Requests side by side are a large call, however few columns each has.
 int choose_batch_variant(const hfe_db* D, const hfe_batch_item* items, int n, int max_level, int64_t mean_cols) {
   if (g_i8_variant.load() >= 0) return g_i8_variant.load();
-  const int tuned = pick_i8_variant(max_level, mean_cols);
-  if (tuned == kDefaultI8Variant) return tuned;
   const int64_t ndb = 1ll << D->keys->P.log_n_db;
   const Grouping gr = group_items(items, n);
+  for (const Problem& P : gr.p)
+    if (P.d3 > kNarrowCols) mean_cols = std::max(mean_cols, kNarrowCols + 1);
+  const int tuned = pick_i8_variant(max_level, mean_cols);
+  if (tuned == kDefaultI8Variant) return tuned;
   auto padded = [&](int v) {
     const int64_t br = i8_variant_tile_rows(v), bq = i8_variant_tile_cols(v);
     double w = 0;
@@ -2291,7 +2276,7 @@ hfe_status hfe_autotune(const hfe_db* db, const hfe_qct* q, int64_t row0, int64_
   if (st != HFE_OK) return st;
   {
     std::lock_guard<std::mutex> l(g_tune_mu);
-    g_tuned[{Qc->level, d3_bucket(Qc->d3)}] = best_v;
+    g_tuned[{Qc->level, tune_bucket(Qc->d3)}] = best_v;
   }
   *best = best_v;
   return HFE_OK;
@@ -2348,7 +2333,7 @@ hfe_status hfe_autotune_load(const char* path) {
   int level;
   long long bucket;
   char name[64];
-  std::map<std::pair<int, int64_t>, int> table;
+  TunedTiles table;
   while (std::fscanf(f, "%d %lld %63s", &level, &bucket, name) == 3) {
     int v = -1;
     for (int i = 0; i < i8_variant_count(); ++i)

@@ -8,6 +8,7 @@
 #include "../../paper_2601_17561_amd/csrc/hfe_per_device.h"
 #include "../../paper_2601_17561_amd/csrc/hfe_slots.h"
 #include "../../paper_2601_17561_amd/csrc/hfe_split.h"
+#include "../../paper_2601_17561_amd/csrc/hfe_tuned.h"
 
 using namespace hfe;
 
@@ -30,6 +31,14 @@ void xc_per_device(const int32_t* dev, int32_t n, const int32_t* counts, int32_t
     asked[i] = queries;
   }
 }
+
+// The tile of a call of (level, d3) by a table of n entries, each {level, bucket, tile}; the bucket that a call of d3 tunes.
+int xc_tuned_tile(const int64_t* entries, int32_t n, int level, int64_t d3, int untuned) {
+  hfe::TunedTiles t;
+  for (int i = 0; i < n; ++i) t[{(int)entries[3 * i], entries[3 * i + 1]}] = (int)entries[3 * i + 2];
+  return hfe::tuned_tile(t, level, d3, untuned);
+}
+int64_t xc_tune_bucket(int64_t d3) { return hfe::tune_bucket(d3); }
 
 // The parts of a contraction of form 0 (digit), 1 (n^2) or 2 (RNS).
 int xc_gemm_splits(int64_t tiles, int64_t cus, int64_t KB, int64_t cols, int form, int64_t bytes) {

@@ -15,6 +15,10 @@ _L.xc_gemm_splits.restype = ctypes.c_int
 _ints = ctypes.POINTER(ctypes.c_int32)
 _L.xc_per_device.argtypes = [_ints, ctypes.c_int32, _ints, _ints, _ints]
 _L.xc_per_device.restype = None
+_L.xc_tuned_tile.argtypes = [ctypes.POINTER(_i64), ctypes.c_int32, ctypes.c_int, _i64, ctypes.c_int]
+_L.xc_tuned_tile.restype = ctypes.c_int
+_L.xc_tune_bucket.argtypes = [_i64]
+_L.xc_tune_bucket.restype = _i64
 
 DIGIT, N2, RNS = 0, 1, 2
 TILE = 64 << 10  # bytes of one tile's results, every form
@@ -50,3 +54,17 @@ def test_each_device_has_its_own_value_asked_for_once():
     assert call([0, 1, 0, 1, 0], [256, 304]) == ([256, 304, 256, 304, 256], [1, 2, 2, 2, 2])
     assert call([1, 1, -1, -1], [256, 0]) == ([0, 0, 0, 0], [1, 2, 3, 4])  # a failed query is not kept
     assert call([70, 70], [0] * 70 + [128]) == ([128, 128], [1, 2])        # beyond the table: asked each time
+
+
+# entries (level, bucket, tile): the nearest of the level, and calls of up to 32 columns apart from larger ones
+@pytest.mark.parametrize("table,level,d3,tile", [
+    ([], 3, 16, 99), ([(3, 512, 5)], 3, 16, 99), ([(3, 512, 5)], 3, 33, 5), ([(3, 32, 12)], 3, 16, 12),
+    ([(3, 32, 12)], 3, 33, 99), ([(3, 32, 12), (3, 64, 4), (3, 1024, 5)], 3, 128, 4), ([(2, 64, 4)], 3, 64, 99),
+    ([(3, 0, 4), (3, -8, 4)], 3, 16, 99)])
+def test_tuned_tiles_serve_calls_of_their_kind(table, level, d3, tile):
+    flat = [x for e in table for x in e]
+    assert _L.xc_tuned_tile((_i64 * len(flat))(*flat), len(table), level, d3, 99) == tile
+
+
+def test_tuning_buckets_separate_the_narrow_tile():
+    assert [_L.xc_tune_bucket(d) for d in (1, 32, 33, 64, 65, 512, 513)] == [32, 32, 64, 64, 128, 512, 1024]
