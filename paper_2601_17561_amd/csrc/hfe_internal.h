@@ -18,7 +18,7 @@ constexpr int kMaxPrimes = HFE_MAX_QPRIMES + 1;  // q_0..q_{L-1} and p
 constexpr int kDigits = 5;                       // balanced base-256 digits per 36-bit residue
 constexpr int kKB = 64;                          // K bytes per digit block
 constexpr int kRowPad = 256;                     // extra zero rows after the digit planes
-constexpr int kMaxLogN = 14;                     // ring degrees handled by the LDS-resident NTT
+constexpr int kMaxLogN = 14;                     // ring degrees handled by one workgroup's NTT
 constexpr int kMaxLogNBig = 16;                  // ring degrees handled at all (two-pass NTT above 2^14)
 constexpr int kXcds = 8;                         // accelerator complex dies (one L2 each) of an MI355X
 
@@ -263,7 +263,7 @@ hipError_t launch_add_errors(uint64_t seed, uint64_t purpose, const uint64_t* cd
 hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, uint64_t* XT, hipStream_t s);
 
 // The same operations for ring degrees above 2^14 (k_ntt_big.hip): two-pass transforms through
-// device workspaces taken from the allocator; the LDS-resident launchers forward to these.
+// device workspaces taken from the allocator; the launchers of smaller rings forward to these.
 hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab tab, bool with_shoup,
                               hipStream_t s);
 hipError_t launch_db_T_big(const int8_t* m_db, int64_t d1, int32_t d2, const uint64_t* sconj_hat, int k,
@@ -313,10 +313,11 @@ struct RnsGemmArgs {
   int splits;                                  // parts of the K-blocks, see hfe_split.h
   int64_t KB, R_pad, n_db, row0, R_out, d3, d3_pad;
 };
-// tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
+// tq: query columns of the workgroup tile, 32, 64, 128 or 256 (g.d3_pad a multiple of it)
 hipError_t launch_gemm_rns(const RnsGemmArgs& g, int tq, hipStream_t s);
-// the tile width with less padded work for problems of d3 columns, R_out rows and nz prime slots
-int64_t rns_tiles(int64_t d3, int64_t R_out, int tq);  // workgroups of one (prime, modulus)
+// workgroups of one (prime, modulus)
+int64_t rns_tiles(int64_t d3, int64_t R_out, int tq);
+// the tile width of a call of d3 columns: 32 or 64 if that holds them, else of 128 and 256 the one with less padded work
 int rns_tile_q(int64_t d3);
 struct RnsCrtArgs {
   int n;                                       // moduli in use
@@ -354,8 +355,9 @@ struct P2GemmArgs {
 };
 // tq: query columns of the workgroup tile, 128 or 256 (g.d3_pad a multiple of it)
 hipError_t launch_gemm_p2(const P2GemmArgs& g, int tq, hipStream_t s);
-// the tile width with less padded work for problems of d3 columns, R_out rows and nz prime slots
-int64_t p2_tiles(int64_t d3, int64_t R_out, int tq);  // workgroups of one (slot, base)
+// workgroups of one (slot, base)
+int64_t p2_tiles(int64_t d3, int64_t R_out, int tq);
+// the tile width with less padded work for n problems of d3 columns, R_out rows and nz prime slots
 int p2_tile_q(const int64_t* d3, const int64_t* R_out, const int* nz, int n);
 struct P2CrtArgs {
   int n;                                       // bases in use

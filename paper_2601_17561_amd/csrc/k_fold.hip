@@ -3,7 +3,7 @@
 //
 // Ciphertexts are kept in the NTT domain as uint64 residues, [item][part (b, a)][slot][N], in the order of the
 // register transforms; every transform is one polynomial per workgroup, in registers from its loads to its stores
-// (hfe_ntt_reg.h).  q_1 .. q_3 lie below 2^24, where a product of two residues is exact in a double and the
+// (hfe_ntt_reg.h; ntt_waves names what is spilled at 2^13 and 2^14).  q_1 .. q_3 lie below 2^24, where a product of two residues is exact in a double and the
 // modular product takes four instructions instead of six (the SM variants).  The operations a fold needs are
 // built from a few passes:
 //   k_fold_encode     the slot encoder (plaintext coefficients from integer slot values, hfe_slots.h)

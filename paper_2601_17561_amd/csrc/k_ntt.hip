@@ -8,8 +8,8 @@
 // INTT(NTT(a) . NTT(s)) with the merged negacyclic transforms of Longa and Naehrig (2016):
 // forward Cooley-Tukey with twiddles psi^brv(i) (output in bit-reversed order), inverse
 // Gentleman-Sande with psi^-brv(i) and a final 1/n scale.  One workgroup transforms one
-// polynomial, kept in its registers from the load to the store (hfe_ntt_reg.h; degrees below 2^9 in LDS,
-// LdsNtt).  Residues are held as doubles (exact signed integers) and multiplied mod q with an error-free
+// polynomial, in its registers from the load to the store (hfe_ntt_reg.h, but for what ntt_waves says is spilled at
+// 2^13 and 2^14; degrees below 2^9 in LDS, LdsNtt).  Residues are held as doubles (exact signed integers) and multiplied mod q with an error-free
 // fp64 product (mulmod_c_d): about a third of the integer instructions of a 64-bit Shoup product, at the
 // same issue rate on this chip.  Arrays in the transform domain (the secrets) use the register order.
 #include <type_traits>

@@ -279,7 +279,7 @@ k_gemm_rns(RnsGemmArgs g) {
 // Persistent batched form: workgroups claim the jobs' tiles in order from one counter per XCD, slot t from XCD t mod
 // 8's, as the digit form's batched kernel.  What bounds it is reading the database planes, which is why requests on the
 // same rows share a job: twelve requests of 16 .. 128 columns on shards of 30,720 rows, K = 20,992 read 133 GB request
-// by request (20.2 + 6.3 ms), 70 GB in shared jobs (3.4 + 14.4 ms).
+// by request (20.2 + 6.3 ms), 71 GB in shared jobs (14.0 + 3.9 ms).
 template <int TQ>
 __global__ void __launch_bounds__(64 * RnsCfg<TQ>::NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_gemm_rns_batched(RnsBatchArgs a) {
