@@ -32,14 +32,12 @@ import hfe_synth as S  # noqa: E402
 
 PEAK_I8_TOPS = 5000.0        # MI355X dense int8 MFMA, TOP/s
 # Bytes beyond L2 per launch of the contraction on the share workload (d3 = 512), from rocprofv3
-# FETCH_SIZE + WRITE_SIZE scaled by a 1 GiB copy (profiles/pmc_k_gemm_i8_dma_q128_r128_share_q512.md,
-# profiles/pmc_k_gemm_i8_dma2_w2_share_q512.md, profiles/pmc_k_gemm_i8_dmas_share_q512.md); reported only
-# for the kernels they were taken on, and None for a tile whose kernel changed after its counters were taken.
-MEASURED_TRAFFIC_GB = {"dma_q128_w2": None, "dma_r128_w2": None, "dma2_w2": None,
-                       "dmas_q128_w2": 27.3, "dmas_r128_w2": 27.5,
-                       # the 256-column RNS and n^2 contractions (profiles/pmc_k_gemm_rns_share_q512.md,
-                       # profiles/pmc_k_gemm_p2_share_q512.md), fetch + write
-                       "rns256": None, "p2_256": None}
+# FETCH_SIZE + WRITE_SIZE scaled by a 1 GiB copy (profiles/pmc_contraction_tiles.md); reported only
+# for the kernels they were taken on.
+MEASURED_TRAFFIC_GB = {"dma_q128_w2": 27.7, "dma_r128_w2": 27.7, "dma2_w2": 85.2,
+                       "dmas_q128_w2": 27.2, "dmas_r128_w2": 27.2,
+                       # the 256-column RNS and n^2 contractions
+                       "rns256": 36.4, "p2_256": 43.3}
 KEY_SEED, DB_SEED, Q_SEED, TX_SEED, FOLD_SEED = 11, 22, 33, 44, 55
 # fp64 vector instructions per second of the chip (256 CUs x 64 lanes x 2.4 GHz; the 78.6 TFLOP/s peak
 # counts a fused multiply-add as two) and the fp64 instructions of one exact modular product in the
