@@ -327,13 +327,13 @@ static hfe_status keygen_impl(const hfe_params* params, uint64_t seed, hfe_keys*
     for (int which = 0; which < 2; ++which) {
       const int logn = which == 0 ? (int)P.log_n_db : (int)P.log_n_q;
       NttTabOwner& o = which == 0 ? K->tab_db[z] : K->tab_q[z];
-      ntt_tables_host(q, logn, tab);  // psi | psi_sh | ipsi | ipsi_sh
+      ntt_tables_host(q, logn, tab);  // psi | ipsi
       const size_t n = (size_t)1 << logn;
       // the transforms take the twiddles as doubles (exact: below 2^36)
       std::vector<double> td(2 * n);
       for (size_t i = 0; i < n; ++i) {
         td[i] = (double)tab[i];
-        td[n + i] = (double)tab[2 * n + i];
+        td[n + i] = (double)tab[n + i];
       }
       HFE_TRY(upload(o.buf, td.data(), td.size() * sizeof(double)));
       const double* base = o.buf.as<double>();
@@ -347,41 +347,40 @@ static hfe_status keygen_impl(const hfe_params* params, uint64_t seed, hfe_keys*
     }
   }
 
-  // NTT-domain secrets with Shoup companions: blocks of [n values | n companions]
+  // NTT-domain secrets: blocks of n values
   auto residue = [](int v, uint64_t q) -> uint64_t { return v >= 0 ? (uint64_t)v : q - (uint64_t)(-v); };
   {
-    std::vector<uint64_t> h((size_t)K->n_primes * K->k * 2 * nq, 0);
+    std::vector<uint64_t> h((size_t)K->n_primes * K->k * nq, 0);
     for (int z = 0; z < K->n_primes; ++z)
       for (int j = 0; j < K->k; ++j)
         for (int t = 0; t < nq; ++t)
-          h[(((size_t)z * K->k + j) * 2) * nq + t] = residue(K->s_host[(size_t)j * nq + t], K->primes[z]);
+          h[((size_t)z * K->k + j) * nq + t] = residue(K->s_host[(size_t)j * nq + t], K->primes[z]);
     HFE_TRY(upload(K->s_hat, h.data(), h.size() * 8));
     for (int z = 0; z < K->n_primes; ++z)
-      HFE_LAUNCH(launch_ntt_fwd(K->s_hat.as<uint64_t>() + (size_t)z * K->k * 2 * nq, K->k, 2 * nq,
-                                K->tab_q[z].tab, true, nullptr));
+      HFE_LAUNCH(launch_ntt_fwd(K->s_hat.as<uint64_t>() + (size_t)z * K->k * nq, K->k, nq, K->tab_q[z].tab, nullptr));
   }
   {
     // s~_j(X) = s_j(1/X) = s_0 - sum_{t>=1} s_{n-t} X^t, mod q_0 (T = M_DB S_Q is exact there)
-    std::vector<uint64_t> h((size_t)K->k * 2 * nq, 0);
+    std::vector<uint64_t> h((size_t)K->k * nq, 0);
     for (int j = 0; j < K->k; ++j)
       for (int t = 0; t < nq; ++t) {
         const int v = t == 0 ? K->s_host[(size_t)j * nq] : -K->s_host[(size_t)j * nq + nq - t];
-        h[(size_t)j * 2 * nq + t] = residue(v, K->primes[0]);
+        h[(size_t)j * nq + t] = residue(v, K->primes[0]);
       }
     HFE_TRY(upload(K->sconj_hat, h.data(), h.size() * 8));
-    HFE_LAUNCH(launch_ntt_fwd(K->sconj_hat.as<uint64_t>(), K->k, 2 * nq, K->tab_q[0].tab, true, nullptr));
+    HFE_LAUNCH(launch_ntt_fwd(K->sconj_hat.as<uint64_t>(), K->k, nq, K->tab_q[0].tab, nullptr));
   }
   {
-    std::vector<uint64_t> h((size_t)K->n_primes * K->k_db * 2 * ndb, 0);
+    std::vector<uint64_t> h((size_t)K->n_primes * K->k_db * ndb, 0);
     for (int z = 0; z < K->n_primes; ++z)
       for (int j = 0; j < K->k_db; ++j)
         for (int t = 0; t < ndb; ++t)
-          h[(((size_t)z * K->k_db + j) * 2) * ndb + t] =
+          h[((size_t)z * K->k_db + j) * ndb + t] =
               residue(K->sdb_host[(size_t)j * ndb + t], K->primes[z]);
     HFE_TRY(upload(K->sdb_hat, h.data(), h.size() * 8));
     for (int z = 0; z < K->n_primes; ++z)
-      HFE_LAUNCH(launch_ntt_fwd(K->sdb_hat.as<uint64_t>() + (size_t)z * K->k_db * 2 * ndb, K->k_db,
-                                2 * ndb, K->tab_db[z].tab, true, nullptr));
+      HFE_LAUNCH(launch_ntt_fwd(K->sdb_hat.as<uint64_t>() + (size_t)z * K->k_db * ndb, K->k_db, ndb,
+                                K->tab_db[z].tab, nullptr));
   }
   if (cdt_table_quad_impl(K->cdt_host) != 0) return fail(HFE_EINTERNAL, "CDT table out of range");
   HFE_TRY(upload(K->cdt, K->cdt_host, sizeof(K->cdt_host)));
@@ -744,7 +743,7 @@ static hfe_status encrypt_db_impl(const hfe_keys* K, const int8_t* m_db, int64_t
   for (int z = 0; z < np; ++z) {
     uint64_t* Dz = keep_plain ? D->Dt.as<uint64_t>() + (size_t)z * prime_elems : one.as<uint64_t>();
     HFE_LAUNCH(launch_db_encrypt(a, Dz, K->prime_id[z], K->mods[z], K->tab_db[z].tab,
-                                 K->sdb_hat.as<uint64_t>() + (size_t)z * K->k_db * 2 * ndb, s));
+                                 K->sdb_hat.as<uint64_t>() + (size_t)z * K->k_db * ndb, s));
     if (forms & HFE_FORM_I8_MFMA)
       HFE_LAUNCH(launch_split_db(Dz, D->K, D->R, D->KB, D->R_pad, K->primes[z],
                                  D->digits.as<int8_t>() + (size_t)z * kDigits * plane, s));
@@ -838,7 +837,7 @@ hfe_status hfe_encrypt(const hfe_keys* keys, const int8_t* m_q, int64_t d3, uint
     b.id[i] = ch ? chain_stream(K->cbase[i]) : K->prime_id[i];
     b.delta[i] = pow_mod(2, (uint64_t)dl, b.M[i].q);
     b.T[i] = K->tab_q[ch ? 0 : i].tab;
-    b.s_hat[i] = K->s_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k * 2 * nq;
+    b.s_hat[i] = K->s_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k * nq;
   }
   const hipError_t e = launch_q_encrypt(a, b, (int)level, Q->XT.as<uint64_t>(), s);
   if (e != hipSuccess) {
@@ -2365,7 +2364,7 @@ hfe_status hfe::decrypt_impl(const hfe_keys* K, const hfe_rct* R, double* v, int
   for (int i = 0; i < level; ++i) {
     b.M[i] = ch ? K->cmod[i] : K->mods[i];
     b.T[i] = K->tab_db[ch ? 0 : i].tab;
-    b.s_hat[i] = K->sdb_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k_db * 2 * ndb;
+    b.s_hat[i] = K->sdb_hat.as<uint64_t>() + (size_t)(ch ? 0 : i) * K->k_db * ndb;
   }
   HFE_LAUNCH(launch_dec_products(R->outp, R->d3, R->R_out, R->row0, R->rows, (int)P.log_n_db, b, level, K->k_db, y, s));
   DecodeArgs da;

@@ -136,7 +136,7 @@ hfe_status small_hat(const hfe_foldkeys* F, const std::vector<int64_t>& poly, De
     for (int t = 0; t < n; ++t) h[(size_t)z * n + t] = residue(poly[(size_t)t], F->C.mod[z].q);
   HFE_TRY(put(out, h.data(), h.size() * 8, s));
   for (int z = 0; z < kFoldSlots; ++z)
-    FD_LAUNCH(launch_ntt_fwd(out.as<uint64_t>() + (size_t)z * n, 1, n, F->C.tab[z], false, s));
+    FD_LAUNCH(launch_ntt_fwd(out.as<uint64_t>() + (size_t)z * n, 1, n, F->C.tab[z], s));
   return HFE_OK;
 }
 
@@ -152,7 +152,7 @@ hfe_status make_ks_key(const hfe_foldkeys* F, uint64_t seed, int kappa, int l, c
   FD_LAUNCH(launch_fold_key_coeffs(F->C, seed, kappa, l, zm, F->cdt.as<uint64_t>(), coef.as<uint64_t>(), s));
   for (int sp = 0; sp < nsl; ++sp)
     FD_LAUNCH(launch_ntt_fwd(coef.as<uint64_t>() + (size_t)sp * (l + 1) * 2 * n, (int64_t)(l + 1) * 2, n,
-                             F->C.tab[zm.z[sp]], false, s));
+                             F->C.tab[zm.z[sp]], s));
   KeyGadget gk{};
   const uint64_t p = F->C.mod[5].q;
   for (int sp = 0; sp < nsl; ++sp) {
@@ -192,11 +192,11 @@ hfe_status fold_keygen_impl(int logn, int k, int rho, uint64_t seed, hfe_foldkey
     C.c32[z] = (double)((1ull << 32) % q);
     C.mod[z] = make_mod(q);
     C.pid[z] = z < 5 ? (uint32_t)z : 16u;
-    ntt_tables_host(q, logn, tab);  // psi | psi_sh | ipsi | ipsi_sh
+    ntt_tables_host(q, logn, tab);  // psi | ipsi
     std::vector<double> td(2 * (size_t)n);
     for (int i = 0; i < n; ++i) {
       td[(size_t)i] = (double)tab[(size_t)i];
-      td[(size_t)n + i] = (double)tab[2 * (size_t)n + i];
+      td[(size_t)n + i] = (double)tab[(size_t)n + i];
     }
     NttTabOwner& o = F->tabs[z];
     HFE_TRY(put(o.buf, td.data(), td.size() * sizeof(double), s));

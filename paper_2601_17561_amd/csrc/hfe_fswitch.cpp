@@ -113,7 +113,7 @@ hfe_status fs_keygen_impl(const hfe_keys* K, int l, int log_n_t, uint64_t seed, 
       for (int t = 0; t < nq; ++t) h[(size_t)z * nq + t] = residue(F->sr_host[(size_t)t], C.mod[z].q);
     HFE_TRY(put(sr_hat, h.data(), h.size() * 8));
     for (int z = 0; z < nz; ++z)
-      FS_LAUNCH(launch_ntt_fwd(sr_hat.as<uint64_t>() + (size_t)z * nq, 1, nq, C.tab[z], false, nullptr, true));
+      FS_LAUNCH(launch_ntt_fwd(sr_hat.as<uint64_t>() + (size_t)z * nq, 1, nq, C.tab[z], nullptr, true));
   }
   // ring-switching keys
   {
@@ -122,7 +122,7 @@ hfe_status fs_keygen_impl(const hfe_keys* K, int l, int log_n_t, uint64_t seed, 
     HFE_TRY(coef.alloc(per_z * nz * 8, nullptr));
     FS_LAUNCH(launch_fs_rk_coeffs(C, seed, F->st.as<int8_t>(), F->cdt.as<uint64_t>(), coef.as<uint64_t>(), nullptr));
     for (int z = 0; z < nz; ++z)
-      FS_LAUNCH(launch_ntt_fwd(coef.as<uint64_t>() + z * per_z, (int64_t)(l + 1) * 2 * rho, nq, C.tab[z], false,
+      FS_LAUNCH(launch_ntt_fwd(coef.as<uint64_t>() + z * per_z, (int64_t)(l + 1) * 2 * rho, nq, C.tab[z],
                                nullptr, true));
     HFE_TRY(F->rk.alloc(per_z * nz * 8, nullptr));
     FS_LAUNCH(launch_fs_rk_finish(C, coef.as<uint64_t>(), sr_hat.as<uint64_t>(), F->rk.as<double>(), nullptr));
@@ -135,7 +135,7 @@ hfe_status fs_keygen_impl(const hfe_keys* K, int l, int log_n_t, uint64_t seed, 
     HFE_TRY(coef.alloc(per_z * nz * 8, nullptr));
     FS_LAUNCH(launch_fs_ck_coeffs(C, seed, sr.as<int8_t>(), F->cdt.as<uint64_t>(), coef.as<uint64_t>(), nullptr));
     for (int z = 0; z < nz; ++z)
-      FS_LAUNCH(launch_ntt_fwd(coef.as<uint64_t>() + z * per_z, (int64_t)(l + 1) * k * (1 + k), nq, C.tab[z], false,
+      FS_LAUNCH(launch_ntt_fwd(coef.as<uint64_t>() + z * per_z, (int64_t)(l + 1) * k * (1 + k), nq, C.tab[z],
                                nullptr, true));
     HFE_TRY(F->ck.alloc(per_z * nz * 8, nullptr));
     FS_LAUNCH(launch_fs_ck_finish(C, coef.as<uint64_t>(), K->s_hat.as<uint64_t>(), K->L, F->ck.as<double>(), nullptr));
@@ -150,12 +150,12 @@ hfe_status fs_keygen_impl(const hfe_keys* K, int l, int log_n_t, uint64_t seed, 
           h[((size_t)i * rho + r) * nq + u] = residue(F->st_host[(size_t)u * rho + r], C.mod[i].q);
     HFE_TRY(put(F->st_hat, h.data(), h.size() * 8));
     for (int i = 0; i <= l; ++i)
-      FS_LAUNCH(launch_ntt_fwd(F->st_hat.as<uint64_t>() + (size_t)i * rho * nq, rho, nq, C.tab[i], false, nullptr, true));
+      FS_LAUNCH(launch_ntt_fwd(F->st_hat.as<uint64_t>() + (size_t)i * rho * nq, rho, nq, C.tab[i], nullptr, true));
     std::vector<uint64_t> y((size_t)(l + 1) * nq, 0);
     for (int i = 0; i <= l; ++i) y[(size_t)i * nq + 1] = 1;
     HFE_TRY(put(F->y_hat, y.data(), y.size() * 8));
     for (int i = 0; i <= l; ++i)
-      FS_LAUNCH(launch_ntt_fwd(F->y_hat.as<uint64_t>() + (size_t)i * nq, 1, nq, C.tab[i], false, nullptr, true));
+      FS_LAUNCH(launch_ntt_fwd(F->y_hat.as<uint64_t>() + (size_t)i * nq, 1, nq, C.tab[i], nullptr, true));
   }
   FS_LAUNCH(hipStreamSynchronize(nullptr));
   return HFE_OK;

@@ -123,13 +123,11 @@ void ntt_tables_host(uint64_t q, int logn, std::vector<uint64_t>& out) {
     pw[i] = mulmod_u128(pw[i - 1], psi, q);
     ipw[i] = mulmod_u128(ipw[i - 1], ipsi, q);
   }
-  out.assign(4 * (size_t)n, 0);
+  out.assign(2 * (size_t)n, 0);
   for (uint32_t i = 0; i < n; ++i) {
     const uint32_t b = bit_reverse(i, logn);
     out[i] = pw[b];
-    out[n + i] = shoup(pw[b], q);
-    out[2 * n + i] = ipw[b];
-    out[3 * n + i] = shoup(ipw[b], q);
+    out[n + i] = ipw[b];
   }
 }
 

@@ -119,9 +119,9 @@ struct hfe_keys : hfe::HandleBase {
   std::vector<int8_t> sdb_host;            // k_db x N_DB
   hfe::NttTabOwner tab_db[hfe::kMaxPrimes];   // ring N_DB
   hfe::NttTabOwner tab_q[hfe::kMaxPrimes];    // ring N_Q
-  hfe::DevBuf s_hat;                       // [prime][k][N_Q]: NTT(s_j), then Shoup companions
-  hfe::DevBuf sconj_hat;                   // [k][N_Q] mod q_0: NTT of s~_j(X) = s_j(1/X), + Shoup
-  hfe::DevBuf sdb_hat;                     // [prime][k_db][N_DB]: NTT(s'_j), + Shoup
+  hfe::DevBuf s_hat;                       // [prime][k][N_Q]: NTT(s_j)
+  hfe::DevBuf sconj_hat;                   // [k][N_Q] mod q_0: NTT of s~_j(X) = s_j(1/X)
+  hfe::DevBuf sdb_hat;                     // [prime][k_db][N_DB]: NTT(s'_j)
   hfe::DevBuf cdt;                         // 19 uint64
   uint64_t cdt_host[19];
   // The n^2 modulus chain (Section 6.3): family 1.  The secrets, the tables of primes[0] (the NTT
@@ -195,10 +195,10 @@ int cdt_table_quad_impl(uint64_t* dst);  // hfe_cdt.cpp (quad precision), 0 on s
 // ------------------------------------------------------------------ launchers (.hip files)
 // All launchers enqueue on `s` and return hipGetLastError() of the launch.
 // Negacyclic forward NTT in place of `count` polynomials of length n = 2^tab.logn starting at
-// a + i * stride; with_shoup also writes the Shoup companions at a + i * stride + n.
+// a + i * stride.
 // The result is in the order of the register transforms (hfe_ntt_reg.h): by_ntt's, or by_ntt_acc's with acc_order.
-hipError_t launch_ntt_fwd(uint64_t* a, int64_t count, int64_t stride, NttTab tab, bool with_shoup,
-                          hipStream_t s, bool acc_order = false);
+hipError_t launch_ntt_fwd(uint64_t* a, int64_t count, int64_t stride, NttTab tab, hipStream_t s,
+                          bool acc_order = false);
 
 // T = M_DB S_Q mod q_0, centered to int32 (row-major in Trow, d1 x N_Q scratch) and
 // transposed into Tt[v][i] (N_Q x d1).
@@ -264,8 +264,7 @@ hipError_t launch_q_encrypt(const QEncArgs& a, const QEncModuli& b, int level, u
 
 // The same operations for ring degrees above 2^14 (k_ntt_big.hip): two-pass transforms through
 // device workspaces taken from the allocator; the launchers of smaller rings forward to these.
-hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab tab, bool with_shoup,
-                              hipStream_t s);
+hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab tab, hipStream_t s);
 hipError_t launch_db_T_big(const int8_t* m_db, int64_t d1, int32_t d2, const uint64_t* sconj_hat, int k,
                            NttTab tab_q0, int32_t* Trow, hipStream_t s);
 hipError_t launch_db_encrypt_big(const DbEncArgs& a, uint64_t* Dt_prime, uint32_t prime_id, const Mod& m,
@@ -755,7 +754,7 @@ hipError_t launch_fs_rk_finish(const FsConsts& C, const uint64_t* coef_hat, cons
                                double* rk, hipStream_t s);
 hipError_t launch_fs_ck_coeffs(const FsConsts& C, uint64_t seed, const int8_t* sr, const uint64_t* cdt,
                                uint64_t* out, hipStream_t s);
-// s_hat: the CCMM secrets' transforms, [prime][k][2 N_Q] uint64 (values, then Shoup companions), p at
+// s_hat: the CCMM secrets' transforms, [prime][k][N_Q] uint64, p at
 // prime index p_index.
 hipError_t launch_fs_ck_finish(const FsConsts& C, const uint64_t* coef_hat, const uint64_t* s_hat, int p_index,
                                double* ck, hipStream_t s);

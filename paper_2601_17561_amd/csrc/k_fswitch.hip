@@ -163,7 +163,7 @@ __global__ void k_fs_ck_finish(FsConsts C, const uint64_t* coef_hat, const uint6
       ck[x] = a;
     } else {
       const int slot = z <= C.level ? z : p_index;
-      const uint64_t* sh = s_hat + ((size_t)slot * C.k + (part - 1)) * 2 * nq;
+      const uint64_t* sh = s_hat + ((size_t)slot * C.k + (part - 1)) * nq;
       // the CCMM's secrets are kept in the other order of the transform domain
       const int w2 = ntt_index(C.logn_q, false, ntt_point(C.logn_q, true, v));
       ck[x] = submod_d(to_d(coef_hat[x]), mulmod_d(to_d(sh[w2]), a, q, qinv), q);

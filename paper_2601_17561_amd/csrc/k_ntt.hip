@@ -22,7 +22,7 @@ namespace hfe {
 
 template <class X>
 __global__ void __launch_bounds__(X::MAXT) __attribute__((amdgpu_waves_per_eu(ntt_waves(X::E, 1), ntt_waves(X::E, 1))))
-k_ntt_fwd(uint64_t* a, int64_t stride, NttTab T, int with_shoup) {
+k_ntt_fwd(uint64_t* a, int64_t stride, NttTab T) {
   extern __shared__ double lds[];
   const int n = 1 << T.logn;
   uint64_t* poly = a + (int64_t)blockIdx.x * stride;
@@ -31,23 +31,18 @@ k_ntt_fwd(uint64_t* a, int64_t stride, NttTab T, int with_shoup) {
   X::fwd(x, lds, T);
 #pragma unroll
   for (int r = 0; r < X::E; ++r) {
-    if (!X::has(r, n)) continue;
-    const uint64_t v = d2residue(x[r], T.qd, T.qinv);
-    (poly + X::base(r))[threadIdx.x] = v;
-    if (with_shoup) (poly + n + X::base(r))[threadIdx.x] = shoup_quot(v, T.q);
+    if (X::has(r, n)) (poly + X::base(r))[threadIdx.x] = d2residue(x[r], T.qd, T.qinv);
   }
 }
 
-hipError_t launch_ntt_fwd(uint64_t* a, int64_t count, int64_t stride, NttTab tab, bool with_shoup,
-                          hipStream_t s, bool acc_order) {
+hipError_t launch_ntt_fwd(uint64_t* a, int64_t count, int64_t stride, NttTab tab, hipStream_t s, bool acc_order) {
   if (count <= 0) return hipSuccess;
-  if (tab.logn > kMaxLogN) return launch_ntt_fwd_big(a, count, stride, tab, with_shoup, s);
+  if (tab.logn > kMaxLogN) return launch_ntt_fwd_big(a, count, stride, tab, s);
   auto go = [&](auto xc, int block) -> hipError_t {
     using X = decltype(xc);
     hipError_t e = allow_lds(k_ntt_fwd<X>, sizeof(double) * X::LDS);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ntt_fwd<X>, dim3((unsigned)count), dim3(block), sizeof(double) * X::LDS, s, a, stride, tab,
-                       with_shoup ? 1 : 0);
+    hipLaunchKernelGGL(k_ntt_fwd<X>, dim3((unsigned)count), dim3(block), sizeof(double) * X::LDS, s, a, stride, tab);
     return hipGetLastError();
   };
   return acc_order ? by_ntt_acc(tab.logn, go) : by_ntt(tab.logn, go);
@@ -77,7 +72,7 @@ k_db_T(const int8_t* m_db, int32_t d2, const uint64_t* sconj_hat, int k, NttTab 
       x[r] = X::has(r, n) && v < left ? (double)(int)(m + X::base(r))[threadIdx.x] : 0.0;
     }
     X::fwd(x, lds, T);
-    const uint64_t* w = sconj_hat + (int64_t)j * 2 * n;
+    const uint64_t* w = sconj_hat + (int64_t)j * n;
 #pragma unroll
     for (int r = 0; r < X::E; ++r)
       if (X::has(r, n))
@@ -145,7 +140,7 @@ k_db_encrypt(DbEncArgs A, uint64_t* Dt, uint32_t prime_id, Mod M, NttTab T, cons
   const int8_t* errs = A.e + c * A.e_col;
   const int chunks = ONE ? 1 : (int)((A.d1 + n - 1) / n);
   for (int j = 0; j < chunks; ++j) {
-    const uint64_t* w = sdb_hat + (int64_t)j * 2 * n;
+    const uint64_t* w = sdb_hat + (int64_t)j * n;
     double x[X::E];
 #pragma unroll
     for (int r = 0; r < X::E; ++r)

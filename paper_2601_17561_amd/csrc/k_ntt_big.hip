@@ -217,19 +217,15 @@ static hipError_t ws_alloc(DevBuf& b, size_t bytes, hipStream_t s) {
 // ------------------------------------------------------------------ element-wise kernels
 // grid (ceil(n / 256), columns); element (v, column).
 
-// Secret transforms: W[j] = a[j * stride + v] -> after the transform a[j * stride + v] = W and
-// a[j * stride + n + v] = its Shoup quotient.
+// Secret transforms: W[j] = a[j * stride + v] -> after the transform a[j * stride + v] = W.
 __global__ void k_big_load_u64(const uint64_t* a, int64_t stride, int n, double* W) {
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v < n) W[(int64_t)blockIdx.y * n + v] = (double)a[(int64_t)blockIdx.y * stride + v];
 }
 
-__global__ void k_big_store_hat(const double* W, int n, uint64_t q, uint64_t* a, int64_t stride, int shoup) {
+__global__ void k_big_store_hat(const double* W, int n, uint64_t* a, int64_t stride) {
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const uint64_t x = (uint64_t)W[(int64_t)blockIdx.y * n + v];
-  a[(int64_t)blockIdx.y * stride + v] = x;
-  if (shoup) a[(int64_t)blockIdx.y * stride + n + v] = shoup_quot(x, q);
+  if (v < n) a[(int64_t)blockIdx.y * stride + v] = (uint64_t)W[(int64_t)blockIdx.y * n + v];
 }
 
 // The n^2 modulus chain takes its products through the table's prime q (as the smaller rings
@@ -342,7 +338,7 @@ static dim3 elem_grid(int64_t n, int64_t cols) { return dim3((unsigned)((n + 255
 // ------------------------------------------------------------------ launchers (same contracts as the
 // register-resident ones in k_ntt.hip and k_query.hip, which call these for ring degrees above 2^14)
 
-hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab T, bool with_shoup, hipStream_t s) {
+hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab T, hipStream_t s) {
   const int n = 1 << T.logn;
   const int64_t nb = big_batch(T.logn, count);
   DevBuf W;
@@ -353,8 +349,8 @@ hipError_t launch_ntt_fwd_big(uint64_t* a, int64_t count, int64_t stride, NttTab
     e = hipGetLastError();
     if (e == hipSuccess) e = big_transform(W.as<double>(), cnt, T, true, s);
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_big_store_hat, elem_grid(n, cnt), dim3(256), 0, s, W.as<double>(), n, T.q, a + c0 * stride,
-                         stride, with_shoup ? 1 : 0);
+      hipLaunchKernelGGL(k_big_store_hat, elem_grid(n, cnt), dim3(256), 0, s, W.as<double>(), n, a + c0 * stride,
+                         stride);
       e = hipGetLastError();
     }
   }
@@ -376,7 +372,7 @@ hipError_t launch_db_T_big(const int8_t* m_db, int64_t d1, int32_t d2, const uin
       if (e == hipSuccess) e = big_transform(W.as<double>(), cnt, T, true, s);
       if (e == hipSuccess) {
         hipLaunchKernelGGL(k_big_pointwise, elem_grid(n, cnt), dim3(256), 0, s, W.as<double>(),
-                           sconj_hat + (int64_t)j * 2 * n, n, T, acc.as<double>(), j > 0 ? 1 : 0);
+                           sconj_hat + (int64_t)j * n, n, T, acc.as<double>(), j > 0 ? 1 : 0);
         e = hipGetLastError();
       }
     }
@@ -405,7 +401,7 @@ hipError_t launch_db_encrypt_big(const DbEncArgs& a, uint64_t* Dt, uint32_t prim
     if (e == hipSuccess) e = big_transform(W.as<double>(), cnt, T, true, s);
     for (int j = 0; e == hipSuccess && j < chunks; ++j) {
       hipLaunchKernelGGL(k_big_pointwise, elem_grid(n, cnt), dim3(256), 0, s, W.as<double>(),
-                         sdb_hat + (int64_t)j * 2 * n, n, T, W2.as<double>(), 0);
+                         sdb_hat + (int64_t)j * n, n, T, W2.as<double>(), 0);
       e = hipGetLastError();
       if (e == hipSuccess) e = big_transform(W2.as<double>(), cnt, T, false, s);
       if (e == hipSuccess) {
@@ -434,7 +430,7 @@ hipError_t launch_q_encrypt_big(const QEncArgs& a, uint64_t* XT, uint32_t prime_
     if (e == hipSuccess) e = big_transform(W.as<double>(), cnt, T, true, s);
     for (int j = 0; e == hipSuccess && j < a.k; ++j) {
       hipLaunchKernelGGL(k_big_pointwise, elem_grid(n, cnt), dim3(256), 0, s, W.as<double>(),
-                         s_hat + (int64_t)j * 2 * n, n, T, W2.as<double>(), 0);
+                         s_hat + (int64_t)j * n, n, T, W2.as<double>(), 0);
       e = hipGetLastError();
       if (e == hipSuccess) e = big_transform(W2.as<double>(), cnt, T, false, s);
       if (e == hipSuccess) {
@@ -462,7 +458,7 @@ hipError_t launch_dec_products_big(const uint64_t* out, int64_t d3, int64_t R_ou
     if (e == hipSuccess) e = big_transform(W.as<double>(), cnt, T, true, s);
     for (int j = j0; e == hipSuccess && j <= j1; ++j) {
       hipLaunchKernelGGL(k_big_pointwise, elem_grid(n, cnt), dim3(256), 0, s, W.as<double>(),
-                         sdb_hat + (int64_t)j * 2 * n, n, T, W2.as<double>(), 0);
+                         sdb_hat + (int64_t)j * n, n, T, W2.as<double>(), 0);
       e = hipGetLastError();
       if (e == hipSuccess) e = big_transform(W2.as<double>(), cnt, T, false, s);
       if (e == hipSuccess) {

@@ -30,7 +30,7 @@ k_q_encrypt(QEncArgs A, QEncModuli B, uint64_t* XT) {
   const int8_t* errs = A.e + c * A.d2;
   const int j0 = ONE ? (int)blockIdx.z : 0, j1 = ONE ? j0 + 1 : A.k;
   for (int j = j0; j < j1; ++j) {
-    const gptr<uint64_t> w = as_global(B.s_hat[z]) + (int64_t)j * 2 * n;
+    const gptr<uint64_t> w = as_global(B.s_hat[z]) + (int64_t)j * n;
     double x[X::E];
 #pragma unroll
     for (int r = 0; r < X::E; ++r)
@@ -155,7 +155,7 @@ k_dec_products(const uint64_t* out, int64_t R_out, int64_t row0, int64_t rows, D
   for (int r = 0; r < X::E; ++r) x[r] = X::has(r, n) ? enter_ntt<CHAIN>((ocol + X::base(r))[threadIdx.x], M.q) : 0.0;
   X::fwd(x, lds, T);  // signed, uncorrected: below 9.1q
   const double q = T.qd, qinv = T.qinv;
-  const gptr<uint64_t> w = as_global(B.s_hat[z]) + (int64_t)j * 2 * n;
+  const gptr<uint64_t> w = as_global(B.s_hat[z]) + (int64_t)j * n;
 #pragma unroll
   for (int r = 0; r < X::E; ++r)
     x[r] = X::has(r, n) ? mulc(x[r], u2d((w + X::base(r))[threadIdx.x]), q, qinv) : 0.0;
