@@ -377,7 +377,7 @@ struct LdsNtt {
 // Waves per SIMD that a kernel with `polys` polynomials in registers is built for (512 registers per lane,
 // about 60 beside the polynomials).  With 32 values a thread (2^13, 2^14) that is 4 waves of 128 registers for one
 // polynomial, and the exchange in halves alone keeps 1.5 of it live, so those kernels spill registers at its ends: the
-// fold's lifts 44 to 104, k_q_encrypt 48 to 52 and k_db_encrypt 18 to 20 with one chunk, k_ntt_fwd 32 to 36,
+// fold's lifts 44 to 104, k_q_encrypt 48 to 52 and k_db_encrypt 18 to 20 with one chunk, k_ntt_fwd 8 and 40,
 // k_dec_products 10 to 12.  The kernels with sums beside the transform spill 77 or 78 (k_fold_ks_mac at 2^13 and 2^14),
 // 86 and 116 (k_fs_ring and k_fs_conv at 2^14); all others at most 8.
 constexpr int ntt_waves(int E, int polys) {
