@@ -19,6 +19,7 @@ constexpr size_t kMaxPartBytes = 256u << 20;
 // the measured times; a further part has to shorten it by 5%, about half of which is seen.  K = 8,192 (128 K-blocks):
 //   digit, 52 workgroups, 48 columns: 232 us, in 4 parts 93, in 5 150 (a second round)
 //   RNS, 154 workgroups, 200 columns: 105 us, in 3 parts 141; 286, 16 columns: 143, in 2 129; 256 columns: 231, in 3 300
+//   RNS, 561 workgroups of 76 K-blocks, 1 column: 137 us, in 2 parts 129; 20 columns: 140 and 140; 64: 152 and 167
 //   n^2, 156 workgroups, 128 columns: 180 us, in 3 parts 199; 16 columns: 157 and 151
 // and K = 20,992 (328):
 //   digit, 2.03 rounds: 2.25 ms, in 2 parts 2.10; 4.06 rounds: 3.98 and 3.80; 5.03 rounds: 4.87 and 4.76, in 11, where
